@@ -7,14 +7,12 @@
 //   skip unless q <= q_max (alpha >= 1/255);   falloff G = exp(-q/2) (PHI) or exp(-q^(beta/2)/2) (GEF)
 //   alpha = min(0.99, o G);  t = T (1 - alpha);  stop before compositing when t < 1e-4
 //   C += alpha T rgb;  T = t.
-// Launch shape (gfx950): the forward pass gives a 16x16 tile two wave64s, each owning 8 rows with 2
-// pixels per lane (one column, rows y and y+4): the tile's serial walk is halved, which shortens the tail
-// of the heaviest tiles (3M-splat 1080p frame: 0.27 -> 0.24 ms; four waves with 1 pixel per lane: 0.30 ms).
-// The backward pass, whose issue rate is saturated, keeps one wave per tile with 4 pixels per lane (rows
-// y, y+4, y+8, y+12), so each splat read from LDS is used four times per lane.  Splats are staged 64 at a
-// time into LDS, then every lane reads the batch back as broadcasts.  A wave stops as soon as no lane has a
-// live pixel (ballot); the forward block once neither wave has.  Tiles are dealt to the 8 XCDs in groups of
-// 8 neighbours (see xcd_tile).
+// Launch shape (gfx950): the forward pass gives a 16x16 tile four wave64s, one 8x8 quadrant each with one pixel
+// per lane; a wave skips the splats that cannot reach its quadrant (see raster_forward_kernel).  The backward
+// pass, whose issue rate is saturated on large frames, keeps one wave per tile with 4 pixels per lane (rows
+// y, y+4, y+8, y+12), so each splat read from LDS is used four times per lane.  Records are staged in LDS and
+// read back as broadcasts.  A wave stops as soon as no lane has a live pixel; the forward block once no wave
+// has.  Tiles are dealt to the 8 XCDs in groups of 8 neighbours (see xcd_tile).
 // The backward pass walks each pixel's contributors back to front, recovering the transmittance
 // before splat j as T_j = T_(j+1) / (1 - alpha_j) from the stored final T, so no per-pixel lists are
 // kept.  Per splat, the 4 pixels of a lane are summed in registers and each row of 16 lanes by a DPP
@@ -75,17 +73,68 @@ __device__ __forceinline__ int64_t ordered_tile(int64_t blk, const uint32_t* gro
   return t < tiles ? t : -1;
 }
 
-constexpr int kFwdWaves = 2;                // waves per tile in the forward pass
-constexpr int kFwdPix = 4 / kFwdWaves;      // pixels per lane (one column, rows 4 apart)
-static_assert(kFwdWaves == 2 || kFwdWaves == 4, "waves 0 and 1 stage the records; 16 rows split evenly");
+// Forward pass: one block of four wave64s per 16x16 tile, each wave owning one 8x8 quadrant with one pixel per
+// lane.  What bounds it is the serial walk down a tile's list, not arithmetic, wherever the frame has fewer
+// tiles than the device has room for, and in the last tiles of every frame; most of what a walk meets misses
+// most of the tile (200k splats at 512x512: 12 % of the examined pairs composite).  So
+//   - each wave first tests 64 listed splats against its quadrant, one per lane (box_may_hit), and walks only
+//     those that may reach it (a bit mask in scalar registers);
+//   - it takes them kFwdGroup at a time: their falloffs are independent of one another and overlap, only the
+//     short transmittance recurrence is serial;
+//   - the next kFwdBatch records are loaded while the current ones are composited (two LDS buffers, one
+//     barrier per batch).
+// The arithmetic of a pair, and the order of a pixel's pairs, do not depend on any of this.  Measured against two
+// waves per tile with two pixels per lane, walking every splat: 1k splats at 64x64 102 -> 36 us, 200k at 512x512
+// 363 -> 133, GEF 300k at 801x533 443 -> 329, 1M at 1600x1040 233 -> 189, 3M at 1920x1080 243 -> 229, 5M of heavy
+// overlap 828 -> 666.  Groups of 2: 41, 139, 349, 185, 228, 659 us; one splat at a time with a branch per
+// decision: 51, 169, 478, 251, 304, 905.
+constexpr int kFwdWaves = 4;
+constexpr int kFwdBatch = 128;              // records staged per barrier: threads 0-127 load words 0-7 of
+                                            // one record each, threads 128-255 words 8-11
+constexpr int kFwdGroup = 4;
+static_assert(kFwdBatch * 2 == 64 * kFwdWaves, "half the block per record part");
+
+// Whether a splat's alpha-floor ellipse may reach a pixel centre of the box (dx, dy: mean minus the box's
+// edges).  False only if pair_q exceeds q_max at every pixel of the box: the least q over the box (on an edge
+// unless the mean lies inside; there a quadratic, least at the clamped stationary point) is compared with
+// q_max plus 4e-6 of the largest term magnitude a pixel of the box can have, which covers the binary32
+// rounding of pair_q (5 roundings, 3e-7 of the magnitude) and of this minimum (below 1e-6 of it).
+__device__ __forceinline__ float box_edge(float a, float b, float c, float rc, float e, float lo, float hi) {
+  const float y = fminf(fmaxf(-(b * e) * rc, lo), hi);
+  return __builtin_fmaf(__builtin_fmaf(a, e, 2.f * b * y), e, c * y * y);
+}
+__device__ __forceinline__ bool box_may_hit(float a, float b, float c, float qm, float dxlo, float dxhi, float dylo,
+                                            float dyhi) {
+  if (dxlo <= 0.f && dxhi >= 0.f && dylo <= 0.f && dyhi >= 0.f) return true;
+  const float ra = fast_rcp(a), rc = fast_rcp(c);
+  const float m = fminf(fminf(box_edge(a, b, c, rc, dxlo, dylo, dyhi), box_edge(a, b, c, rc, dxhi, dylo, dyhi)),
+                        fminf(box_edge(c, b, a, ra, dylo, dxlo, dxhi), box_edge(c, b, a, ra, dyhi, dxlo, dxhi)));
+  const float ax = fmaxf(fabsf(dxlo), fabsf(dxhi)), ay = fmaxf(fabsf(dylo), fabsf(dyhi));
+  const float mag = __builtin_fmaf(__builtin_fmaf(a, ax, 2.f * fabsf(b) * ay), ax, c * ay * ay);
+  return !(m > __builtin_fmaf(4e-6f, mag, qm));
+}
+
+// The lanes whose comparison holds, as a scalar mask (one compare; NaN compares false).
+__device__ __forceinline__ uint64_t lanes_le(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 5); }
+__device__ __forceinline__ uint64_t lanes_lt(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 4); }
+
+// An empty instruction that takes a group's record words: their LDS reads are issued together before it.
+template <int N>
+__device__ __forceinline__ void group_loaded(Vec4 (&A)[N], Vec4 (&B)[N]) {
+  static_assert(N == 2 || N == 4, "one operand list per size");
+  if constexpr (N == 4)
+    asm volatile("" : "+v"(A[0]), "+v"(A[1]), "+v"(A[2]), "+v"(A[3]), "+v"(B[0]), "+v"(B[1]), "+v"(B[2]), "+v"(B[3]));
+  else
+    asm volatile("" : "+v"(A[0]), "+v"(A[1]), "+v"(B[0]), "+v"(B[1]));
+}
 
 template <int FALLOFF>
 __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const DeviceBatch* __restrict__ db,
                                                              const uint2* __restrict__ sorted_pairs,
                                                              int64_t total_tiles,
                                                              uint64_t capacity) {
-  __shared__ float4 sA[64], sB[64], sC[64];
-  __shared__ uint32_t live[kFwdWaves];
+  __shared__ Vec4 stage[2][3][kFwdBatch];   // record words 0-3 (b doubled), 4-7 and 8-11
+  __shared__ uint32_t live[2][kFwdWaves];
   __shared__ unsigned long long red[kFwdWaves][2];
   __shared__ uint32_t red_m[kFwdWaves];
   const int64_t gt = xcd_tile(blockIdx.x);
@@ -94,88 +143,177 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
   const ViewDesc& V = db->views[v];
   const int lt = (int)(gt - db->tile_prefix[v]);
   const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int px = tx * kTile + (lane & 15);
-  const int py0 = ty * kTile + (kTile / kFwdWaves) * w + (lane >> 4);   // the wave's rows: py0 + 4 k
-  const float pxf = (float)px;
-  float pyf[kFwdPix];
-  uint32_t alive = 0;
-#pragma unroll
-  for (int k = 0; k < kFwdPix; ++k) {
-    pyf[k] = (float)(py0 + 4 * k);
-    if (px < V.width && py0 + 4 * k < V.height) alive |= 1u << k;
-  }
-  float T[kFwdPix], C[kFwdPix][3];
-  uint32_t last[kFwdPix];
-#pragma unroll
-  for (int k = 0; k < kFwdPix; ++k) {
-    T[k] = 1.f;
-    C[k][0] = C[k][1] = C[k][2] = 0.f;
-    last[k] = 0u;
-  }
-  uint32_t n_exam = 0;    // pairs examined: each terminated pixel adds 1 + its terminating position
-  uint32_t n_blend = 0;   // pairs composited, for the statistics
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qx = tx * kTile + (w & 1) * 8, qy = ty * kTile + (w >> 1) * 8;   // the wave's quadrant
+  const int px = qx + (lane & 7), py = qy + (lane >> 3);
+  const bool inside = px < V.width && py < V.height;
+  uint64_t alive = __ballot(inside);   // pixels still compositing
+  // a pixel that has stopped takes a NaN centre: its q is NaN and fails the alpha-floor test of every splat
+  float pxf = inside ? (float)px : __builtin_nanf("");
+  const float pyf = (float)py;
+  const float bx0 = (float)qx, bx1 = (float)min(qx + 7, V.width - 1);    // pixel centres of the quadrant
+  const float by0 = (float)qy, by1 = (float)min(qy + 7, V.height - 1);
+  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  uint32_t last = 0u;
+  // wave totals (scalars): pairs examined by pixels that terminated (1 + the terminating position each), and
+  // pairs composited
+  uint64_t n_exam = 0;
+  uint32_t n_blend = 0;
   const uint2 rg = V.ranges[lt];
   // a range beyond the key buffer (inconsistent key count) renders as background; the list length is made
   // a scalar, so that the batch and splat loop control runs on the scalar unit
   const int n = __builtin_amdgcn_readfirstlane((uint64_t)rg.y <= capacity ? (int)(rg.y - rg.x) : 0);
   const GlobalRec* rec = (const GlobalRec*)(V.rec);
-  for (int base = 0; base < n; base += 64) {
-    const int cnt = min(64, n - base);
-    if (lane < cnt) {   // wave 0 stages words 0-7 of the batch's records, wave 1 words 8-11
-      const uint32_t id = sorted_pairs[rg.x + base + lane].x;
-      if (w == 0) {
-        const float4 a = rec_load(rec, 4 * (size_t)id);
-        const float4 b = rec_load(rec, 4 * (size_t)id + 1);
-        sA[lane] = make_float4(a.x, a.y, a.z, a.w + a.w);
-        sB[lane] = b;
-      } else if (w == 1) {
-        sC[lane] = rec_load(rec, 4 * (size_t)id + 2);
+  const uint2* list = sorted_pairs + rg.x;
+  // staging: this thread's record of a batch, and which part of it
+  const int sj = threadIdx.x & (kFwdBatch - 1);
+  const bool part0 = w < kFwdWaves / 2;
+  uint32_t id = 0;
+  Vec4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
+  auto load_id = [&](int base) {
+    if (base + sj < n) id = list[base + sj].x;
+  };
+  auto load_rec = [&](int base) {
+    if (base + sj < n) {
+      if (part0) {
+        r0 = rec[4 * (size_t)id];
+        r1 = rec[4 * (size_t)id + 1];
+      } else {
+        r0 = rec[4 * (size_t)id + 2];
       }
     }
+  };
+  auto store_rec = [&](int buf) {
+    if (part0) {
+      stage[buf][0][sj] = Vec4{r0.x, r0.y, r0.z, r0.w + r0.w};
+      stage[buf][1][sj] = r1;
+    } else {
+      stage[buf][2][sj] = r0;
+    }
+  };
+  if (n > 0) {
+    load_id(0);
+    load_rec(0);
+    load_id(kFwdBatch);
+    store_rec(0);
     __syncthreads();
-    if (__any(alive != 0)) {   // wave-uniform: a wave whose pixels have all stopped only stages
-      for (int j = 0; j < cnt; ++j) {
-        const float4 A = sA[j];
-        const float4 B = sB[j];
-        const float4 Cc = sC[j];
-        const uint32_t pos1 = (uint32_t)(base + j + 1);
-#pragma unroll
-        for (int k = 0; k < kFwdPix; ++k) {
-          if (!(alive & (1u << k))) continue;
-          float dx, dy;
-          float q = pair_q(A.x, A.y, A.z, A.w, B.x, pxf, pyf[k], dx, dy);
-          if (!(q <= B.y)) continue;
-          q = clamp_q(q);
-          float G;
-          if (FALLOFF == GES_FALLOFF_PHI) {
-            G = fast_exp2(kNegHalfLog2e * q);
-          } else {
-            const float qb = fast_exp2(0.5f * B.w * fast_log2(q));
-            G = fast_exp2(kNegHalfLog2e * qb);
-          }
-          const float alpha = fminf(kAlphaMax, B.z * G);
-          const float t = T[k] * (1.f - alpha);
-          if (t < kTMin) { alive &= ~(1u << k); n_exam += pos1; continue; }
-          const float wgt = alpha * T[k];
-          C[k][0] = __builtin_fmaf(wgt, Cc.x, C[k][0]);
-          C[k][1] = __builtin_fmaf(wgt, Cc.y, C[k][1]);
-          C[k][2] = __builtin_fmaf(wgt, Cc.z, C[k][2]);
-          T[k] = t;
-          last[k] = pos1;
-          ++n_blend;
+  }
+  int buf = 0;
+  for (int base = 0; base < n; base += kFwdBatch, buf ^= 1) {
+    const int cnt = min(kFwdBatch, n - base);
+    load_rec(base + kFwdBatch);       // the records of the next batch, and the list entries of the one after,
+    load_id(base + 2 * kFwdBatch);    // arrive while this one is composited
+    const Vec4(*st)[kFwdBatch] = stage[buf];
+    if (alive) {                      // wave-uniform: a wave whose pixels have all stopped only stages
+      for (int c0 = 0; c0 < cnt; c0 += 64) {
+        bool hit = false, inf = false;
+        if (c0 + lane < cnt) {
+          const Vec4 A = st[0][c0 + lane];
+          const Vec4 B = st[1][c0 + lane];
+          const Vec4 Cl = st[2][c0 + lane];
+          inf = !(fabsf(Cl.x) + fabsf(Cl.y) + fabsf(Cl.z) < __builtin_inff());
+          hit = box_may_hit(A.z, 0.5f * A.w, B.x, B.y, A.x - bx1, A.x - bx0, A.y - by1, A.y - by0);
         }
-        if (!__any(alive != 0)) break;
+        uint64_t mask = __ballot(hit);
+        const uint64_t odd = __ballot(inf);   // a colour that is not finite (or a sum of magnitudes that is not)
+        while (mask) {
+          // the next kFwdGroup splats (a short last group repeats its first, switched off)
+          int js[kFwdGroup];
+          uint64_t have[kFwdGroup];
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {
+            have[e] = mask ? ~0ull : 0ull;
+            js[e] = mask ? c0 + (int)__builtin_ctzll(mask) : js[0];
+            mask &= mask - 1ull;   // 0 stays 0
+          }
+          Vec4 A[kFwdGroup], B[kFwdGroup], Cc[kFwdGroup];
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {
+            A[e] = st[0][js[e]];
+            B[e] = st[1][js[e]];
+            Cc[e] = st[2][js[e]];
+          }
+          group_loaded(A, B);   // all the group's LDS reads before the first use
+          float q[kFwdGroup], alpha[kFwdGroup];
+          uint64_t ok[kFwdGroup], some = 0ull;   // lanes whose pixel takes the splat (a stopped pixel's q is NaN)
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {
+            float dx, dy;
+            q[e] = pair_q(A[e].x, A[e].y, A[e].z, A[e].w, B[e].x, pxf, pyf, dx, dy);
+            ok[e] = lanes_le(q[e], B[e].y) & have[e];
+            some |= ok[e];
+          }
+          if (!some) continue;
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {
+            const float qc = clamp_q(q[e]);
+            float G;
+            if (FALLOFF == GES_FALLOFF_PHI) {
+              G = fast_exp2(kNegHalfLog2e * qc);
+            } else {
+              const float qb = fast_exp2(0.5f * B[e].w * fast_log2(qc));
+              G = fast_exp2(kNegHalfLog2e * qb);
+            }
+            alpha[e] = fminf(kAlphaMax, B[e].z * G);
+}
+          // transmittance behind each splat of the group, a pixel that does not take one keeping its own
+          float t[kFwdGroup + 1], a0[kFwdGroup];
+          t[0] = T;
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {
+            a0[e] = __builtin_amdgcn_inverse_ballot_w64(ok[e]) ? alpha[e] : 0.f;
+            t[e + 1] = t[e] * (1.f - a0[e]);   // exactly t[e] where the splat is not taken
+          }
+          if (!((lanes_lt(t[kFwdGroup], kTMin) & alive) | odd)) {
+            // no pixel stops in this group (t never grows) and every colour is finite, so a weight of 0 adds
+            // exactly nothing: straight-line for the whole wave
+#pragma unroll
+            for (int e = 0; e < kFwdGroup; ++e) {
+              const float wgt = a0[e] * t[e];
+              C0 = __builtin_fmaf(wgt, Cc[e].x, C0);
+              C1 = __builtin_fmaf(wgt, Cc[e].y, C1);
+              C2 = __builtin_fmaf(wgt, Cc[e].z, C2);
+              last = __builtin_amdgcn_inverse_ballot_w64(ok[e]) ? (uint32_t)(base + js[e] + 1) : last;
+              n_blend += (uint32_t)__builtin_popcountll(ok[e]);
+            }
+            T = t[kFwdGroup];
+            continue;
+          }
+#pragma unroll
+          for (int e = 0; e < kFwdGroup; ++e) {   // splat by splat, a pixel stopping at its own
+            const uint32_t pos1 = (uint32_t)(base + js[e] + 1);
+            const float te = T * (1.f - alpha[e]);
+            const uint64_t ended = lanes_lt(te, kTMin) & ok[e] & alive;
+            if (ended) {
+              alive &= ~ended;
+              n_exam += (uint64_t)pos1 * (uint32_t)__builtin_popcountll(ended);
+              pxf = __builtin_amdgcn_inverse_ballot_w64(ended) ? __builtin_nanf("") : pxf;
+            }
+            const uint64_t blend = ok[e] & alive;
+            n_blend += (uint32_t)__builtin_popcountll(blend);
+            if (__builtin_amdgcn_inverse_ballot_w64(blend)) {
+              const float wgt = alpha[e] * T;
+              C0 = __builtin_fmaf(wgt, Cc[e].x, C0);
+              C1 = __builtin_fmaf(wgt, Cc[e].y, C1);
+              C2 = __builtin_fmaf(wgt, Cc[e].z, C2);
+              T = te;
+              last = pos1;
+            }
+          }
+          if (!alive) break;
+        }
+        if (!alive) break;
       }
     }
-    // the block stops once every pixel of the tile has (the same decision in both waves, taken after the
+    // the block stops once every pixel of the tile has (the same decision in every wave, taken after the
     // barrier that also ends the reads of this batch)
-    const bool wl = __any(alive != 0);
-    if (lane == 0) live[w] = wl ? 1u : 0u;
+    if (lane == 0) live[buf][w] = alive ? 1u : 0u;
+    store_rec(buf ^ 1);
     __syncthreads();
     uint32_t any_live = 0;
 #pragma unroll
-    for (int q = 0; q < kFwdWaves; ++q) any_live |= live[q];
+    for (int k = 0; k < kFwdWaves; ++k) any_live |= live[buf][k];
     if (!any_live) break;
   }
   {
@@ -183,16 +321,11 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
     // and composited, stored per tile and summed by raster_stats_kernel.  (Device-scope atomics from
     // every tile into one counter serialise across the XCDs: two per tile cost about 50 us per frame.)
     // pixels still alive examined the whole list (out-of-image pixels were never alive)
-    unsigned long long e = (unsigned long long)n_exam + (unsigned long long)__popc(alive) * (uint32_t)n, b = n_blend;
+    const unsigned long long e = n_exam + (unsigned long long)__builtin_popcountll(alive) * (uint32_t)n;
+    const unsigned long long b = n_blend;
     // and the length of the backward walk over the tile: its last composited position
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 0; k < kFwdPix; ++k) m = max(m, last[k]);
-    for (int off = 32; off > 0; off >>= 1) {
-      e += __shfl_xor(e, off, 64);
-      b += __shfl_xor(b, off, 64);
-      m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-    }
+    uint32_t m = last;
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
     if (lane == 0) { red[w][0] = e; red[w][1] = b; red_m[w] = m; }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -209,16 +342,13 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
       V.tile_work[lt] = sm;
     }
   }
-#pragma unroll
-  for (int k = 0; k < kFwdPix; ++k) {
-    const int py = py0 + 4 * k;
-    if (px >= V.width || py >= V.height) continue;
+  if (inside) {
     const size_t pix = (size_t)py * V.width + px;
-    V.out_rgb[3 * pix + 0] = __builtin_fmaf(T[k], V.bg[0], C[k][0]);
-    V.out_rgb[3 * pix + 1] = __builtin_fmaf(T[k], V.bg[1], C[k][1]);
-    V.out_rgb[3 * pix + 2] = __builtin_fmaf(T[k], V.bg[2], C[k][2]);
-    if (V.final_T) V.final_T[pix] = T[k];
-    if (V.n_contrib) V.n_contrib[pix] = last[k];
+    V.out_rgb[3 * pix + 0] = __builtin_fmaf(T, V.bg[0], C0);
+    V.out_rgb[3 * pix + 1] = __builtin_fmaf(T, V.bg[1], C1);
+    V.out_rgb[3 * pix + 2] = __builtin_fmaf(T, V.bg[2], C2);
+    if (V.final_T) V.final_T[pix] = T;
+    if (V.n_contrib) V.n_contrib[pix] = last;
   }
 }
 
