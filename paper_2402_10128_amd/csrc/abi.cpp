@@ -115,6 +115,7 @@ hipError_t upload_views(const ges_splats* s, const ges_camera* cams, int32_t nv,
       V.grad_rows = reinterpret_cast<float*>(kw + kp.off_rows);
       V.grad_bits = reinterpret_cast<uint32_t*>(kw + kp.off_bits);
       V.grad_slots = key_slots;
+      V.ckpt = reinterpret_cast<ges::Checkpoint*>(kw + kp.off_ckpt);
     }
     V.keep_grad2d = (p->flags & GES_RASTER_KEEP_GRAD2D) ? 1 : 0;
   }
@@ -253,14 +254,20 @@ ges_status render_backward(const ges_splats* splats, const ges_camera* cams, int
                              slots), "upload");
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
   const ges::KeyPlan kp = ges::plan_keys(slots, true);
-  if (slots) b.sorted_pairs = reinterpret_cast<const uint2*>(reinterpret_cast<char*>(key_ws) + kp.off_pv0);
+  b.key_capacity = slots;
+  if (slots) {
+    b.kw = ges::attach_key_ws(kp, key_ws);
+    b.sorted_pairs = b.kw.pv[0];
+  }
   const ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
-  if (slots)
+  if (slots) {   // without a slot no pixel composited anything
     GES_CHECK_HIP(timed(GES_STAGE_ZERO, stream, [&] {
-                    return ges::launch_zero(reinterpret_cast<char*>(key_ws) + kp.off_bits, (slots + 31) / 32 * 4,
-                                            stream);
-                  }), "clear row marks");
-  GES_CHECK_HIP(timed(GES_STAGE_RASTER_BACKWARD, stream, [&] { return ges::launch_raster_backward(db, b, stream); }), "raster_backward");
+                    return ges::launch_backward_prepare(
+                        db, b, reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(key_ws) + kp.off_bits),
+                        (size_t)((slots + 31) / 32), stream);
+                  }), "backward_prepare");
+    GES_CHECK_HIP(timed(GES_STAGE_RASTER_BACKWARD, stream, [&] { return ges::launch_raster_backward(db, b, stream); }), "raster_backward");
+  }
   // every listed splat's row of grad2d (zero when its slots lie beyond the key capacity)
   char* kwb = reinterpret_cast<char*>(key_ws);
   GES_CHECK_HIP(timed(GES_STAGE_ROW_REDUCE, stream, [&] {

@@ -58,7 +58,7 @@ struct FramePlan {
   // splat workspace; the binning buffers of the frame's own batch come last (a server gives a batch of
   // views one such region and its views only the part before it)
   size_t off_db = 0, off_hdr = 0, off_rec = 0, off_grad = 0, off_vis = 0, off_slotoff = 0, off_ranges = 0,
-         off_tstats = 0, off_twork = 0, off_gorder = 0, off_sort = 0;
+         off_tstats = 0, off_twork = 0, off_tckpt = 0, off_gorder = 0, off_sort = 0;
   size_t view_bytes = 0, splat_bytes = 0;
   // pixel workspace
   size_t off_final_T = 0, off_n_contrib = 0, pixel_bytes = 0;
@@ -79,6 +79,7 @@ inline FramePlan plan_frame(int64_t n, int w, int h) {
   p.off_ranges = o;  o += align256((size_t)p.tiles * 8);
   p.off_tstats = o;  o += align256((size_t)p.tiles * 16);
   p.off_twork = o;   o += align256((size_t)p.tiles * 4);
+  p.off_tckpt = o;   o += align256((size_t)p.tiles * 4);
   p.off_gorder = o;  o += align256((size_t)(p.tiles + 7) / 8 * 4);
   p.view_bytes = o;
   p.off_sort = o;    o += plan_sort(n).bytes;
@@ -123,10 +124,10 @@ inline int tile_passes(int64_t total_tiles) {
 // Key workspace of `slots` candidate slots: two buffers of (tile; splat index, slot) pairs, the values of
 // buffer 0 first (the sorted pairs the raster reads); the table of the tile passes; and, for frames that
 // run the backward pass, one 48-byte row per slot for the backward's per-(tile, splat) sums with a bit per
-// slot marking the written rows.
+// slot marking the written rows, and the checkpoints of the cut walks.
 struct KeyPlan {
   size_t off_pv0 = 0, off_key0 = 0, off_pv1 = 0, off_key1 = 0, off_table = 0, off_totals = 0, off_rows = 0,
-         off_bits = 0, bytes = 0;
+         off_bits = 0, off_ckpt = 0, bytes = 0;
 };
 
 inline KeyPlan plan_keys(uint64_t slots, bool backward_rows) {
@@ -142,6 +143,7 @@ inline KeyPlan plan_keys(uint64_t slots, bool backward_rows) {
   if (backward_rows) {
     p.off_rows = o; o += align256(k * kRowFloats * 4);
     p.off_bits = o; o += align256((k + 31) / 32 * 4);
+    p.off_ckpt = o; o += align256((size_t)max_checkpoints(slots) * kTilePx * sizeof(Checkpoint));
   }
   p.bytes = o;
   return p;
@@ -247,6 +249,7 @@ inline void attach_splat_ws(ViewDesc& V, const FramePlan& fp, void* splat_ws) {
   V.ranges = reinterpret_cast<uint2*>(b + fp.off_ranges);
   V.tile_stats = reinterpret_cast<unsigned long long*>(b + fp.off_tstats);
   V.tile_work = reinterpret_cast<uint32_t*>(b + fp.off_twork);
+  V.tile_ckpt = reinterpret_cast<uint32_t*>(b + fp.off_tckpt);
   V.group_order = reinterpret_cast<uint32_t*>(b + fp.off_gorder);
   V.header = reinterpret_cast<unsigned long long*>(b + fp.off_hdr);
 }

@@ -35,6 +35,16 @@ enum : int {
   R_U = 0, R_V, R_A, R_B, R_C, R_QMAX, R_OPA, R_BETA, R_CR, R_CG, R_CB, R_DEPTH, R_RADFLAGS, R_RECT0, R_RECT1, R_TOUCHED
 };
 
+// Long backward walks are cut at boundaries, where a pass over them leaves every pixel's transmittance and the
+// colour behind it (raster.hip).  A boundary stands for 64 walked list positions or more, and a frame has at most
+// kMaxCheckpoints of them (32 MB).
+struct __attribute__((aligned(16))) Checkpoint {
+  float T;
+  float rgb[3];
+};
+constexpr uint32_t kMaxCheckpoints = 8192;
+inline int64_t max_checkpoints(uint64_t slots) { return (int64_t)std::min<uint64_t>(slots / 64, kMaxCheckpoints); }
+
 struct ViewDesc {
   // scene
   const float* means;
@@ -76,6 +86,8 @@ struct ViewDesc {
   uint32_t* vis;                 // [n] bit 31: the splat touches a tile; bits 0..4: its clamp flags
   float* final_T;                // [h*w]
   uint32_t* n_contrib;           // [h*w]
+  Checkpoint* ckpt;              // [max_checkpoints][256] state at the boundaries of the cut walks (backward)
+  uint32_t* tile_ckpt;           // [tiles] first checkpoint of a tile whose walk is cut (backward)
   float* out_rgb;                // [h*w*3]
   const float* dL_drgb;          // [h*w*3] (backward only)
 };
@@ -218,12 +230,15 @@ inline uint32_t radix_blocks(uint64_t n, int items, int sub = 1) {
   return (uint32_t)((n + span - 1) / span);
 }
 hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
+// clears the row marks and, for frames whose walks are cut, lists the backward raster's work items (in
+// b.kw.pv[1]) and cut tiles (b.kw.table), with the plan in b.kw.totals; the raster then takes them
+hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
+                                   hipStream_t stream);
 hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // args (may be NULL): the fused update's arguments when `fused`; otherwise only accumulate and the
 // densification statistic are read
 hipError_t launch_preprocess_backward(const DeviceBatch* dbatch, const Batch& b, const ges_splat_grads* grads,
                                       hipStream_t stream, const AdamSplats* args = nullptr, bool fused = false);
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t stream);
 
 hipError_t launch_freq_mask(const float* target, int w, int h, float omega, void* scratch, uint8_t* mask,
                             hipStream_t stream);

@@ -243,19 +243,4 @@ hipError_t launch_loss(const float* img, const float* target, const uint8_t* mas
   return hipGetLastError();
 }
 
-__global__ void zero_kernel(uint4* p, size_t n16, uint8_t* tail, size_t ntail) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
-}
-
-hipError_t launch_zero(void* p, size_t bytes, hipStream_t stream) {
-  if (bytes == 0) return hipSuccess;
-  const size_t n16 = bytes / 16;
-  const unsigned blocks = (unsigned)std::min<size_t>(4096, (n16 + 255) / 256 + 1);
-  hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, stream, reinterpret_cast<uint4*>(p), n16,
-                     reinterpret_cast<uint8_t*>(p) + n16 * 16, bytes - n16 * 16);
-  return hipGetLastError();
-}
-
 }  // namespace ges

@@ -15,7 +15,10 @@
 // has.  Tiles are dealt to the 8 XCDs in groups of 8 neighbours (see xcd_tile).
 // The backward pass walks each pixel's contributors back to front, recovering the transmittance
 // before splat j as T_j = T_(j+1) / (1 - alpha_j) from the stored final T, so no per-pixel lists are
-// kept.  Per splat, the 4 pixels of a lane are summed in registers and each row of 16 lanes by a DPP
+// kept.  A long walk is cut into segments that several waves take at once (a wave needs about 0.5 us per splat,
+// and a 64x64 frame has 16 tiles): backward_prepare_kernel plans them and raster_recover_kernel leaves the
+// state at their boundaries.
+// Per splat, the 4 pixels of a lane are summed in registers and each row of 16 lanes by a DPP
 // reduce-scatter; the row's lanes park the row sums in LDS, and every 32 splats each lane finishes one
 // parked splat (4 row sums) and stores the tile's ten sums of the splat as a row at the pair's candidate
 // slot, marking the slot; a row reduction then adds each splat's rows in binary64 in slot order (the
@@ -91,7 +94,6 @@ __device__ __forceinline__ int64_t ordered_tile(int64_t blk, const uint32_t* gro
 constexpr int kFwdWaves = 4;
 constexpr int kFwdBatch = 128;              // records staged per barrier: threads 0-127 load words 0-7 of
                                             // one record each, threads 128-255 words 8-11
-constexpr int kFwdGroup = 4;
 static_assert(kFwdBatch * 2 == 64 * kFwdWaves, "half the block per record part");
 
 // Whether a splat's alpha-floor ellipse may reach a pixel centre of the box (dx, dy: mean minus the box's
@@ -114,6 +116,10 @@ __device__ __forceinline__ bool box_may_hit(float a, float b, float c, float qm,
   return !(m > __builtin_fmaf(4e-6f, mag, qm));
 }
 
+__device__ __forceinline__ float scalar_f32(float x) {   // of a wave-uniform value
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
 // The lanes whose comparison holds, as a scalar mask (one compare; NaN compares false).
 __device__ __forceinline__ uint64_t lanes_le(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 5); }
 __device__ __forceinline__ uint64_t lanes_lt(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 4); }
@@ -128,7 +134,7 @@ __device__ __forceinline__ void group_loaded(Vec4 (&A)[N], Vec4 (&B)[N]) {
     asm volatile("" : "+v"(A[0]), "+v"(A[1]), "+v"(B[0]), "+v"(B[1]));
 }
 
-template <int FALLOFF>
+template <int FALLOFF, int kFwdGroup>
 __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const DeviceBatch* __restrict__ db,
                                                              const uint2* __restrict__ sorted_pairs,
                                                              int64_t total_tiles,
@@ -152,8 +158,9 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
   // a pixel that has stopped takes a NaN centre: its q is NaN and fails the alpha-floor test of every splat
   float pxf = inside ? (float)px : __builtin_nanf("");
   const float pyf = (float)py;
-  const float bx0 = (float)qx, bx1 = (float)min(qx + 7, V.width - 1);    // pixel centres of the quadrant
-  const float by0 = (float)qy, by1 = (float)min(qy + 7, V.height - 1);
+  // pixel centres of the quadrant, in scalar registers
+  const float bx0 = scalar_f32((float)qx), bx1 = scalar_f32((float)min(qx + 7, V.width - 1));
+  const float by0 = scalar_f32((float)qy), by1 = scalar_f32((float)min(qy + 7, V.height - 1));
   float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
   uint32_t last = 0u;
   // wave totals (scalars): pairs examined by pixels that terminated (1 + the terminating position each), and
@@ -249,10 +256,10 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
           for (int e = 0; e < kFwdGroup; ++e) {
             const float qc = clamp_q(q[e]);
             float G;
-            if (FALLOFF == GES_FALLOFF_PHI) {
+            if constexpr (FALLOFF == GES_FALLOFF_PHI) {
               G = fast_exp2(kNegHalfLog2e * qc);
             } else {
-              const float qb = fast_exp2(0.5f * B[e].w * fast_log2(qc));
+              const float qb = fast_exp2(0.5f * B[e][3] * fast_log2(qc));
               G = fast_exp2(kNegHalfLog2e * qb);
             }
             alpha[e] = fminf(kAlphaMax, B[e].z * G);
@@ -402,10 +409,164 @@ __device__ __forceinline__ float row_scatter8(float a0, float a1, float a2, floa
 
 constexpr int kFlush = 32;   // splats whose row partials are parked in LDS before one flush of rows
 
+// Words of the backward's plan (b.kw.totals): where each XCD's work items start, the number of tiles whose walk
+// is cut, and the list positions per segment.
+enum : int { P_STARTS = 0, P_CUT = 9, P_SEG = 10 };
+
+// Walks the cut tiles back to front only to leave, at every segment boundary, the transmittance and the colour
+// behind it: the recurrences of the backward pass, the same operations in the same order (so that cutting a walk
+// changes no bit of the gradients), without its sums.  Launch shape and walk as in the forward pass: a quadrant
+// per wave, only the splats that can reach it, kRecGroup at a time; a splat that a pixel does not take has alpha
+// 0, which leaves its transmittance and colour exactly as they are.
+constexpr int kRecGroup = 4;
 template <int FALLOFF>
+__global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const DeviceBatch* __restrict__ db,
+                                                             const uint2* __restrict__ sorted_pairs,
+                                                             const uint32_t* __restrict__ cut_tiles,
+                                                             const uint32_t* __restrict__ plan) {
+  __shared__ Vec4 stage[2][3][kFwdBatch];   // record words 0-3 (b doubled), 4-7 and 8-11
+  if (blockIdx.x >= plan[P_CUT]) return;   // the whole block
+  const int64_t gt = cut_tiles[blockIdx.x];
+  const int v = view_of_block(db->tile_prefix, db->nviews, gt);
+  const ViewDesc& V = db->views[v];
+  const int lt = (int)(gt - db->tile_prefix[v]);
+  const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qx = tx * kTile + (w & 1) * 8, qy = ty * kTile + (w >> 1) * 8;   // the wave's quadrant
+  const int px = qx + (lane & 7), py = qy + (lane >> 3);
+  const float pxf = (float)px, pyf = (float)py;
+  const float bx0 = scalar_f32((float)qx), bx1 = scalar_f32((float)min(qx + 7, V.width - 1));
+  const float by0 = scalar_f32((float)qy), by1 = scalar_f32((float)min(qy + 7, V.height - 1));
+  float T = 1.f, S0 = 0.f, S1 = 0.f, S2 = 0.f;
+  uint32_t last = 0u;
+  if (px < V.width && py < V.height) {
+    const size_t pix = (size_t)py * V.width + px;
+    T = V.final_T[pix];
+    last = V.n_contrib[pix];
+  }
+  uint32_t wl = last;
+  for (int off = 32; off > 0; off >>= 1) wl = max(wl, (uint32_t)__shfl_xor((int)wl, off, 64));
+  const int wlast = __builtin_amdgcn_readfirstlane((int)wl);   // the wave's own walk
+  const int n = __builtin_amdgcn_readfirstlane((int)V.tile_work[lt]);
+  const int seg = __builtin_amdgcn_readfirstlane((int)plan[P_SEG]);
+  int bound = (n - 1) / seg * seg;   // the next boundary on the way down
+  GlobalVec4* ck = (GlobalVec4*)V.ckpt + (size_t)V.tile_ckpt[lt] * kTilePx + ((w >> 1) * 8 + (lane >> 3)) * kTile +
+                   (w & 1) * 8 + (lane & 7);   // the pixel's entry at the tile's first boundary
+  const GlobalRec* rec = (const GlobalRec*)(V.rec);
+  const uint2* list = sorted_pairs + V.ranges[lt].x;
+  const int sj = threadIdx.x & (kFwdBatch - 1);
+  const bool part0 = w < kFwdWaves / 2;
+  uint32_t id = 0;
+  Vec4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
+  auto load_id = [&](int base) {
+    if (base >= 0 && base + sj < n) id = list[base + sj].x;
+  };
+  auto load_rec = [&](int base) {
+    if (base >= 0 && base + sj < n) {
+      if (part0) {
+        r0 = rec[4 * (size_t)id];
+        r1 = rec[4 * (size_t)id + 1];
+      } else {
+        r0 = rec[4 * (size_t)id + 2];
+      }
+    }
+  };
+  auto store_rec = [&](int buf) {
+    if (part0) {
+      stage[buf][0][sj] = Vec4{r0.x, r0.y, r0.z, r0.w + r0.w};
+      stage[buf][1][sj] = r1;
+    } else {
+      stage[buf][2][sj] = r0;
+    }
+  };
+  const int top = (n - 1) / kFwdBatch * kFwdBatch;
+  load_id(top);
+  load_rec(top);
+  load_id(top - kFwdBatch);
+  store_rec(0);
+  __syncthreads();
+  int buf = 0;
+  for (int base = top; base >= 0 && base + kFwdBatch >= seg; base -= kFwdBatch, buf ^= 1) {   // to the first boundary
+    load_rec(base - kFwdBatch);
+    load_id(base - 2 * kFwdBatch);
+    const Vec4(*st)[kFwdBatch] = stage[buf];
+    for (int c0 = kFwdBatch - 64; c0 >= 0; c0 -= 64) {
+      const int lo = base + c0;
+      if (lo + 64 == bound) {
+        if (wlast > bound) ck[(size_t)(bound / seg - 1) * kTilePx] = Vec4{T, S0, S1, S2};
+        bound -= seg;
+      }
+      if (wlast <= lo) continue;   // the quadrant's pixels all stopped before these splats
+      bool hit = false;
+      if (lo + lane < wlast) {
+        const Vec4 A = st[0][c0 + lane];
+        const Vec4 B = st[1][c0 + lane];
+        hit = box_may_hit(A.z, 0.5f * A.w, B.x, B.y, A.x - bx1, A.x - bx0, A.y - by1, A.y - by0);
+      }
+      uint64_t mask = __ballot(hit);
+      while (mask) {
+        // the next kRecGroup splats from the back (a short last group repeats its first, switched off)
+        int js[kRecGroup];
+        uint64_t have[kRecGroup];
+#pragma unroll
+        for (int e = 0; e < kRecGroup; ++e) {
+          have[e] = mask ? ~0ull : 0ull;
+          js[e] = mask ? 63 - (int)__builtin_clzll(mask) : js[0];
+          mask &= ~(1ull << js[e]);   // 0 stays 0
+        }
+        Vec4 A[kRecGroup], B[kRecGroup], Cc[kRecGroup];
+#pragma unroll
+        for (int e = 0; e < kRecGroup; ++e) {
+          A[e] = st[0][c0 + js[e]];
+          B[e] = st[1][c0 + js[e]];
+          Cc[e] = st[2][c0 + js[e]];
+        }
+        group_loaded(A, B);
+        float alpha[kRecGroup], inv[kRecGroup];
+#pragma unroll
+        for (int e = 0; e < kRecGroup; ++e) {
+          float dx, dy;
+          const float q0 = pair_q(A[e].x, A[e].y, A[e].z, A[e].w, B[e].x, pxf, pyf, dx, dy);
+          const uint64_t take = lanes_le(q0, B[e].y) & have[e] &
+                                __builtin_amdgcn_uicmp((uint32_t)(lo + js[e]), last, 36);   // position < last
+          const float q = clamp_q(q0);
+          float G;
+          if (FALLOFF == GES_FALLOFF_PHI) {
+            G = fast_exp2(kNegHalfLog2e * q);
+          } else {
+            const float qb = fast_exp2(0.5f * B[e].w * fast_log2(q));
+            G = fast_exp2(kNegHalfLog2e * qb);
+          }
+          const float oG = B[e].z * G;
+          const float full = oG > kAlphaMax ? kAlphaMax : oG;
+          alpha[e] = __builtin_amdgcn_inverse_ballot_w64(take) ? full : 0.f;
+          inv[e] = __builtin_amdgcn_inverse_ballot_w64(take) ? fast_rcp(1.f - alpha[e]) : 1.f;
+        }
+#pragma unroll
+        for (int e = 0; e < kRecGroup; ++e) {
+          T = T * inv[e];
+          S0 = __builtin_fmaf(alpha[e], Cc[e].x - S0, S0);
+          S1 = __builtin_fmaf(alpha[e], Cc[e].y - S1, S1);
+          S2 = __builtin_fmaf(alpha[e], Cc[e].z - S2, S2);
+        }
+      }
+    }
+    store_rec(buf ^ 1);
+    __syncthreads();
+  }
+}
+
+// One block of one wave per work item.  SEGMENTED: an item is a segment of a tile's walk (see
+// backward_prepare_kernel), and a block takes further items in turn; it starts from the transmittance behind the
+// segment and the colour behind it, which are the pixel's final transmittance and nothing where its last
+// composited splat lies in the segment, else what raster_recover_kernel left at the boundary.  Otherwise an item
+// is a whole tile, dealt by ordered_tile or xcd_tile.
+template <int FALLOFF, bool SEGMENTED>
 __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* __restrict__ db,
                                                              const uint2* __restrict__ sorted_pairs,
-                                                             int64_t total_tiles, int ordered) {
+                                                             int64_t total_tiles, const uint2* __restrict__ items,
+                                                             const uint32_t* __restrict__ plan) {
   __shared__ float4 sA[64], sB[64], sC[64];
   __shared__ float sRed[kFlush][4][10];   // [parked splat][lane row][component]
   __shared__ uint32_t sSlot[kFlush];      // the parked splat's slot: its row of this tile's sums
@@ -413,192 +574,219 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
   __shared__ uint32_t sFirst[kFlush];     // into its row)
   __shared__ uint32_t sIdx[64];           // batch item and first candidate slot of each staged splat
   __shared__ uint32_t sLo[64];
-  const int64_t gt = ordered ? ordered_tile(blockIdx.x, db->views[0].group_order, total_tiles) : xcd_tile(blockIdx.x);
-  if (gt < 0 || gt >= total_tiles) return;
-  const int v = view_of_block(db->tile_prefix, db->nviews, gt);
-  const ViewDesc& V = db->views[v];
-  const int lt = (int)(gt - db->tile_prefix[v]);
-  const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
   const int lane = threadIdx.x;
   const int row = lane >> 4;
-  const int px = tx * kTile + (lane & 15);
-  const int py0 = ty * kTile + (lane >> 4);
-  const float pxf = (float)px;
-  float pyf[4], T[4], TfB[4], g[4][3], S[4][3];
-  uint32_t last[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int py = py0 + 4 * k;
-    pyf[k] = (float)py;
-    S[k][0] = S[k][1] = S[k][2] = 0.f;
-    if (px < V.width && py < V.height) {
-      const size_t pix = (size_t)py * V.width + px;
-      T[k] = V.final_T[pix];
-      last[k] = V.n_contrib[pix];
-      g[k][0] = V.dL_drgb[3 * pix];
-      g[k][1] = V.dL_drgb[3 * pix + 1];
-      g[k][2] = V.dL_drgb[3 * pix + 2];
-    } else {
-      T[k] = 1.f;
-      last[k] = 0u;
-      g[k][0] = g[k][1] = g[k][2] = 0.f;
+  const uint32_t xcd = blockIdx.x & 7u;
+  const uint32_t end = SEGMENTED ? plan[P_STARTS + xcd + 1] : 1u;
+  for (uint32_t it = SEGMENTED ? plan[P_STARTS + xcd] + (blockIdx.x >> 3) : 0u; it < end;
+       it += SEGMENTED ? gridDim.x >> 3 : 1u) {
+    const uint2 item = SEGMENTED ? items[it] : make_uint2(0u, 0u);   // batch tile, segment
+    const int64_t gt = SEGMENTED ? (int64_t)item.x
+                       : db->nviews == 1 ? ordered_tile(blockIdx.x, db->views[0].group_order, total_tiles)
+                                         : xcd_tile(blockIdx.x);
+    if (gt < 0 || gt >= total_tiles) return;
+    const int v = view_of_block(db->tile_prefix, db->nviews, gt);
+    const ViewDesc& V = db->views[v];
+    const int lt = (int)(gt - db->tile_prefix[v]);
+    const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
+    const int px = tx * kTile + (lane & 15);
+    const int py0 = ty * kTile + (lane >> 4);
+    const float pxf = (float)px;
+    const uint2 rg = V.ranges[lt];
+    const uint32_t seg = SEGMENTED ? plan[P_SEG] : 0u;
+    const uint32_t first_pos = item.y * seg, end_pos = SEGMENTED ? first_pos + seg : ~0u;
+    float pyf[4], T[4], TfB[4], g[4][3], S[4][3];
+    uint32_t last[4];
+  #pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int py = py0 + 4 * k;
+      pyf[k] = (float)py;
+      S[k][0] = S[k][1] = S[k][2] = 0.f;
+      if (px < V.width && py < V.height) {
+        const size_t pix = (size_t)py * V.width + px;
+        T[k] = V.final_T[pix];
+        last[k] = V.n_contrib[pix];
+        g[k][0] = V.dL_drgb[3 * pix];
+        g[k][1] = V.dL_drgb[3 * pix + 1];
+        g[k][2] = V.dL_drgb[3 * pix + 2];
+      } else {
+        T[k] = 1.f;
+        last[k] = 0u;
+        g[k][0] = g[k][1] = g[k][2] = 0.f;
+      }
+      // T_final (bg . g): the background's share of dL/dalpha, divided by (1 - alpha) per splat
+      TfB[k] = T[k] * (V.bg[0] * g[k][0] + V.bg[1] * g[k][1] + V.bg[2] * g[k][2]);
     }
-    // T_final (bg . g): the background's share of dL/dalpha, divided by (1 - alpha) per splat
-    TfB[k] = T[k] * (V.bg[0] * g[k][0] + V.bg[1] * g[k][1] + V.bg[2] * g[k][2]);
-  }
-  // wave max of the last contributor position per band of 4 rows and over the tile, made scalars: the walk's
-  // loop control (positions, the parked-splat count, the flush test) then runs on the scalar unit instead of
-  // taking VALU issue slots, and a band skips its test of the splats behind all of its pixels' last ones
-  uint32_t band_last[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    uint32_t m = last[k];
-    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-    band_last[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
-  }
-  const uint32_t maxlast = max(max(band_last[0], band_last[1]), max(band_last[2], band_last[3]));
-  const uint2 rg = V.ranges[lt];
-  const GlobalRec* rec = (const GlobalRec*)(V.rec);
-  // global address space: the row stores then count only against vmcnt, and the LDS waits of the following
-  // splats do not wait for them (flat stores count against lgkmcnt too)
-  GlobalVec4* rows = (GlobalVec4*)(V.grad_rows);
-  GlobalU32* bits = (GlobalU32*)(V.grad_bits);
-  int nslot = 0;
-  for (int hi = (int)maxlast; hi > 0; hi -= 64) {
-    const int lo = max(0, hi - 64);
-    const int cnt = hi - lo;
-    if (lane < cnt) {
-      const uint2 pr = sorted_pairs[rg.x + lo + lane];   // (splat index, slot)
-      const float4 a = rec_load(rec, 4 * (size_t)pr.x);
-      const float4 b = rec_load(rec, 4 * (size_t)pr.x + 1);
-      const float4 c = rec_load(rec, 4 * (size_t)pr.x + 2);
-      sA[lane] = make_float4(a.x, a.y, a.z, a.w);
-      sB[lane] = b;
-      sC[lane] = make_float4(c.x, c.y, c.z, __uint_as_float(pr.y));
-      sIdx[lane] = (uint32_t)db->item_prefix[v] + pr.x;
-      sLo[lane] = V.slot_off[pr.x];
-    }
-    __syncthreads();
-    for (int j = cnt - 1; j >= 0; --j) {
-      const float4 A = sA[j];
-      const float4 B = sB[j];
-      const float4 Cc = sC[j];
-      const uint32_t pos = (uint32_t)(lo + j);
-      const float bb = A.w + A.w;
-      // per lane: sums over its pixels of dq (a dx + b dy), dq (b dx + c dy), dq dx^2, dq dx dy, dq dy^2
-      // (dq = dL/dq; halves of the mean2D and b gradients), of G dL/dalpha (opacity), of alpha T g
-      // (colour) and, for GEF, of dL/dbeta
-      float su = 0.f, sv = 0.f, pa = 0.f, pb = 0.f, pc = 0.f, po = 0.f, pr = 0.f, pg = 0.f, pbl = 0.f, pbeta = 0.f;
-      bool entered = false;   // wave-uniform: some row band had a pixel that took the splat
+      if constexpr (SEGMENTED) {
+      const GlobalRec* ck = (const GlobalRec*)V.ckpt + ((size_t)V.tile_ckpt[lt] + item.y) * kTilePx + lane;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        if (pos >= band_last[k]) continue;   // scalar: every pixel of the band composited its last splat before
-        float dx, dy;
-        const float q0 = pair_q(A.x, A.y, A.z, bb, B.x, pxf, pyf[k], dx, dy);
-        const bool valid = (pos < last[k]) && (q0 <= B.y);
-        if (!__any(valid)) continue;   // wave-uniform: no pixel of this row band took the splat
-        entered = true;
-        // straight-line for every lane; a pixel that did not take the splat gets alpha = 0 (T, S and every
-        // accumulated term are then unchanged: 1/(1 - 0) = 1 exactly)
-        const float q = clamp_q(q0);
-        float G, qb = 0.f, lq = 0.f;
-        if (FALLOFF == GES_FALLOFF_PHI) {
-          G = fast_exp2(kNegHalfLog2e * q);
-        } else {
-          lq = fast_log2(q);
-          qb = fast_exp2(0.5f * B.w * lq);
-          G = fast_exp2(kNegHalfLog2e * qb);
+        if (last[k] > end_pos) {   // the walk of this pixel, 16 (row + 4 k) + column, goes on behind the segment
+          const Vec4 c = ck[64 * k];
+          T[k] = c.x;
+          S[k][0] = c.y;
+          S[k][1] = c.z;
+          S[k][2] = c.w;
+          last[k] = end_pos;
+        } else if (last[k] <= first_pos) {
+          last[k] = 0u;
         }
-        const float oG = B.z * G;
-        const bool clamped = oG > kAlphaMax;
-        const float alpha = valid ? (clamped ? kAlphaMax : oG) : 0.f;
-        const float inv = valid ? fast_rcp(1.f - alpha) : 1.f;
-        T[k] = T[k] * inv;                 // transmittance before this splat (unchanged: inv = 1 exactly)
-        const float w = alpha * T[k];
-        pr = __builtin_fmaf(w, g[k][0], pr);
-        pg = __builtin_fmaf(w, g[k][1], pg);
-        pbl = __builtin_fmaf(w, g[k][2], pbl);
-        const float d0 = Cc.x - S[k][0], d1 = Cc.y - S[k][1], d2 = Cc.z - S[k][2];
-        float dalpha = __builtin_fmaf(d0, g[k][0], __builtin_fmaf(d1, g[k][1], d2 * g[k][2]));
-        dalpha = __builtin_fmaf(dalpha, T[k], -TfB[k] * inv);
-        S[k][0] = __builtin_fmaf(alpha, d0, S[k][0]);
-        S[k][1] = __builtin_fmaf(alpha, d1, S[k][1]);
-        S[k][2] = __builtin_fmaf(alpha, d2, S[k][2]);
-        // below the clamp: dL/do = G dL/dalpha and G dL/dG = alpha dL/dalpha = o (G dL/dalpha); above it
-        // both are 0.  Per pixel only gd = G dL/dalpha is formed: the opacity o and the constant of dG/dq
-        // are common to the splat's terms and multiply its row sums once (dq below is dL/dq / (o k)).
-        const float gd = (valid && !clamped) ? G * dalpha : 0.f;
-        po += gd;
-        float dq;
-        if (FALLOFF == GES_FALLOFF_PHI) {
-          dq = q0 >= 0.f ? gd : 0.f;   // dG/dq = -G/2: k = -1/2
-        } else {
-          // dG/dq = -(beta/4) q^(beta/2 - 1) G  (q floored at 1e-12): k = -beta/4;
-          // dG/dbeta = -(1/4) q^(beta/2) ln q G: the row sum of q^(beta/2) log2 q gd takes -(ln 2)/4 o
-          const float qf = __int_as_float(max(__float_as_int(q), __float_as_int(1e-12f)));   // q >= +0
-          const float qpow = fast_exp2((0.5f * B.w - 1.f) * fast_log2(qf));
-          dq = q0 >= 0.f ? qpow * gd : 0.f;
-          pbeta = __builtin_fmaf(q > 0.f ? qb * lq : 0.f, gd, pbeta);
-        }
-        const float dqdx = dq * dx, dqdy = dq * dy;
-        su = __builtin_fmaf(dq, __builtin_fmaf(A.z, dx, A.w * dy), su);
-        sv = __builtin_fmaf(dq, __builtin_fmaf(A.w, dx, B.x * dy), sv);
-        pa = __builtin_fmaf(dqdx, dx, pa);
-        pb = __builtin_fmaf(dqdx, dy, pb);
-        pc = __builtin_fmaf(dqdy, dy, pc);
-      }
-      if (entered) {
-        // rows of 16 lanes reduce in registers: the first 8 sums by a reduce-scatter (after it, lanes 2i and
-        // 2i+1 of a row hold row sum i), the blue and beta sums by a full row sum; the row's lanes then park
-        // the 10 sums in LDS, each scaled by the splat's common factor (o k for the dq sums, o for dL/dbeta)
-        const float e = row_scatter8(su, sv, pa, pb, pc, po, pr, pg, lane);
-        const float r8 = row_sum(pbl);
-        const float r9 = FALLOFF == GES_FALLOFF_GEF ? row_sum(pbeta) : 0.f;
-        const float kq = FALLOFF == GES_FALLOFF_PHI ? -0.5f * B.z : (-0.25f * B.w) * B.z;
-        float* d = sRed[nslot][row];
-        const int idx = (lane >> 1) & 7;
-        if ((lane & 1) == 0) d[idx] = idx < 5 ? kq * e : e;
-        if ((lane & 15) == 15) {
-          d[8] = r8;
-          d[9] = FALLOFF == GES_FALLOFF_GEF ? (-0.25f * 0.69314718055994531f * B.z) * r9 : 0.f;
-        }
-        if (lane == 0) {
-          sSlot[nslot] = __float_as_uint(Cc.w);
-          sItem[nslot] = sIdx[j];
-          sFirst[nslot] = sLo[j];
-        }
-        ++nslot;
-      }
-      if (nslot == kFlush || (j == 0 && hi - 64 <= 0 && nslot > 0)) {
-        // one lane per parked splat: add the four row sums and store the tile's sums of the splat, the splat's
-        // batch item and its first candidate slot in the row of its slot (the row reduction adds a splat's rows
-        // in slot order), marking the slot
-        __syncthreads();
-        if (lane < nslot) {   // entries 0 .. nslot-1 hold row partials
-          const uint32_t slot = sSlot[lane];
-          float val[10];
-#pragma unroll
-          for (int c = 0; c < 10; ++c)
-            val[c] = (sRed[lane][0][c] + sRed[lane][1][c]) + (sRed[lane][2][c] + sRed[lane][3][c]);
-          val[0] = 2.f * val[0];   // dL/du = 2 sum dq (a dx + b dy)
-          val[1] = 2.f * val[1];   // dL/dv = 2 sum dq (b dx + c dy)
-          val[3] = 2.f * val[3];   // dL/db = 2 sum dq dx dy
-          if (FALLOFF != GES_FALLOFF_GEF) val[9] = 0.f;
-          GlobalVec4* r = rows + (size_t)slot * (kRowFloats / 4);
-          Vec4 v0, v1, v2;
-          v0[0] = val[0]; v0[1] = val[1]; v0[2] = val[2]; v0[3] = val[3];
-          v1[0] = val[4]; v1[1] = val[5]; v1[2] = val[6]; v1[3] = val[7];
-          v2[0] = val[8]; v2[1] = val[9]; v2[2] = __uint_as_float(sItem[lane]); v2[3] = __uint_as_float(sFirst[lane]);
-          r[0] = v0;
-          r[1] = v1;
-          r[2] = v2;
-          __hip_atomic_fetch_or(bits + (slot >> 5), 1u << (slot & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        nslot = 0;
       }
     }
-    __syncthreads();
+    // wave max of the last contributor position per band of 4 rows and over the tile, made scalars: the walk's
+    // loop control (positions, the parked-splat count, the flush test) then runs on the scalar unit instead of
+    // taking VALU issue slots, and a band skips its test of the splats behind all of its pixels' last ones
+    uint32_t band_last[4];
+  #pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint32_t m = last[k];
+      for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+      band_last[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    }
+    const uint32_t maxlast = max(max(band_last[0], band_last[1]), max(band_last[2], band_last[3]));
+    const GlobalRec* rec = (const GlobalRec*)(V.rec);
+    // global address space: the row stores then count only against vmcnt, and the LDS waits of the following
+    // splats do not wait for them (flat stores count against lgkmcnt too)
+    GlobalVec4* rows = (GlobalVec4*)(V.grad_rows);
+    GlobalU32* bits = (GlobalU32*)(V.grad_bits);
+    int nslot = 0;
+    const int stop = __builtin_amdgcn_readfirstlane((int)first_pos);
+    for (int hi = (int)maxlast; hi > stop; hi -= 64) {
+      const int lo = max(stop, hi - 64);
+      const int cnt = hi - lo;
+      if (lane < cnt) {
+        const uint2 pr = sorted_pairs[rg.x + lo + lane];   // (splat index, slot)
+        const float4 a = rec_load(rec, 4 * (size_t)pr.x);
+        const float4 b = rec_load(rec, 4 * (size_t)pr.x + 1);
+        const float4 c = rec_load(rec, 4 * (size_t)pr.x + 2);
+        sA[lane] = make_float4(a.x, a.y, a.z, a.w);
+        sB[lane] = b;
+        sC[lane] = make_float4(c.x, c.y, c.z, __uint_as_float(pr.y));
+        sIdx[lane] = (uint32_t)db->item_prefix[v] + pr.x;
+        sLo[lane] = V.slot_off[pr.x];
+      }
+      __syncthreads();
+      for (int j = cnt - 1; j >= 0; --j) {
+        const float4 A = sA[j];
+        const float4 B = sB[j];
+        const float4 Cc = sC[j];
+        const uint32_t pos = (uint32_t)(lo + j);
+        const float bb = A.w + A.w;
+        // per lane: sums over its pixels of dq (a dx + b dy), dq (b dx + c dy), dq dx^2, dq dx dy, dq dy^2
+        // (dq = dL/dq; halves of the mean2D and b gradients), of G dL/dalpha (opacity), of alpha T g
+        // (colour) and, for GEF, of dL/dbeta
+        float su = 0.f, sv = 0.f, pa = 0.f, pb = 0.f, pc = 0.f, po = 0.f, pr = 0.f, pg = 0.f, pbl = 0.f, pbeta = 0.f;
+        bool entered = false;   // wave-uniform: some row band had a pixel that took the splat
+  #pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (pos >= band_last[k]) continue;   // scalar: every pixel of the band composited its last splat before
+          float dx, dy;
+          const float q0 = pair_q(A.x, A.y, A.z, bb, B.x, pxf, pyf[k], dx, dy);
+          const bool valid = (pos < last[k]) && (q0 <= B.y);
+          if (!__any(valid)) continue;   // wave-uniform: no pixel of this row band took the splat
+          entered = true;
+          // straight-line for every lane; a pixel that did not take the splat gets alpha = 0 (T, S and every
+          // accumulated term are then unchanged: 1/(1 - 0) = 1 exactly)
+          const float q = clamp_q(q0);
+          float G, qb = 0.f, lq = 0.f;
+          if (FALLOFF == GES_FALLOFF_PHI) {
+            G = fast_exp2(kNegHalfLog2e * q);
+          } else {
+            lq = fast_log2(q);
+            qb = fast_exp2(0.5f * B.w * lq);
+            G = fast_exp2(kNegHalfLog2e * qb);
+          }
+          const float oG = B.z * G;
+          const bool clamped = oG > kAlphaMax;
+          const float alpha = valid ? (clamped ? kAlphaMax : oG) : 0.f;
+          const float inv = valid ? fast_rcp(1.f - alpha) : 1.f;
+          T[k] = T[k] * inv;                 // transmittance before this splat (unchanged: inv = 1 exactly)
+          const float w = alpha * T[k];
+          pr = __builtin_fmaf(w, g[k][0], pr);
+          pg = __builtin_fmaf(w, g[k][1], pg);
+          pbl = __builtin_fmaf(w, g[k][2], pbl);
+          const float d0 = Cc.x - S[k][0], d1 = Cc.y - S[k][1], d2 = Cc.z - S[k][2];
+          float dalpha = __builtin_fmaf(d0, g[k][0], __builtin_fmaf(d1, g[k][1], d2 * g[k][2]));
+          dalpha = __builtin_fmaf(dalpha, T[k], -TfB[k] * inv);
+          S[k][0] = __builtin_fmaf(alpha, d0, S[k][0]);
+          S[k][1] = __builtin_fmaf(alpha, d1, S[k][1]);
+          S[k][2] = __builtin_fmaf(alpha, d2, S[k][2]);
+          // below the clamp: dL/do = G dL/dalpha and G dL/dG = alpha dL/dalpha = o (G dL/dalpha); above it
+          // both are 0.  Per pixel only gd = G dL/dalpha is formed: the opacity o and the constant of dG/dq
+          // are common to the splat's terms and multiply its row sums once (dq below is dL/dq / (o k)).
+          const float gd = (valid && !clamped) ? G * dalpha : 0.f;
+          po += gd;
+          float dq;
+          if (FALLOFF == GES_FALLOFF_PHI) {
+            dq = q0 >= 0.f ? gd : 0.f;   // dG/dq = -G/2: k = -1/2
+          } else {
+            // dG/dq = -(beta/4) q^(beta/2 - 1) G  (q floored at 1e-12): k = -beta/4;
+            // dG/dbeta = -(1/4) q^(beta/2) ln q G: the row sum of q^(beta/2) log2 q gd takes -(ln 2)/4 o
+            const float qf = __int_as_float(max(__float_as_int(q), __float_as_int(1e-12f)));   // q >= +0
+            const float qpow = fast_exp2((0.5f * B.w - 1.f) * fast_log2(qf));
+            dq = q0 >= 0.f ? qpow * gd : 0.f;
+            pbeta = __builtin_fmaf(q > 0.f ? qb * lq : 0.f, gd, pbeta);
+          }
+          const float dqdx = dq * dx, dqdy = dq * dy;
+          su = __builtin_fmaf(dq, __builtin_fmaf(A.z, dx, A.w * dy), su);
+          sv = __builtin_fmaf(dq, __builtin_fmaf(A.w, dx, B.x * dy), sv);
+          pa = __builtin_fmaf(dqdx, dx, pa);
+          pb = __builtin_fmaf(dqdx, dy, pb);
+          pc = __builtin_fmaf(dqdy, dy, pc);
+        }
+        if (entered) {
+          // rows of 16 lanes reduce in registers: the first 8 sums by a reduce-scatter (after it, lanes 2i and
+          // 2i+1 of a row hold row sum i), the blue and beta sums by a full row sum; the row's lanes then park
+          // the 10 sums in LDS, each scaled by the splat's common factor (o k for the dq sums, o for dL/dbeta)
+          const float e = row_scatter8(su, sv, pa, pb, pc, po, pr, pg, lane);
+          const float r8 = row_sum(pbl);
+          const float r9 = FALLOFF == GES_FALLOFF_GEF ? row_sum(pbeta) : 0.f;
+          const float kq = FALLOFF == GES_FALLOFF_PHI ? -0.5f * B.z : (-0.25f * B.w) * B.z;
+          float* d = sRed[nslot][row];
+          const int idx = (lane >> 1) & 7;
+          if ((lane & 1) == 0) d[idx] = idx < 5 ? kq * e : e;
+          if ((lane & 15) == 15) {
+            d[8] = r8;
+            d[9] = FALLOFF == GES_FALLOFF_GEF ? (-0.25f * 0.69314718055994531f * B.z) * r9 : 0.f;
+          }
+          if (lane == 0) {
+            sSlot[nslot] = __float_as_uint(Cc.w);
+            sItem[nslot] = sIdx[j];
+            sFirst[nslot] = sLo[j];
+          }
+          ++nslot;
+        }
+        if (nslot == kFlush || (j == 0 && hi - 64 <= stop && nslot > 0)) {
+          // one lane per parked splat: add the four row sums and store the tile's sums of the splat, the splat's
+          // batch item and its first candidate slot in the row of its slot (the row reduction adds a splat's rows
+          // in slot order), marking the slot
+          __syncthreads();
+          if (lane < nslot) {   // entries 0 .. nslot-1 hold row partials
+            const uint32_t slot = sSlot[lane];
+            float val[10];
+  #pragma unroll
+            for (int c = 0; c < 10; ++c)
+              val[c] = (sRed[lane][0][c] + sRed[lane][1][c]) + (sRed[lane][2][c] + sRed[lane][3][c]);
+            val[0] = 2.f * val[0];   // dL/du = 2 sum dq (a dx + b dy)
+            val[1] = 2.f * val[1];   // dL/dv = 2 sum dq (b dx + c dy)
+            val[3] = 2.f * val[3];   // dL/db = 2 sum dq dx dy
+            if (FALLOFF != GES_FALLOFF_GEF) val[9] = 0.f;
+            GlobalVec4* r = rows + (size_t)slot * (kRowFloats / 4);
+            Vec4 v0, v1, v2;
+            v0[0] = val[0]; v0[1] = val[1]; v0[2] = val[2]; v0[3] = val[3];
+            v1[0] = val[4]; v1[1] = val[5]; v1[2] = val[6]; v1[3] = val[7];
+            v2[0] = val[8]; v2[1] = val[9]; v2[2] = __uint_as_float(sItem[lane]); v2[3] = __uint_as_float(sFirst[lane]);
+            r[0] = v0;
+            r[1] = v1;
+            r[2] = v2;
+            __hip_atomic_fetch_or(bits + (slot >> 5), 1u << (slot & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+          __syncthreads();
+          nslot = 0;
+        }
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -617,7 +805,7 @@ __device__ __forceinline__ int group_bucket(const uint32_t* work, int64_t g, int
   return kOrderBuckets - 1 - (int)min(w, (uint32_t)(kOrderBuckets - 1));
 }
 
-// One block: every view's per-tile pair statistics summed into its header ([2] examined, [3] composited);
+// One block per view: its per-tile pair statistics summed into its header ([2] examined, [3] composited);
 // for a single view, also the order of its tile groups for the backward pass: a counting sort on the
 // group's longest walk, heaviest first (the order within a bucket is immaterial).
 __global__ void __launch_bounds__(1024) raster_stats_kernel(const DeviceBatch* __restrict__ db) {
@@ -625,8 +813,8 @@ __global__ void __launch_bounds__(1024) raster_stats_kernel(const DeviceBatch* _
   __shared__ uint32_t cursor[kOrderBuckets];
   __shared__ uint32_t wsum[16];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int v = 0; v < db->nviews; ++v) {
-    const ViewDesc& V = db->views[v];
+  const ViewDesc& V = db->views[blockIdx.x];
+  {
     const int T = V.tiles_x * V.tiles_y;
     unsigned long long e = 0, c = 0;
     for (int t = threadIdx.x; t < T; t += 1024) {
@@ -645,10 +833,8 @@ __global__ void __launch_bounds__(1024) raster_stats_kernel(const DeviceBatch* _
       V.header[2] = se;
       V.header[3] = sc;
     }
-    __syncthreads();   // part[] is rewritten for the next view
   }
   if (db->nviews != 1) return;
-  const ViewDesc& V = db->views[0];
   const int64_t tiles = (int64_t)V.tiles_x * V.tiles_y;
   const int64_t ngroups = (tiles + kXcdGroup - 1) / kXcdGroup;
   const int tid = threadIdx.x;
@@ -674,34 +860,149 @@ __global__ void __launch_bounds__(1024) raster_stats_kernel(const DeviceBatch* _
   }
 }
 
+// Before the backward raster: the blocks past the first clear the row marks; block 0 plans the walk of a frame
+// that is to be cut (items not NULL).  Its segment is the length that gives about kItemTarget items (a multiple
+// of 64, the backward's staged batch), longer walks are cut there, and every piece is a work item.  Tile groups
+// (tiles, in a frame of few) go to the XCDs in turn, heaviest walks first where the forward ordered them, so
+// that a group's records meet in one L2 and the last items to start are short; the items of XCD x are
+// items[plan[P_STARTS + x], plan[P_STARTS + x + 1]).  There are at most as many items as walked list positions,
+// and a boundary stands for at least 64 of them, so items and cut tiles fit the buffers of the tile sort.
+constexpr uint32_t kOrderTiles = 2048;
+// Targets of 2,560 / 4,096 / 8,192 / 16,384: four views of 512x512 686 / 602 / 561 / 568 us, GEF 300k at 801x533
+// 1,025 / 868 / 864 / 845; smaller frames reach the shortest segment with any.
+constexpr uint32_t kItemTarget = kMaxCheckpoints;   // boundaries <= walked positions / segment <= this
+__global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatch* __restrict__ db, uint2* items,
+                                                                uint32_t* cut_tiles, uint32_t* plan, uint32_t* bits,
+                                                                size_t nwords) {
+  if (blockIdx.x > 0) {
+    const size_t n4 = nwords / 4, step = (size_t)(gridDim.x - 1) * 1024;
+    const size_t i0 = (size_t)(blockIdx.x - 1) * 1024 + threadIdx.x;
+    for (size_t i = i0; i < n4; i += step) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 < nwords - 4 * n4) bits[4 * n4 + i0] = 0u;
+    return;
+  }
+  if (!items) return;
+  __shared__ unsigned long long wsum[16];
+  __shared__ unsigned long long carry;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const bool one = db->nviews == 1;
+  const uint32_t tiles = (uint32_t)db->tile_prefix[db->nviews], view_tiles = (uint32_t)db->tile_prefix[1];
+  const uint32_t* work0 = db->views[0].tile_work;
+  auto walk = [&](uint32_t t) -> uint32_t {   // the views of a backward share a resolution
+    const uint32_t v = one ? 0u : t / view_tiles;
+    return (one ? work0 : db->views[v].tile_work)[t - v * view_tiles];
+  };
+  unsigned long long sum = 0;   // walked positions
+  for (uint32_t t = threadIdx.x; t < tiles; t += 1024) sum += walk(t);
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0) wsum[w] = sum;
+  if (threadIdx.x == 0) carry = 0ull;
+  __syncthreads();
+  sum = 0;
+  for (int k = 0; k < 16; ++k) sum += wsum[k];
+  __syncthreads();
+  const uint32_t seg = (uint32_t)max(1ull, (sum + 64ull * kItemTarget - 1) / (64ull * kItemTarget)) * 64u;
+  // positions of the list order: XCD by XCD, a padded run of groups each; one tile per thread and round
+  const uint32_t gs = tiles < kOrderTiles ? 1u : (uint32_t)kXcdGroup;   // tiles dealt to an XCD together
+  const uint32_t ngroups = (tiles + gs - 1) / gs, run = (ngroups + 7) / 8 * gs;
+  const uint32_t* order = one && gs > 1 ? db->views[0].group_order : nullptr;
+  for (uint32_t o0 = 0; o0 < 8 * run; o0 += 1024) {
+    const uint32_t o = o0 + threadIdx.x, x = o / run, i = o - x * run;
+    uint32_t g = 8 * (i / gs) + x, t = tiles, ns = 0;
+    if (x < 8 && g < ngroups) {
+      if (order) g = order[g];
+      t = g < ngroups ? g * gs + i % gs : tiles;
+      if (t < tiles) ns = (walk(t) + seg - 1u) / seg;
+    }
+    // items, walks and cut walks before this tile (at most 2^32, 2^16 and 2^16: see cut_walks)
+    const unsigned long long mine = ((unsigned long long)ns << 32) | (ns ? 1u << 16 : 0u) | (ns > 1 ? 1u : 0u);
+    unsigned long long s = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const unsigned long long y = __shfl_up(s, d, 64);
+      if (lane >= d) s += y;
+    }
+    if (lane == 63) wsum[w] = s;
+    __syncthreads();
+    unsigned long long at = carry + s - mine;
+    for (int k = 0; k < w; ++k) at += wsum[k];
+    const uint32_t first = (uint32_t)(at >> 32), walks = (uint32_t)at >> 16, cut = (uint32_t)at & 0xffffu;
+    if (x < 8 && i == 0) plan[P_STARTS + x] = first;
+    if (ns > 1) {
+      const uint32_t v = one ? 0u : t / view_tiles;
+      cut_tiles[cut] = t;
+      db->views[v].tile_ckpt[t - v * view_tiles] = first - walks;   // the boundaries of the walks before it
+    }
+    for (uint32_t k = 0; k < ns; ++k) items[first + k] = make_uint2(t, k);
+    __syncthreads();
+    if (threadIdx.x == 1023) carry = at + mine;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    plan[P_STARTS + 8] = (uint32_t)(carry >> 32);
+    plan[P_CUT] = (uint32_t)carry & 0xffffu;
+    plan[P_SEG] = seg;
+  }
+}
+
+// Cutting pays where the longest walk, at about 0.5 us a splat, outlasts the whole frame's work spread over the
+// device (0.27 ns a walked position); from about 6,000 tiles on it does
+// not (cutting there: 1600x1040 354 -> 457 us, 1920x1080 420 -> 524, heavy overlap 1,366 -> 1,670).
+static bool cut_walks(const Batch& b) { return b.total_tiles <= 6144; }
+
+hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
+                                   hipStream_t stream) {
+  const size_t clear = std::min<size_t>(1024, (nwords + 4095) / 4096);
+  hipLaunchKernelGGL(backward_prepare_kernel, dim3((unsigned)(1 + clear)), dim3(1024), 0, stream, dbatch,
+                     cut_walks(b) ? b.kw.pv[1] : nullptr, b.kw.table, b.kw.totals, bits, nwords);
+  return hipGetLastError();
+}
+
 hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
   if (b.total_tiles == 0) return hipSuccess;
   const int64_t span = 8 * kXcdGroup;   // the grid covers whole rounds of groups
   const dim3 grid((unsigned)((b.total_tiles + span - 1) / span * span));
-  // every view of a batch shares the falloff (the server fixes it per instance)
-  if (b.falloff != GES_FALLOFF_GEF)   // Gaussian falloff (PHI, PHI_EXACT)
-    hipLaunchKernelGGL(raster_forward_kernel<GES_FALLOFF_PHI>, grid, dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs,
-                       b.total_tiles, b.key_capacity);
-  else
-    hipLaunchKernelGGL(raster_forward_kernel<GES_FALLOFF_GEF>, grid, dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs,
-                       b.total_tiles, b.key_capacity);
+  // every view of a batch shares the falloff (the server fixes it per instance).  Splats per group: 4 shorten
+  // the serial walk, 2 leave registers for more waves per SIMD, which counts once the frame fills the device
+  // (4 against 2, with the statistics pass: 512x512 153 / 162 us, 801x533 GEF 318 / 361, four views of 512x512
+  // 274 / 274, 1600x1040 209 / 200, 1920x1080 252 / 239, heavy overlap 710 / 678)
+  const bool phi = b.falloff != GES_FALLOFF_GEF, few = b.total_tiles <= 4096;   // PHI and PHI_EXACT: Gaussian
+  void (*kernel)(const DeviceBatch*, const uint2*, int64_t, uint64_t) =
+      phi ? (few ? raster_forward_kernel<GES_FALLOFF_PHI, 4> : raster_forward_kernel<GES_FALLOFF_PHI, 2>)
+          : (few ? raster_forward_kernel<GES_FALLOFF_GEF, 4> : raster_forward_kernel<GES_FALLOFF_GEF, 2>);
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs, b.total_tiles,
+                     b.key_capacity);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(raster_stats_kernel, dim3(1), dim3(1024), 0, stream, dbatch);
+  hipLaunchKernelGGL(raster_stats_kernel, dim3((unsigned)b.nviews), dim3(1024), 0, stream, dbatch);
   return hipGetLastError();
 }
 
 hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
   if (b.total_tiles == 0) return hipSuccess;
-  const int ordered = b.nviews == 1;   // the forward's statistics pass ordered the groups of a single view
-  const int64_t span = 8 * kXcdGroup;   // the grid covers whole rounds of groups
-  const dim3 grid((unsigned)((b.total_tiles + span - 1) / span * span));
-  if (b.falloff != GES_FALLOFF_GEF)
-    hipLaunchKernelGGL(raster_backward_kernel<GES_FALLOFF_PHI>, grid, dim3(64), 0, stream, dbatch, b.sorted_pairs,
-                       b.total_tiles, ordered);
-  else
-    hipLaunchKernelGGL(raster_backward_kernel<GES_FALLOFF_GEF>, grid, dim3(64), 0, stream, dbatch, b.sorted_pairs,
-                       b.total_tiles, ordered);
+  const bool phi = b.falloff != GES_FALLOFF_GEF;
+  if (!cut_walks(b)) {
+    const int64_t span = 8 * kXcdGroup;   // the grid covers whole rounds of groups
+    const dim3 grid((unsigned)((b.total_tiles + span - 1) / span * span));
+    hipLaunchKernelGGL((phi ? raster_backward_kernel<GES_FALLOFF_PHI, false>
+                            : raster_backward_kernel<GES_FALLOFF_GEF, false>),
+                       grid, dim3(64), 0, stream, dbatch, b.sorted_pairs, b.total_tiles, nullptr, nullptr);
+    return hipGetLastError();
+  }
+  const int64_t most = max_checkpoints(b.key_capacity);   // boundaries, hence cut tiles
+  if (most > 0) {
+    const dim3 grid((unsigned)std::min<int64_t>(b.total_tiles, most));
+    hipLaunchKernelGGL((phi ? raster_recover_kernel<GES_FALLOFF_PHI> : raster_recover_kernel<GES_FALLOFF_GEF>), grid,
+                       dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs, b.kw.table, b.kw.totals);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  // a block per item, whichever XCD it belongs to, up to a few rounds of the device (the item counts are known
+  // there only): blocks past the items leave at once, items past the blocks are taken in turn
+  const int64_t blocks = std::min<int64_t>(8 * (b.total_tiles + most), 16384);
+  hipLaunchKernelGGL((phi ? raster_backward_kernel<GES_FALLOFF_PHI, true> : raster_backward_kernel<GES_FALLOFF_GEF, true>),
+                     dim3((unsigned)blocks), dim3(64), 0, stream, dbatch, b.sorted_pairs, b.total_tiles, b.kw.pv[1],
+                     b.kw.totals);
   return hipGetLastError();
 }
 
