@@ -11,8 +11,10 @@
  * Conventions shared by every entry point
  *   - All tensor arguments are DEVICE pointers to contiguous row-major FP32 (or the
  *     stated integer type) buffers owned by the caller.  The library never frees
- *     them and never allocates on the render path; the workspace buffers it needs
- *     are caller-allocated with the sizes returned by the *_query calls.
+ *     them and never allocates device memory on the render path; the workspace
+ *     buffers it needs are caller-allocated with the sizes returned by the *_query
+ *     calls.  (The first call that reads a slot count back allocates one page of
+ *     host memory for the process, which the device posts such counts to.)
  *   - Work is enqueued on `stream` (a hipStream_t; NULL = the null stream) and is
  *     asynchronous unless a call says otherwise.  Calls on one frame's buffers must
  *     be issued on one stream in the order preprocess -> forward -> backward.
@@ -123,7 +125,8 @@ ges_status ges_workspace_query(int64_t n, int32_t width, int32_t height, size_t*
 
 /* Size of the key workspace for num_keys candidate (tile, splat) slots of a width x height
  * frame with n splats: two buffers of (tile, splat index) pairs (16 B per slot, the sorted
- * splat ids first) and the digit table of the tile sort (1 B per 4 slots).  Width/height
+ * splat ids first), the digit table of the tile sort (1 B per 2 slots), one 48-byte row
+ * and a mark bit per slot for the backward pass, and its checkpoints (at most 32 MB).  Width/height
  * outside [1,16384]: GES_ERR_INVALID_ARGUMENT; num_keys >= 2^32-1: GES_ERR_CAPACITY. */
 ges_status ges_key_workspace_query(uint64_t num_keys, int64_t n, int32_t width, int32_t height,
                                    size_t* key_ws_bytes);
@@ -133,10 +136,12 @@ ges_status ges_key_workspace_query(uint64_t num_keys, int64_t n, int32_t width, 
  * mean2D, alpha-floor threshold, beta-dependent screen radius, tile rectangle and
  * SH colour; then sorts the listed splats by depth (ties by index) and lays out one
  * slot per candidate tile of each splat along that order.
- * num_keys_host: if not NULL, the call waits for the stream and stores the number
- * of candidate slots of this frame there -- the key capacity the frame needs, an upper
- * bound of its (tile, splat) keys (equal to it for GES_TILES_SQUARE) -- the only host
- * synchronisation of a frame.
+ * num_keys_host: if not NULL, the call waits for the number of candidate slots of this
+ * frame and stores it there -- the key capacity the frame needs, an upper bound of its
+ * (tile, splat) keys (equal to it for GES_TILES_SQUARE) -- the only host synchronisation
+ * of a frame.  When it returns, everything enqueued on the stream before the call has
+ * run and the splats have been read; the depth sort may still be running in splat_ws.
+ * Not available while the stream is being captured (DEVICE).
  * Errors: INVALID_ARGUMENT (see conventions), CAPACITY if splat_ws_bytes is too small. */
 ges_status ges_preprocess(const ges_splats* splats, const ges_camera* cam, const ges_raster_params* params,
                           void* splat_ws, size_t splat_ws_bytes, uint64_t* num_keys_host, void* stream);

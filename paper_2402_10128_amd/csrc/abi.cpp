@@ -14,6 +14,69 @@
 #include "frame.h"
 #include "ges_internal.h"
 
+namespace ges {
+namespace {
+// One page of host memory the device can write, for the slot counts of the calls under way; a call that finds no
+// free word reads its count from the device.  Kept for the life of the process (a kernel may be posting to it).
+constexpr int kMailSlots = 64;
+std::mutex g_mail_mu;
+unsigned long long* g_mail_page = nullptr;
+std::vector<int> g_mail_free;
+uint32_t g_mail_token = 0;
+}  // namespace
+
+CountMail mail_take() {
+  CountMail m;
+  std::lock_guard<std::mutex> lk(g_mail_mu);
+  if (!g_mail_page) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kMailSlots * 64, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+      (void)hipGetLastError();
+      return m;
+    }
+    std::memset(p, 0, kMailSlots * 64);
+    g_mail_page = static_cast<unsigned long long*>(p);
+    for (int k = 0; k < kMailSlots; ++k) g_mail_free.push_back(k);
+  }
+  if (g_mail_free.empty()) return m;
+  m.slot = g_mail_page + 8 * g_mail_free.back();
+  g_mail_free.pop_back();
+  if (++g_mail_token == 0) ++g_mail_token;   // 0 marks a word nobody posted to
+  m.token = g_mail_token;
+  return m;
+}
+
+// Only for a word whose count has arrived: after an error its kernel may still post, and it stays out of use.
+void mail_give(const CountMail& m) {
+  if (!m.slot) return;
+  std::lock_guard<std::mutex> lk(g_mail_mu);
+  g_mail_free.push_back((int)((m.slot - g_mail_page) / 8));
+}
+
+hipError_t mail_wait(const CountMail& m, const uint32_t* counter, hipStream_t stream, uint32_t* count) {
+  if (!m.slot) {
+    const hipError_t e = hipMemcpyAsync(count, counter, 4, hipMemcpyDeviceToHost, stream);
+    return e != hipSuccess ? e : hipStreamSynchronize(stream);
+  }
+  for (uint32_t spins = 1;; ++spins) {
+    bool ended = false;
+    if ((spins & 0x3fffu) == 0) {   // every 50 us or so: the stream may have failed
+      const hipError_t e = hipStreamQuery(stream);
+      if (e != hipSuccess && e != hipErrorNotReady) return e;
+      ended = e == hipSuccess;
+    }
+    const unsigned long long v = __atomic_load_n(m.slot, __ATOMIC_ACQUIRE);
+    if ((uint32_t)(v >> 32) == m.token) {
+      *count = (uint32_t)v;
+      return hipSuccess;
+    }
+    if (ended) return hipErrorUnknown;   // everything ran and nothing was posted
+    __builtin_ia32_pause();
+  }
+}
+
+}  // namespace ges
+
 namespace {
 
 thread_local std::string g_last_error;
@@ -174,16 +237,27 @@ ges_status preprocess_views(const ges_splats* splats, const ges_camera* cams, in
   const ges::ViewsPlan vp = ges::plan_views(splats->n, nv, cams[0].width, cams[0].height);
   if (splat_ws_bytes < vp.splat_bytes) return fail(GES_ERR_CAPACITY, "splat workspace too small");
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
+  ges::CountMail mail;
+  if (num_keys_host) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    GES_CHECK_HIP(hipStreamIsCapturing(stream, &capture), "capture status");
+    if (capture != hipStreamCaptureStatusNone) {
+      g_last_error = "the slot count cannot be read back while the stream is being captured";
+      return GES_ERR_DEVICE;
+    }
+    mail = ges::mail_take();
+  }
   GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, nullptr, nullptr, nullptr, stream), "upload");
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
+  b.mail = mail;
   const ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
   GES_CHECK_HIP(timed(GES_STAGE_PREPROCESS, stream, [&] { return ges::launch_preprocess(db, b, stream); }), "preprocess");
   GES_CHECK_HIP(timed(GES_STAGE_DEPTH_SORT, stream, [&] { return ges::launch_depth_sort(db, b, stream); }), "depth_sort");
   GES_CHECK_HIP(timed(GES_STAGE_KEY_SCAN, stream, [&] { return ges::launch_key_scan(db, b, stream); }), "key_scan");
   if (num_keys_host) {
     uint32_t k = 0;
-    GES_CHECK_HIP(hipMemcpyAsync(&k, b.keys_total, 4, hipMemcpyDeviceToHost, stream), "read num_keys");
-    GES_CHECK_HIP(hipStreamSynchronize(stream), "sync");
+    GES_CHECK_HIP(ges::mail_wait(mail, b.keys_total, stream, &k), "read num_keys");
+    ges::mail_give(mail);
     if (k == 0xffffffffu) return fail(GES_ERR_CAPACITY, "more than 2^32-2 candidate (tile, splat) pairs in one step");
     *num_keys_host = k;
   }

@@ -6,71 +6,134 @@
 //   1. depth sort (in ges_preprocess): the listed splats of every view, keyed by the depth bits the
 //      preprocess writes, in four stable 8-bit LSD radix passes carrying (candidate count, item); the first
 //      pass drops unlisted splats.  Stability keeps equal depths in index order.
+//      The first pass also adds up the candidates of all splats and posts the sum to the host, which has the
+//      key capacity a frame needs while the sort goes on.
 //   2. key scan: every listed splat owns one slot per candidate tile (tile_geom.h), laid out along the
-//      depth order; the offset of each 256-splat chunk and the batch's slot count (the key capacity a frame
-//      needs, read back by the host).
+//      depth order; the offset of each 256-splat chunk and the batch's slot count.
 //   3. duplicate (render): each wave takes 64 consecutive splats of the depth order, expands their
 //      candidates and tests one per lane; every slot receives (batch tile, splat index) or a dropped key.
 //      Slots are written in order, so the writes are contiguous.
 //   4. tile sort: stable LSD radix passes on the batch tile id (two for up to 65,536 tiles); the first
 //      drops the empty slots.  Pairs of one tile keep the depth order of step 3, hence (depth, index).
 //   5. ranges: each tile's [start, end) from the boundaries of the sorted tile ids (empty tiles (0, 0)).
+// Up to 8,192 items, steps 1 and 2 are one block working in LDS, and up to 8,192 slots so are 4 and 5.
 // HBM: per listed splat its record (64 B, gathered in depth order) and a few words; per slot 8 B written
 // by the duplication and 12 B read and written per radix pass.
 #include <algorithm>
 
 #include "ges_internal.h"
+#include "radix_small.h"
 #include "tile_geom.h"
 
 namespace ges {
 
 constexpr int kDepthPasses = 4;   // 31 key bits (positive binary32 depths)
 
-__global__ void clear_cells_kernel(uint32_t* cells) {
+// No splat: no sort runs, so nothing else would write the counts.
+__global__ void clear_cells_kernel(uint32_t* cells, unsigned long long* mail, uint32_t token) {
   if (threadIdx.x < 4) cells[threadIdx.x] = 0u;
+  if (threadIdx.x == 0 && mail) post_count(mail, token, 0ull);
 }
 
-hipError_t launch_depth_sort(const DeviceBatch* /*dbatch*/, Batch& b, hipStream_t stream) {
+// Words a coming render starts from: per view its header (keys, error word, pair statistics) and tile ranges.
+__device__ __forceinline__ void clear_views(const DeviceBatch* db) {   // by one block
+  for (int v = 0; v < db->nviews; ++v) {
+    const ViewDesc& V = db->views[v];
+    const int64_t T = (int64_t)V.tiles_x * V.tiles_y;
+    for (int64_t t = threadIdx.x; t < T; t += blockDim.x) V.ranges[t] = make_uint2(0u, 0u);
+    if (threadIdx.x < 4) V.header[threadIdx.x] = 0ull;
+  }
+}
+
+// The depth sort and key scan of up to kRadixSmall items as one block: the keys and their order in LDS.  A
+// launch takes about 4.6 us on the stream however little it does, and the general path has ten to fourteen (1k
+// splats at 64x64: depth sort and scan 73 -> 16 us, tile sort 24 -> 10).
+__global__ void __launch_bounds__(kSmallThreads) small_depth_kernel(const DeviceBatch* __restrict__ db, uint32_t items,
+                                                                    const uint32_t* __restrict__ keys,
+                                                                    const uint32_t* __restrict__ cand, uint2* order,
+                                                                    uint32_t* chunk_off, uint32_t* cells,
+                                                                    unsigned long long* mail, uint32_t token) {
+  __shared__ SmallSort L;
+  __shared__ unsigned long long wave_sum[kSmallThreads / 64];
+  __shared__ unsigned long long chunk_sum[kRadixSmall / 256];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  unsigned long long sum = 0;
+  for (uint32_t i = t; i < items; i += kSmallThreads) {
+    L.key[i] = keys[i];
+    L.perm[i] = (uint16_t)i;
+    sum += cand[i];   // 0 for an unlisted item
+  }
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0) wave_sum[w] = sum;
+  __syncthreads();
+  sum = 0;
+  for (int k = 0; k < kSmallThreads / 64; ++k) sum += wave_sum[k];
+  if (t == 0 && mail) post_count(mail, token, sum);   // the host goes on while the sort runs
+  uint32_t n = items;
+  for (int pass = 0; pass < kDepthPasses; ++pass) n = small_sort_pass(L, n, 8 * pass, 8, pass == 0);
+  // the order, and the slots before each chunk of 256 splats of it
+  for (uint32_t j0 = 0; j0 < n; j0 += kSmallThreads) {
+    const uint32_t j = j0 + t;
+    uint32_t c = 0;
+    if (j < n) {
+      const uint32_t i = L.perm[j];
+      c = cand[i];
+      order[j] = make_uint2(c, i);
+    }
+    unsigned long long s = c;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    __syncthreads();
+    if (lane == 0) wave_sum[w] = s;
+    __syncthreads();
+    if (t < kSmallThreads / 256)
+      chunk_sum[j0 / 256 + t] = ((wave_sum[4 * t] + wave_sum[4 * t + 1]) + wave_sum[4 * t + 2]) + wave_sum[4 * t + 3];
+  }
+  __syncthreads();
+  if (t * 256u < n) {
+    unsigned long long before = 0;
+    for (int k = 0; k < t; ++k) before += chunk_sum[k];
+    chunk_off[t] = before > 0xffffffffull ? 0xffffffffu : (uint32_t)before;
+  }
+  if (t == 0) {
+    cells[0] = n;
+    cells[1] = sum >= 0xffffffffull ? 0xffffffffu : (uint32_t)sum;
+    cells[2] = 0u;
+    cells[3] = 0u;
+  }
+  clear_views(db);
+}
+
+hipError_t launch_depth_sort(const DeviceBatch* dbatch, Batch& b, hipStream_t stream) {
   SortWs& w = b.sw;
-  const int sub = radix_sub((uint64_t)b.items, kRadixItemsDepth);
-  const uint32_t nb = radix_blocks((uint64_t)b.items, kRadixItemsDepth, sub);
-  if (nb == 0) {   // no splat: no pass runs, so nothing else would write the listed count
-    hipLaunchKernelGGL(clear_cells_kernel, dim3(1), dim3(64), 0, stream, w.cells);
-    w.depth_final = 1;
+  w.depth_final = (kDepthPasses - 1) & 1;   // the buffer of the last pass
+  if (b.items == 0) {
+    hipLaunchKernelGGL(clear_cells_kernel, dim3(1), dim3(64), 0, stream, w.cells, b.mail.slot, b.mail.token);
+    return hipGetLastError();
+  }
+  if (b.items <= kRadixSmall) {
+    hipLaunchKernelGGL(small_depth_kernel, dim3(1), dim3(kSmallThreads), 0, stream, dbatch, (uint32_t)b.items,
+                       w.item_key, w.item_cand, w.dv[w.depth_final], w.chunk_off, w.cells, b.mail.slot, b.mail.token);
     return hipGetLastError();
   }
   // the values are (candidate count, item) pairs, made by the first pass from the counts and the item
   // indices, so that the key scan and the duplication read the counts in depth order
-  const uint32_t* kin = w.item_key;
-  const uint2* vin = nullptr;
-  int cur = 0;
-  for (int pass = 0; pass < kDepthPasses; ++pass) {
-    RadixPass p{};
-    p.items = kRadixItemsDepth;
-    p.sub = sub;
-    p.bits = 8;
-    p.pair = 1;
-    p.keys_in = kin;
-    if (pass == 0) p.vals_in = w.item_cand;
-    else p.pvals_in = vin;
-    p.keys_out = w.dk[cur];
-    p.pvals_out = w.dv[cur];
-    p.count_dev = pass == 0 ? nullptr : &w.cells[0];
-    p.count_host = (uint32_t)b.items;
-    p.nblocks = nb;
-    p.shift = 8 * pass;
-    p.filter = pass == 0;
-    p.table = w.table;
-    p.totals = w.totals;
-    p.count_out = &w.cells[0];
-    hipError_t e = launch_radix_pass(p, stream);
-    if (e != hipSuccess) return e;
-    kin = w.dk[cur];
-    vin = w.dv[cur];
-    cur ^= 1;
-  }
-  w.depth_final = cur ^ 1;
-  return hipSuccess;
+  RadixSort s{};
+  s.passes = kDepthPasses;
+  for (int k = 0; k < kDepthPasses; ++k) { s.bits[k] = 8; s.shift[k] = 8 * k; }
+  s.keys = w.item_key;
+  s.vals = w.item_cand;
+  for (int k = 0; k < 2; ++k) { s.key_buf[k] = w.dk[k]; s.pair_buf[k] = w.dv[k]; }
+  s.count_host = (uint32_t)b.items;
+  s.sub = radix_sub((uint64_t)b.items);
+  s.nblocks = radix_blocks((uint64_t)b.items, s.sub);
+  s.table = w.table;
+  s.totals = w.totals;
+  s.kept = &w.cells[0];
+  s.weights = w.item_cand;
+  s.weight_sums = w.weights;
+  s.mail = b.mail.slot;
+  s.token = b.mail.token;
+  return launch_radix_sort(s, stream);
 }
 
 // Which view owns batch item j (linear scan over at most kMaxViews views).
@@ -141,16 +204,12 @@ __global__ void __launch_bounds__(1024) chunk_scan_kernel(const DeviceBatch* __r
     cells[2] = 0u;
     cells[3] = 0u;
   }
-  for (int v = 0; v < db->nviews; ++v) {
-    const ViewDesc& V = db->views[v];
-    const int64_t T = (int64_t)V.tiles_x * V.tiles_y;
-    for (int64_t t = threadIdx.x; t < T; t += 1024) V.ranges[t] = make_uint2(0u, 0u);
-    if (threadIdx.x < 4) V.header[threadIdx.x] = 0ull;   // keys, error word, pair statistics of the render
-  }
+  clear_views(db);
 }
 
 hipError_t launch_key_scan(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
   const SortWs& w = b.sw;
+  if (b.items > 0 && b.items <= kRadixSmall) return hipSuccess;   // part of the depth sort
   const int64_t chunks = (b.items + 255) / 256;
   if (chunks > 0) {
     hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, w.dv[w.depth_final], w.cells,
@@ -601,45 +660,90 @@ __global__ void __launch_bounds__(256) tile_ranges_kernel(const DeviceBatch* __r
   }
 }
 
+// The tile sort of up to kRadixSmall slots and its ranges as one block (see small_depth_kernel).  The last
+// buffer may be the one the duplication wrote: everything read from it is read before the first write.
+__global__ void __launch_bounds__(kSmallThreads) small_tile_kernel(const DeviceBatch* __restrict__ db, uint32_t* cells,
+                                                                   int tile_bits, int passes, const uint32_t* keys,
+                                                                   const uint32_t* ids, uint32_t* keys_out,
+                                                                   uint2* pairs_out, int64_t total_tiles) {
+  __shared__ SmallSort L;
+  const int t = threadIdx.x;
+  uint32_t n = min(cells[3], kRadixSmall);
+  for (uint32_t i = t; i < n; i += kSmallThreads) {
+    L.key[i] = keys[i];
+    L.perm[i] = (uint16_t)i;
+  }
+  __syncthreads();
+  int shift = 0;
+  for (int pass = 0; pass < passes; ++pass) {
+    const int left = passes - pass, bits = (tile_bits - shift + left - 1) / left;
+    n = small_sort_pass(L, n, shift, bits, pass == 0);
+    shift += bits;
+  }
+  uint32_t id[kRadixSmall / kSmallThreads];
+#pragma unroll
+  for (uint32_t r = 0; r < kRadixSmall / kSmallThreads; ++r) {
+    const uint32_t j = r * kSmallThreads + t;
+    id[r] = j < n ? ids[L.perm[j]] : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < kRadixSmall / kSmallThreads; ++r) {
+    const uint32_t j = r * kSmallThreads + t;
+    if (j >= n) break;
+    const uint32_t tile = L.key[j];
+    keys_out[j] = tile;
+    pairs_out[j] = make_uint2(id[r], L.perm[j]);
+    if ((int64_t)tile >= total_tiles) continue;   // not a tile of the batch (never written by the duplication)
+    const bool first = j == 0 || L.key[j - 1] != tile, last = j + 1 == n || L.key[j + 1] != tile;
+    if (!first && !last) continue;
+    const int v = view_of_block(db->tile_prefix, db->nviews, (int64_t)tile);
+    uint2* g = db->views[v].ranges + ((int64_t)tile - db->tile_prefix[v]);
+    if (first) g->x = j;
+    if (last) g->y = j + 1;
+  }
+  if (t == 0) cells[2] = n;
+}
+
 hipError_t launch_tile_sort(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
-  if (b.key_capacity == 0) return hipSuccess;
+  if (b.key_capacity == 0 || b.items == 0) return hipSuccess;   // no pair: the ranges are clear
   const SortWs& w = b.sw;
-  const int sub = radix_sub(b.key_capacity, kRadixItemsPair);
-  const uint32_t nb = radix_blocks(b.key_capacity, kRadixItemsPair, sub);
+  const KeyWs& k = b.kw;
+  const int X = b.dup_buffer;
+  if (((X + b.tile_passes) & 1) != 0 || b.tile_passes > kRadixMaxPasses) return hipErrorInvalidValue;
   // the tile bits split evenly over the passes (13 bits: 7 + 6), so that no pass scatters to more digit
   // runs than it must
   int bits = 1;
   while (bits < 32 && ((int64_t)1 << bits) < b.total_tiles) ++bits;
-  int shift = 0, cur = b.dup_buffer;
-  for (int pass = 0; pass < b.tile_passes; ++pass) {
-    const int left = b.tile_passes - pass;
-    const int pb = (bits - shift + left - 1) / left;
-    RadixPass p{};
-    p.items = kRadixItemsPair;
-    p.sub = sub;
-    p.bits = pb;
-    p.pair = 1;   // the first pass pairs each splat index with its slot
-    p.keys_in = b.kw.key[cur];
-    if (pass == 0) p.vals_in = reinterpret_cast<const uint32_t*>(b.kw.pv[cur]);
-    else p.pvals_in = b.kw.pv[cur];
-    p.keys_out = b.kw.key[cur ^ 1];
-    p.pvals_out = b.kw.pv[cur ^ 1];
-    p.count_dev = pass == 0 ? &w.cells[3] : &w.cells[2];
-    p.nblocks = nb;
-    p.shift = shift;
-    p.filter = pass == 0;
-    p.table = b.kw.table;
-    p.totals = b.kw.totals;
-    p.count_out = &w.cells[2];
-    hipError_t e = launch_radix_pass(p, stream);
-    if (e != hipSuccess) return e;
-    shift += pb;
-    cur ^= 1;
+  if (b.key_capacity <= kRadixSmall) {
+    hipLaunchKernelGGL(small_tile_kernel, dim3(1), dim3(kSmallThreads), 0, stream, dbatch, w.cells, bits,
+                       b.tile_passes, k.key[X], reinterpret_cast<const uint32_t*>(k.pv[X]), k.key[0], k.pv[0],
+                       b.total_tiles);
+    return hipGetLastError();
   }
-  if (cur != 0) return hipErrorInvalidValue;   // the plan puts the final order in buffer 0
+  RadixSort s{};
+  s.passes = b.tile_passes;
+  int shift = 0;
+  for (int pass = 0; pass < s.passes; ++pass) {
+    const int left = s.passes - pass;
+    s.bits[pass] = (bits - shift + left - 1) / left;
+    s.shift[pass] = shift;
+    shift += s.bits[pass];
+  }
+  s.keys = k.key[X];
+  s.vals = reinterpret_cast<const uint32_t*>(k.pv[X]);   // the first pass pairs each splat index with its slot
+  for (int e = 0; e < 2; ++e) { s.key_buf[e] = k.key[X ^ 1 ^ e]; s.pair_buf[e] = k.pv[X ^ 1 ^ e]; }
+  s.count_dev = &w.cells[3];
+  s.sub = radix_sub(b.key_capacity);
+  s.nblocks = radix_blocks(b.key_capacity, s.sub);
+  s.table = k.table;
+  s.totals = k.totals;
+  s.kept = &w.cells[2];
+  hipError_t e = launch_radix_sort(s, stream);
+  if (e != hipSuccess) return e;
   const uint64_t rblocks = (b.key_capacity + 1023) / 1024;
   hipLaunchKernelGGL(tile_ranges_kernel, dim3((unsigned)rblocks), dim3(256), 0, stream, dbatch,
-                     b.kw.key[0], w.cells, b.total_tiles);
+                     k.key[0], w.cells, b.total_tiles);
   return hipGetLastError();
 }
 

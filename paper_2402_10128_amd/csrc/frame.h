@@ -14,7 +14,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Depth-first binning buffers of a batch of `items` splats (SortWs).
 struct SortPlan {
   size_t off_key = 0, off_cand = 0, off_dk0 = 0, off_dv0 = 0, off_dk1 = 0, off_dv1 = 0, off_table = 0,
-         off_totals = 0, off_chunks = 0, off_cells = 0, bytes = 0;
+         off_totals = 0, off_weights = 0, off_chunks = 0, off_cells = 0, bytes = 0;
 };
 
 inline SortPlan plan_sort(int64_t items) {
@@ -27,8 +27,9 @@ inline SortPlan plan_sort(int64_t items) {
   p.off_dv0 = o;    o += align256(n * 8);
   p.off_dk1 = o;    o += align256(n * 4);
   p.off_dv1 = o;    o += align256(n * 8);
-  p.off_table = o;  o += align256((size_t)256 * radix_blocks((uint64_t)n, kRadixItemsDepth) * 4);
+  p.off_table = o;  o += align256((size_t)256 * radix_blocks((uint64_t)n) * 4);
   p.off_totals = o; o += 1024;
+  p.off_weights = o; o += align256((size_t)radix_blocks((uint64_t)n) * 8);
   p.off_chunks = o; o += align256(((n + 255) / 256 + 1) * 4);
   p.off_cells = o;  o += 256;
   p.bytes = o;
@@ -46,6 +47,7 @@ inline SortWs attach_sort_ws(const SortPlan& p, void* base) {
   w.dv[1] = reinterpret_cast<uint2*>(b + p.off_dv1);
   w.table = reinterpret_cast<uint32_t*>(b + p.off_table);
   w.totals = reinterpret_cast<uint32_t*>(b + p.off_totals);
+  w.weights = reinterpret_cast<unsigned long long*>(b + p.off_weights);
   w.chunk_off = reinterpret_cast<uint32_t*>(b + p.off_chunks);
   w.cells = reinterpret_cast<uint32_t*>(b + p.off_cells);
   w.depth_final = 1;   // four passes: 0 -> 1 -> 0 -> 1 from the item keys (set again by launch_depth_sort)
@@ -126,8 +128,8 @@ inline int tile_passes(int64_t total_tiles) {
 // run the backward pass, one 48-byte row per slot for the backward's per-(tile, splat) sums with a bit per
 // slot marking the written rows, and the checkpoints of the cut walks.
 struct KeyPlan {
-  size_t off_pv0 = 0, off_key0 = 0, off_pv1 = 0, off_key1 = 0, off_table = 0, off_totals = 0, off_rows = 0,
-         off_bits = 0, off_ckpt = 0, bytes = 0;
+  size_t off_pv0 = 0, off_key0 = 0, off_pv1 = 0, off_key1 = 0, off_table = 0, off_totals = 0, off_plan = 0,
+         off_rows = 0, off_bits = 0, off_ckpt = 0, bytes = 0;
 };
 
 inline KeyPlan plan_keys(uint64_t slots, bool backward_rows) {
@@ -138,8 +140,9 @@ inline KeyPlan plan_keys(uint64_t slots, bool backward_rows) {
   p.off_key0 = o;   o += align256(k * 4);
   p.off_pv1 = o;    o += align256(k * 8);
   p.off_key1 = o;   o += align256(k * 4);
-  p.off_table = o;  o += align256((size_t)256 * radix_blocks(slots, kRadixItemsPair) * 4);
+  p.off_table = o;  o += align256((size_t)256 * radix_blocks(slots) * 4);
   p.off_totals = o; o += 1024;
+  p.off_plan = o;   o += 256;
   if (backward_rows) {
     p.off_rows = o; o += align256(k * kRowFloats * 4);
     p.off_bits = o; o += align256((k + 31) / 32 * 4);
@@ -158,6 +161,7 @@ inline KeyWs attach_key_ws(const KeyPlan& p, void* base) {
   w.key[1] = reinterpret_cast<uint32_t*>(b + p.off_key1);
   w.table = reinterpret_cast<uint32_t*>(b + p.off_table);
   w.totals = reinterpret_cast<uint32_t*>(b + p.off_totals);
+  w.plan = reinterpret_cast<uint32_t*>(b + p.off_plan);
   return w;
 }
 

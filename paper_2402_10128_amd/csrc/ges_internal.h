@@ -20,8 +20,9 @@ constexpr int kRecWords = 16;            // 64-byte per-splat record
 constexpr int kGradStride = GES_GRAD2D_STRIDE;   // doubles per splat in the 2-D gradient accumulator
 constexpr int kMaxViews = 64;
 constexpr int kRadixThreads = 256;       // radix passes: blocks of 256 threads ...
-constexpr int kRadixItemsDepth = 8;      // ... holding 8 items each (the depth sort of the splats) ...
-constexpr int kRadixItemsPair = 8;       // ... or 8 (the pair sort: its 12-byte items need twice the LDS)
+constexpr int kRadixItems = 8;           // ... holding 8 items each
+constexpr int kRadixMaxPasses = 4;
+constexpr uint32_t kRadixSmall = 8192;   // sorts of up to this many items are one block's work in LDS
 constexpr uint32_t kNoKey = 0xffffffffu; // radix key of an item that a filtering pass drops
 constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 1e-4f;
@@ -92,6 +93,21 @@ struct ViewDesc {
   const float* dL_drgb;          // [h*w*3] (backward only)
 };
 
+// A word of host memory that a kernel posts a count to (saturating at 2^32 - 1) under a token, so that the host
+// has it while the stream goes on.
+__device__ __forceinline__ void post_count(unsigned long long* mail, uint32_t token, unsigned long long count) {
+  const unsigned long long v = ((unsigned long long)token << 32) | (count > 0xffffffffull ? 0xffffffffull : count);
+  __hip_atomic_store(mail, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+struct CountMail {
+  unsigned long long* slot = nullptr;   // NULL: none free; the count is read from the device instead
+  uint32_t token = 0;
+};
+CountMail mail_take();
+void mail_give(const CountMail& m);
+// waits for the count; `counter` is the device word that holds it too
+hipError_t mail_wait(const CountMail& m, const uint32_t* counter, hipStream_t stream, uint32_t* count);
+
 // Depth-first binning of a batch.  Items are the splats of every view, view after view (item j of view v
 // is splat j - item_prefix[v]).  The preprocess writes each item's depth key and candidate-tile count;
 // the listed items are sorted by depth (stable: equal depths keep index order), their candidate tiles are
@@ -104,6 +120,7 @@ struct SortWs {
   uint2* dv[2];                  // [items] depth-sort values (candidate count, item index), ping-pong
   uint32_t* table;               // [16][items_blocks][16] per-block digit counts of a pass, then their prefix
   uint32_t* totals;              // [256] per-digit totals of a pass
+  unsigned long long* weights;   // [items_blocks] candidate slots of each block's items
   uint32_t* chunk_off;           // [items / 256 + 1] candidate slots before each 256-item chunk of the depth order
   uint32_t* cells;               // [0] listed items, [1] candidate slots (saturating), [2] keys, [3] spare
   int depth_final;               // dv[depth_final] holds the depth order after the last pass
@@ -115,8 +132,9 @@ struct KeyWs {
   uint2* pv[2];                  // (splat index, slot) values of the tile passes; the duplication writes the
                                  // splat indices as u32 into the first half of pv[dup_buffer]
   uint32_t* key[2];
-  uint32_t* table;               // [16][key_blocks][16]
+  uint32_t* table;               // [16][key_blocks][16]; after the sort, the tiles of the cut walks
   uint32_t* totals;              // [256]
+  uint32_t* plan;                // [16] work items of the backward raster
 };
 constexpr int kRowFloats = 12;   // floats per backward row (10 used; 48 bytes keep rows 16-byte aligned)
 
@@ -135,6 +153,7 @@ struct Batch {
   uint32_t* sorted_tiles;        // [key capacity] batch tile per sorted pair (kw.key[0])
   int dup_buffer;                // buffer the duplication writes (so that the last tile pass ends in 0)
   uint64_t key_capacity;
+  CountMail mail;                // where the batch's slot count is posted (slot NULL: nowhere)
   int32_t shared_scene;          // every view renders the same splats (the views of a training step): the
                                  // preprocess backward sums the views' gradients per splat, in view order
 };
@@ -196,42 +215,59 @@ hipError_t launch_tile_sort(const DeviceBatch* dbatch, const Batch& b, hipStream
 // marked in bits), its rows added in slot order (binary64); splats without a row are left alone
 hipError_t launch_row_reduce(const DeviceBatch* dbatch, const Batch& b, const float* rows, const uint32_t* bits,
                              uint64_t nslots, hipStream_t stream);
-// one stable LSD radix pass over (u32 key, u32 value) items with 8-bit digits (radix.hip)
-struct RadixPass {
-  int32_t items;                 // per thread: kRadixItemsDepth (pair == 0) or kRadixItemsPair (pair == 1)
-  int32_t bits;                  // digit width (1..8)
-  int32_t pair;                  // values are (u32, slot) pairs: read from pvals_in, or made from vals_in and
-                                 // the item index; written to pvals_out
-  const uint32_t* keys_in;
-  const uint32_t* vals_in;       // NULL: an item's value is its index
-  const uint2* pvals_in;
-  uint32_t* keys_out;
-  uint32_t* vals_out;
-  uint2* pvals_out;
+// A stable LSD radix sort of (u32 key, (u32, u32)) items by digits of up to 8 bits (radix.hip); an item's value
+// is (vals[i], i), items whose key is kNoKey are dropped.  Pass k writes buffer k & 1.
+struct RadixSort {
+  int32_t passes;
+  int32_t bits[kRadixMaxPasses], shift[kRadixMaxPasses];   // digit k = (key >> shift) & ((1 << bits) - 1)
+  const uint32_t* keys;
+  const uint32_t* vals;
+  uint32_t* key_buf[2];          // buffer 1 may hold keys and vals
+  uint2* pair_buf[2];
   const uint32_t* count_dev;     // number of items (device), or NULL: count_host
   uint32_t count_host;
-  int32_t sub;                   // tiles of 256 x items items per block
-  uint32_t nblocks;              // table width: blocks of sub x 256 x items items covering the largest count
-  int32_t shift;                 // digit = (key >> shift) & ((1 << bits) - 1)
-  int32_t filter;                // drop items whose key is kNoKey; the kept count goes to count_out
+  int32_t sub;                   // tiles of kRadixThreads x kRadixItems items per block
+  uint32_t nblocks;              // blocks covering the largest count
   uint32_t* table;               // [16][nblocks][16] (digit group, block, digit in the group)
   uint32_t* totals;              // [256]
-  uint32_t* count_out;
+  uint32_t* kept;                // receives the number of items kept
+  const uint32_t* weights;       // NULL, or [items], 0 for a dropped one: their sum is posted to mail
+  unsigned long long* weight_sums;   // [nblocks]
+  unsigned long long* mail;
+  uint32_t token;
 };
-hipError_t launch_radix_pass(const RadixPass& p, hipStream_t stream);
-// Tiles of kRadixThreads x items items that one radix block takes in turn: 1 up to 8,192 tiles (enough
+struct RadixPass {
+  int32_t bits, shift, filter, sub;
+  uint32_t nblocks;
+  const uint32_t* keys_in;
+  const uint32_t* vals_in;       // first pass
+  const uint2* pvals_in;         // later passes
+  uint32_t* keys_out;
+  uint2* pvals_out;
+  const uint32_t* count_dev;
+  uint32_t count_host;
+  uint32_t* table;
+  uint32_t* totals;
+  uint32_t* count_out;
+  const uint32_t* weights;
+  unsigned long long* weight_sums;
+  unsigned long long* mail;
+  uint32_t token;
+};
+hipError_t launch_radix_sort(const RadixSort& s, hipStream_t stream);
+// Tiles of kRadixThreads x kRadixItems items that one radix block takes in turn: 1 up to 8,192 tiles (enough
 // blocks to fill the device), then up to 8 (fewer, longer blocks: a shorter digit table).
-inline int radix_sub(uint64_t n, int items) {
-  const uint64_t tiles = (n + (uint64_t)kRadixThreads * items - 1) / ((uint64_t)kRadixThreads * items);
+inline int radix_sub(uint64_t n) {
+  const uint64_t tiles = (n + (uint64_t)kRadixThreads * kRadixItems - 1) / ((uint64_t)kRadixThreads * kRadixItems);
   return (int)std::min<uint64_t>(8, std::max<uint64_t>(1, tiles / 8192));
 }
-inline uint32_t radix_blocks(uint64_t n, int items, int sub = 1) {
-  const uint64_t span = (uint64_t)kRadixThreads * items * sub;
+inline uint32_t radix_blocks(uint64_t n, int sub = 1) {
+  const uint64_t span = (uint64_t)kRadixThreads * kRadixItems * sub;
   return (uint32_t)((n + span - 1) / span);
 }
 hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // clears the row marks and, for frames whose walks are cut, lists the backward raster's work items (in
-// b.kw.pv[1]) and cut tiles (b.kw.table), with the plan in b.kw.totals; the raster then takes them
+// b.kw.pv[1]) and cut tiles (b.kw.table), with the plan in b.kw.plan; the raster then takes them
 hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
                                    hipStream_t stream);
 hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);

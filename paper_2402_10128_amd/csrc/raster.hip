@@ -409,7 +409,7 @@ __device__ __forceinline__ float row_scatter8(float a0, float a1, float a2, floa
 
 constexpr int kFlush = 32;   // splats whose row partials are parked in LDS before one flush of rows
 
-// Words of the backward's plan (b.kw.totals): where each XCD's work items start, the number of tiles whose walk
+// Words of the backward's plan (b.kw.plan): where each XCD's work items start, the number of tiles whose walk
 // is cut, and the list positions per segment.
 enum : int { P_STARTS = 0, P_CUT = 9, P_SEG = 10 };
 
@@ -954,7 +954,7 @@ hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, ui
                                    hipStream_t stream) {
   const size_t clear = std::min<size_t>(1024, (nwords + 4095) / 4096);
   hipLaunchKernelGGL(backward_prepare_kernel, dim3((unsigned)(1 + clear)), dim3(1024), 0, stream, dbatch,
-                     cut_walks(b) ? b.kw.pv[1] : nullptr, b.kw.table, b.kw.totals, bits, nwords);
+                     cut_walks(b) ? b.kw.pv[1] : nullptr, b.kw.table, b.kw.plan, bits, nwords);
   return hipGetLastError();
 }
 
@@ -993,16 +993,16 @@ hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hip
   if (most > 0) {
     const dim3 grid((unsigned)std::min<int64_t>(b.total_tiles, most));
     hipLaunchKernelGGL((phi ? raster_recover_kernel<GES_FALLOFF_PHI> : raster_recover_kernel<GES_FALLOFF_GEF>), grid,
-                       dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs, b.kw.table, b.kw.totals);
+                       dim3(64 * kFwdWaves), 0, stream, dbatch, b.sorted_pairs, b.kw.table, b.kw.plan);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   // a block per item, whichever XCD it belongs to, up to a few rounds of the device (the item counts are known
   // there only): blocks past the items leave at once, items past the blocks are taken in turn
-  const int64_t blocks = std::min<int64_t>(8 * (b.total_tiles + most), 16384);
+  const int64_t blocks = std::min<int64_t>(8 * (b.total_tiles + most), 8192);
   hipLaunchKernelGGL((phi ? raster_backward_kernel<GES_FALLOFF_PHI, true> : raster_backward_kernel<GES_FALLOFF_GEF, true>),
                      dim3((unsigned)blocks), dim3(64), 0, stream, dbatch, b.sorted_pairs, b.total_tiles, b.kw.pv[1],
-                     b.kw.totals);
+                     b.kw.plan);
   return hipGetLastError();
 }
 
