@@ -197,7 +197,6 @@ ges::Batch views_batch(const ges_splats* s, const ges_raster_params* p, const ge
   b.keys_total = &b.sw.cells[1];
   b.tile_passes = ges::tile_passes(b.total_tiles);
   b.dup_buffer = b.tile_passes & 1;
-  b.shared_scene = 1;
   return b;
 }
 
@@ -350,7 +349,7 @@ ges_status render_backward(const ges_splats* splats, const ges_camera* cams, int
                                                 slots, stream);
                 }), "row_reduce");
   GES_CHECK_HIP(timed(GES_STAGE_PREPROCESS_BACKWARD, stream,
-                      [&] { return ges::launch_preprocess_backward(db, b, grads, stream, adam, fused); }),
+                      [&] { return ges::launch_preprocess_backward(db, b, splats->sh_degree, grads, stream, adam, fused); }),
                 "preprocess_backward");
   return GES_OK;
 }
@@ -555,15 +554,12 @@ ges_status ges_render_backward_views_adam(const ges_splats* splats, const ges_ca
   ges::AdamSplats a;
   const ges_status st = adam_args(splats, &cams[0], opt, a);
   if (st != GES_OK) return st;
-  if (num_views > 1) {   // the earlier views' sum goes through `grads`, which the last view's update reads
+  if (num_views > 1) {   // the views' sum is what the update takes; `grads` receives it
     for (int k = 0; k < ges::kNumPar; ++k)
       if (opt->grads_in[k]) return fail(GES_ERR_INVALID_ARGUMENT, "grads_in must be NULL with more than one view");
     if (!grads || !grads->means || !grads->log_scales || !grads->quats || !grads->opacity_logits || !grads->sh ||
         !grads->beta)
       return fail(GES_ERR_INVALID_ARGUMENT, "every grads buffer is needed with more than one view");
-    const float* g[ges::kNumPar] = {grads->means, grads->log_scales, grads->quats, grads->opacity_logits, grads->sh,
-                                    grads->beta};
-    for (int k = 0; k < ges::kNumPar; ++k) a.gin[k] = g[k];
   }
   return render_backward(splats, cams, num_views, params, splat_ws, key_ws, pixel_ws, dL_drgb, grads, &a, true,
                          stream);

@@ -59,7 +59,7 @@ struct FramePlan {
   int64_t tiles = 0;
   // splat workspace; the binning buffers of the frame's own batch come last (a server gives a batch of
   // views one such region and its views only the part before it)
-  size_t off_db = 0, off_hdr = 0, off_rec = 0, off_grad = 0, off_vis = 0, off_slotoff = 0, off_ranges = 0,
+  size_t off_db = 0, off_hdr = 0, off_rec = 0, off_grad = 0, off_chain = 0, off_vis = 0, off_slotoff = 0, off_ranges = 0,
          off_tstats = 0, off_twork = 0, off_tckpt = 0, off_gorder = 0, off_sort = 0;
   size_t view_bytes = 0, splat_bytes = 0;
   // pixel workspace
@@ -76,6 +76,7 @@ inline FramePlan plan_frame(int64_t n, int w, int h) {
   p.off_hdr = o;     o += 256;
   p.off_rec = o;     o += align256((size_t)n * kRecWords * 4);
   p.off_grad = o;    o += align256((size_t)n * kGradStride * 8);
+  p.off_chain = o;   o += align256((size_t)n * 12 * 4);
   p.off_vis = o;     o += align256((size_t)n * 4);
   p.off_slotoff = o; o += align256((size_t)n * 4);
   p.off_ranges = o;  o += align256((size_t)p.tiles * 8);
@@ -248,6 +249,7 @@ inline void attach_splat_ws(ViewDesc& V, const FramePlan& fp, void* splat_ws) {
   char* b = reinterpret_cast<char*>(splat_ws);
   V.rec = reinterpret_cast<float4*>(b + fp.off_rec);
   V.grad2d = reinterpret_cast<double*>(b + fp.off_grad);
+  V.chain = reinterpret_cast<float*>(b + fp.off_chain);
   V.vis = reinterpret_cast<uint32_t*>(b + fp.off_vis);
   V.slot_off = reinterpret_cast<uint32_t*>(b + fp.off_slotoff);
   V.ranges = reinterpret_cast<uint2*>(b + fp.off_ranges);

@@ -78,6 +78,7 @@ struct ViewDesc {
   uint32_t* tile_work;           // [tiles] list position + 1 of the tile's last composited splat (forward pass)
   uint32_t* group_order;         // [ceil(tiles / 8)] tile groups, heaviest backward walk first
   double* grad2d;                // [n][kGradStride] binary64 2-D gradients (stored with keep_grad2d only)
+  float* chain;                  // [n][12] chained gradients of the splats with rows (backward)
   uint32_t* slot_off;            // [n] first candidate slot of a listed splat (the duplication writes it)
   const uint2* sorted_pairs;     // [keys] (splat index, slot) per sorted pair (backward)
   float* grad_rows;              // [slots][kRowFloats] per-(tile, splat) sums of the backward, at the pair's slot
@@ -154,8 +155,6 @@ struct Batch {
   int dup_buffer;                // buffer the duplication writes (so that the last tile pass ends in 0)
   uint64_t key_capacity;
   CountMail mail;                // where the batch's slot count is posted (slot NULL: nowhere)
-  int32_t shared_scene;          // every view renders the same splats (the views of a training step): the
-                                 // preprocess backward sums the views' gradients per splat, in view order
 };
 
 // Device view table and per-batch constants, copied to the device by the host before launches.
@@ -273,8 +272,9 @@ hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, ui
 hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // args (may be NULL): the fused update's arguments when `fused`; otherwise only accumulate and the
 // densification statistic are read
-hipError_t launch_preprocess_backward(const DeviceBatch* dbatch, const Batch& b, const ges_splat_grads* grads,
-                                      hipStream_t stream, const AdamSplats* args = nullptr, bool fused = false);
+hipError_t launch_preprocess_backward(const DeviceBatch* dbatch, const Batch& b, int sh_degree,
+                                      const ges_splat_grads* grads, hipStream_t stream,
+                                      const AdamSplats* args = nullptr, bool fused = false);
 
 hipError_t launch_freq_mask(const float* target, int w, int h, float omega, void* scratch, uint8_t* mask,
                             hipStream_t stream);

@@ -1,4 +1,4 @@
-// preprocess_bwd.hip -- chain rule of the per-splat preprocess (GES Sec. 4.1-4.2), one thread per splat.
+// preprocess_bwd.hip -- chain rule of the per-splat preprocess (GES Sec. 4.1-4.2).
 //
 // From the accumulated gradients of a splat's 2-D quantities (mean2D, conic a/b/c, opacity, colour and,
 // with the GEF falloff, beta) to its mean, log-scale, quaternion, opacity logit, SH coefficients and
@@ -7,11 +7,20 @@
 // (visibility, guard clamp of the Jacobian, colour clamp) come from the forward pass, through a 4-byte
 // visibility word per splat.  Several of the sums cancel (e.g. the scale gradient of an axis along the
 // view ray), and binary32 there leaves an error proportional to the splat's whole gradient; the FP64
-// vector rate of gfx950 equals its non-packed FP32 rate and the kernel is memory-bound, so binary64
-// costs little.  Nothing here feeds a decision, so this file is built with contraction allowed.
-// Memory: per visible splat the 2-D gradient row, the parameters (240 B at SH degree 3) and the
-// parameter gradients (240 B); per culled splat the visibility word and zero gradients.  The SH rows
-// (192 B at degree 3) of a wave's 64 splats are staged in LDS and written as one contiguous block.
+// vector rate of gfx950 equals its non-packed FP32 rate.  Nothing here feeds a decision, so this file is built
+// with contraction allowed.
+// Two launches:
+//   chain:  the splats with a 2-D gradient (about a tenth: the backward raster composited them somewhere) are
+//           gathered from the visibility words and chained one per lane, 48 bytes of gradients each;
+//   emit:   every splat's gradients are written, or applied at once as an Adam update, as one stream over the
+//           parameter arrays; the SH gradients are the product of the basis of the view direction and the colour
+//           gradient, formed there.  The views of one scene are added up in registers and LDS.
+// In one launch the chain's registers (203, and 430 with spills for several views) left two waves per SIMD for what
+// is a stream over memory, and a tenth of its lanes working.  Measured, one launch -> chain and emit: Adam fused, 3M
+// splats 1,061 -> 60 + 800 us, four views of 200k 315 -> 65 + 92; gradients stored, 1M 105 -> 45 + 50, 5M 456 -> 362 in
+// all; 1k 8 -> 11 (the second launch).
+// Memory: the stream reads 4 bytes per splat and view and writes the gradients (240 B at SH degree 3), or reads and
+// writes the parameters and both moments (1,440 B); the chain reads about 430 B per splat it takes.
 #include "ges_internal.h"
 
 namespace ges {
@@ -55,19 +64,32 @@ __device__ __forceinline__ void nt_store4(float4* d, float4 v) {
   __builtin_nontemporal_store(x, reinterpret_cast<NtF4*>(d));
 }
 
-// Output of one parameter gradient: stored when the caller asked for gradients, and with kAdam also
-// applied at once as an Adam update of the parameter (the gradient never goes through memory).
-template <bool kAdam, int P>
+// How the stream takes the gradients: stored; applied as an Adam update; or applied with the parameters and moments
+// loaded past the caches too.  That pays once they exceed the last-level cache (256 MB): at 3M splats, 2.2 GB, the
+// stream takes 800 us against 946, and the next frame's preprocess 174 against 207; at 200k, 144 MB, they are
+// still there from one step to the next, and it takes 99 against 92.
+enum EmitMode : int { kStore, kUpdate, kUpdateStream };
+constexpr int64_t kStreamBytes = 256 << 20;
+
+template <EmitMode M, class T>
+__device__ __forceinline__ T emit_load(const T* p) {
+  if constexpr (M == kUpdateStream) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+// Output of one parameter gradient: stored when the caller asked for gradients, and with an update also
+// applied at once to the parameter (the gradient never goes through memory).
+template <EmitMode M, int P>
 __device__ __forceinline__ void emit(float* g, const AdamSplats& A, int64_t idx, float val) {
-  if constexpr (kAdam) {
+  if constexpr (M != kStore) {
     if (A.gin[P]) val = A.gin[P][idx] + val;      // the other views' gradients, then this view's
   }
   if (g) {
     if (A.accumulate) g[idx] = g[idx] + val;
     else __builtin_nontemporal_store(val, g + idx);
   }
-  if constexpr (kAdam) {
-    float p = A.p[P][idx], m = A.m[P][idx], v = A.v[P][idx];
+  if constexpr (M != kStore) {
+    float p = emit_load<M>(A.p[P] + idx), m = emit_load<M>(A.m[P] + idx), v = emit_load<M>(A.v[P] + idx);
     adam_update(p, val, m, v, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
     __builtin_nontemporal_store(p, A.p[P] + idx);
     __builtin_nontemporal_store(m, A.m[P] + idx);
@@ -75,9 +97,9 @@ __device__ __forceinline__ void emit(float* g, const AdamSplats& A, int64_t idx,
   }
 }
 
-template <bool kAdam, int P>
+template <EmitMode M, int P>
 __device__ __forceinline__ void emit4(float* g, const AdamSplats& A, int64_t idx4, float4 val) {
-  if constexpr (kAdam) {
+  if constexpr (M != kStore) {
     if (A.gin[P]) {
       const float4 o = reinterpret_cast<const float4*>(A.gin[P])[idx4];
       val = make_float4(o.x + val.x, o.y + val.y, o.z + val.z, o.w + val.w);
@@ -92,17 +114,22 @@ __device__ __forceinline__ void emit4(float* g, const AdamSplats& A, int64_t idx
       nt_store4(d, val);
     }
   }
-  if constexpr (kAdam) {
-    float4 p = reinterpret_cast<const float4*>(A.p[P])[idx4];
-    float4 m = reinterpret_cast<const float4*>(A.m[P])[idx4];
-    float4 v = reinterpret_cast<const float4*>(A.v[P])[idx4];
-    adam_update(p.x, val.x, m.x, v.x, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
-    adam_update(p.y, val.y, m.y, v.y, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
-    adam_update(p.z, val.z, m.z, v.z, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
-    adam_update(p.w, val.w, m.w, v.w, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
-    nt_store4(reinterpret_cast<float4*>(A.p[P]) + idx4, p);
-    nt_store4(reinterpret_cast<float4*>(A.m[P]) + idx4, m);
-    nt_store4(reinterpret_cast<float4*>(A.v[P]) + idx4, v);
+  if constexpr (M != kStore) {
+    NtF4 p = emit_load<M>(reinterpret_cast<const NtF4*>(A.p[P]) + idx4);
+    NtF4 m = emit_load<M>(reinterpret_cast<const NtF4*>(A.m[P]) + idx4);
+    NtF4 v = emit_load<M>(reinterpret_cast<const NtF4*>(A.v[P]) + idx4);
+    const float gr[4] = {val.x, val.y, val.z, val.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float pc = p[c], mc = m[c], vc = v[c];
+      adam_update(pc, gr[c], mc, vc, A.b1, A.b2, A.eps, A.step_size[P], A.inv_sqrt_bc2);
+      p[c] = pc;
+      m[c] = mc;
+      v[c] = vc;
+    }
+    __builtin_nontemporal_store(p, reinterpret_cast<NtF4*>(A.p[P]) + idx4);
+    __builtin_nontemporal_store(m, reinterpret_cast<NtF4*>(A.m[P]) + idx4);
+    __builtin_nontemporal_store(v, reinterpret_cast<NtF4*>(A.v[P]) + idx4);
   }
 }
 
@@ -119,56 +146,30 @@ __device__ __forceinline__ double digamma(double x) {
   return acc + log(x) - 0.5 * i - series;
 }
 
-constexpr int kRowPad = 13;   // float4 slots per staged SH-gradient row (12 used at degree 3; 13 spreads LDS banks)
+// View direction of a splat in binary64, and its length.
+__device__ __forceinline__ void view_dir(const ViewDesc& V, double mx, double my, double mz, double& x, double& y,
+                                         double& z, double& len) {
+  double cpos[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    cpos[j] = -((double)V.R[j] * (double)V.t[0] + (double)V.R[3 + j] * (double)V.t[1] + (double)V.R[6 + j] * (double)V.t[2]);
+  const double e0 = mx - cpos[0], e1 = my - cpos[1], e2 = mz - cpos[2];
+  len = sqrt(e0 * e0 + e1 * e1 + e2 * e2);
+  x = e0 / len;
+  y = e1 / len;
+  z = e2 / len;
+}
 
-
-
-// Chain rule of splat i.  SH-gradient rows of degrees 1 and 3 (whole float4s) go to `row` in LDS; other
-// degrees are written straight to memory.
-template <int D, bool kAdam>
-__device__ __forceinline__ void backward_splat(const ViewDesc& V, const ges_splat_grads& G, const AdamSplats& A,
-                                               int64_t i, float4* row) {
+// Chain rule of splat i, whose 2-D gradient the row reduction left in grad2d: everything but the SH gradients, as
+// (mean, log-scale, opacity, beta, quaternion) in V.chain.  EXACT: the exact shape modification (its ln Gamma takes
+// many registers).
+template <int D, bool EXACT>
+__device__ __forceinline__ void chain_splat(const ViewDesc& V, int64_t i) {
   constexpr int K = (D + 1) * (D + 1);
-  const uint32_t vis = V.vis[i];
-  const int64_t sh0 = (int64_t)3 * K * i;
-  if (!(vis & kVisBit)) {
-    if (V.keep_grad2d) {   // inspection: the rows of unlisted splats read as zero
-      double2* gz = reinterpret_cast<double2*>(V.grad2d + (int64_t)kGradStride * i);
-#pragma unroll
-      for (int k = 0; k < kGradStride / 2; ++k) gz[k] = make_double2(0.0, 0.0);
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      emit<kAdam, kParMeans>(G.means, A, 3 * i + c, 0.f);
-      emit<kAdam, kParScales>(G.log_scales, A, 3 * i + c, 0.f);
-    }
-    emit4<kAdam, kParQuats>(G.quats, A, i, make_float4(0.f, 0.f, 0.f, 0.f));
-    emit<kAdam, kParOpacity>(G.opacity_logits, A, i, 0.f);
-    emit<kAdam, kParBeta>(G.beta, A, i, 0.f);
-    if constexpr ((3 * K) % 4 == 0) {
-#pragma unroll
-      for (int m = 0; m < 3 * K / 4; ++m) row[m] = make_float4(0.f, 0.f, 0.f, 0.f);
-    } else {
-      for (int k = 0; k < 3 * K; ++k) emit<kAdam, kParSh>(G.sh, A, sh0 + k, 0.f);
-    }
-    return;
-  }
-  const uint32_t flags = vis & 0xffu;
-  // the splat's 2-D gradient, summed from its rows by the reduction that follows the backward raster (zero
-  // when no pixel composited it)
-  double2 g01 = make_double2(0.0, 0.0), g23 = g01, g45 = g01, g67 = g01, g89 = g01;
-  double2* gp = reinterpret_cast<double2*>(V.grad2d + (int64_t)kGradStride * i);
-  if (vis & kRowBit) {
-    g01 = gp[0]; g23 = gp[1]; g45 = gp[2]; g67 = gp[3]; g89 = gp[4];
-  } else if (V.keep_grad2d) {
-#pragma unroll
-    for (int k = 0; k < 5; ++k) gp[k] = make_double2(0.0, 0.0);
-  }
-  if (A.stat_accum) {   // densification statistic: the mean-2D gradient in NDC units
-    const double su = g01.x * A.half_w, sv = g01.y * A.half_h;
-    A.stat_accum[i] += (float)sqrt(su * su + sv * sv);
-    A.stat_count[i] += 1.f;
-  }
+  const uint32_t flags = V.vis[i] & 0xffu;
+  const double2* gp = reinterpret_cast<const double2*>(V.grad2d + (int64_t)kGradStride * i);
+  const double2 g01 = gp[0], g23 = gp[1], g45 = gp[2], g67 = gp[3], g89 = gp[4];
+  float out[12];
   const double grgb[3] = {g67.x, g67.y, g89.x};
   const double gu = g01.x, gv = g01.y, ga = g23.x, gb = g23.y, gc = g45.x, gop = g45.y;
   const double gbeta2 = g89.y;
@@ -197,7 +198,7 @@ __device__ __forceinline__ void backward_splat(const ViewDesc& V, const ges_spla
   double phi = 1.0;
   const double rho = V.rho;
   if (V.falloff == GES_FALLOFF_PHI) phi = 2.0 / (1.0 + exp(-(rho * beta - 2.0 * rho)));
-  else if (V.falloff == GES_FALLOFF_PHI_EXACT) phi = 2.0 * exp(lgamma(3.0 / beta) - lgamma(1.0 / beta));
+  else if (EXACT) phi = 2.0 * exp(lgamma(3.0 / beta) - lgamma(1.0 / beta));
   const double S[3] = {phi * s[0], phi * s[1], phi * s[2]};
   double Mm[9];
   for (int r = 0; r < 3; ++r)
@@ -275,14 +276,14 @@ __device__ __forceinline__ void backward_splat(const ViewDesc& V, const ges_spla
       gQ[3 * r + c] = gM * S[c];
     }
   const double gphi = gS[0] * s[0] + gS[1] * s[1] + gS[2] * s[2];
-  for (int c = 0; c < 3; ++c) emit<kAdam, kParScales>(G.log_scales, A, 3 * i + c, (float)(gS[c] * phi * s[c]));
+  for (int c = 0; c < 3; ++c) out[3 + c] = (float)(gS[c] * phi * s[c]);
   {
     double gb_ = 0.0;
     if (V.falloff == GES_FALLOFF_PHI) gb_ = gphi * rho * phi * (1.0 - 0.5 * phi);
-    else if (V.falloff == GES_FALLOFF_PHI_EXACT)   // d phi / d beta = phi (psi(1/b) - 3 psi(3/b)) / b^2
+    else if (EXACT)   // d phi / d beta = phi (psi(1/b) - 3 psi(3/b)) / b^2
       gb_ = gphi * phi * (digamma(1.0 / beta) - 3.0 * digamma(3.0 / beta)) / (beta * beta);
     else gb_ = gbeta2;
-    emit<kAdam, kParBeta>(G.beta, A, i, (float)gb_);
+    out[7] = (float)gb_;
   }
   // rotation -> unit quaternion -> quaternion
   {
@@ -292,59 +293,45 @@ __device__ __forceinline__ void backward_splat(const ViewDesc& V, const ges_spla
     const double gyq = 2.0 * (-2.0 * y * gQ[0] + x * gQ[1] + w * gQ[2] + x * gQ[3] + zq * gQ[5] - w * gQ[6] + zq * gQ[7] - 2.0 * y * gQ[8]);
     const double gzq = 2.0 * (-2.0 * zq * gQ[0] - w * gQ[1] + x * gQ[2] + w * gQ[3] - 2.0 * zq * gQ[4] + y * gQ[5] + x * gQ[6] + y * gQ[7]);
     const double dot = gw * w + gxq * x + gyq * y + gzq * zq;
-    emit4<kAdam, kParQuats>(G.quats, A, i,
-                            make_float4((float)((gw - w * dot) / nr), (float)((gxq - x * dot) / nr),
-                                        (float)((gyq - y * dot) / nr), (float)((gzq - zq * dot) / nr)));
+    out[8] = (float)((gw - w * dot) / nr);
+    out[9] = (float)((gxq - x * dot) / nr);
+    out[10] = (float)((gyq - y * dot) / nr);
+    out[11] = (float)((gzq - zq * dot) / nr);
   }
-  emit<kAdam, kParOpacity>(G.opacity_logits, A, i, (float)(gop * op * (1.0 - op)));
+  out[6] = (float)(gop * op * (1.0 - op));
 
-  // colour: SH coefficients and the view direction
+
+  // colour: the SH coefficients' dependence on the view direction
   double gmu[3] = {0.0, 0.0, 0.0};
-  double gc3[3];
-#pragma unroll
-  for (int ch = 0; ch < 3; ++ch) gc3[ch] = (flags & (1u << ch)) ? 0.0 : grgb[ch];
-  double cpos[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-    cpos[j] = -(R[j] * (double)V.t[0] + R[3 + j] * (double)V.t[1] + R[6 + j] * (double)V.t[2]);
-  const double e0 = mx - cpos[0], e1 = my - cpos[1], e2 = mz - cpos[2];
-  const double len = sqrt(e0 * e0 + e1 * e1 + e2 * e2);
-  const double x = e0 / len, y = e1 / len, zz_ = e2 / len;
-  double Y[16];
-  sh_basis_f64(x, y, zz_, D, Y);
-  const float* shc = V.sh + (int64_t)3 * K * i;
-  // dL/dc_k,ch = Y_k gc3[ch]; dL/dY_k = sum_ch gc3[ch] c_k,ch.  Rows of 3K floats; for degrees 1 and 3
-  // they are 16-byte aligned (checked on the host), so they move as float4.
-  double gY[16];
-#pragma unroll
-  for (int k = 0; k < K; ++k) gY[k] = 0.0;
-  if constexpr ((3 * K) % 4 == 0) {
-    const float4* s4 = reinterpret_cast<const float4*>(shc);
-    float4 xv[3 * K / 4];
-#pragma unroll
-    for (int m = 0; m < 3 * K / 4; ++m) xv[m] = s4[m];
-#pragma unroll
-    for (int m = 0; m < 3 * K / 4; ++m) {
-      const float xs[4] = {xv[m].x, xv[m].y, xv[m].z, xv[m].w};
-      float ys[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = (4 * m + e) / 3, ch = (4 * m + e) % 3;
-        gY[k] += gc3[ch] * (double)xs[e];
-        ys[e] = (float)(Y[k] * gc3[ch]);
-      }
-      row[m] = make_float4(ys[0], ys[1], ys[2], ys[3]);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int ch = 0; ch < 3; ++ch) {
-        gY[k] += gc3[ch] * (double)shc[3 * k + ch];
-        emit<kAdam, kParSh>(G.sh, A, sh0 + 3 * k + ch, (float)(Y[k] * gc3[ch]));
-      }
-  }
   if (D > 0) {
+    double gc3[3];
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) gc3[ch] = (flags & (1u << ch)) ? 0.0 : grgb[ch];
+    double x, y, zz_, len;
+    view_dir(V, mx, my, mz, x, y, zz_, len);
+    // dL/dY_k = sum_ch gc3[ch] c_k,ch.  Rows of 3K floats; for degrees 1 and 3 they are 16-byte aligned (checked on
+    // the host), so they move as float4.
+    const float* shc = V.sh + (int64_t)3 * K * i;
+    double gY[16];
+#pragma unroll
+    for (int k = 0; k < K; ++k) gY[k] = 0.0;
+    if constexpr ((3 * K) % 4 == 0) {
+      const float4* s4 = reinterpret_cast<const float4*>(shc);
+      float4 xv[3 * K / 4];
+#pragma unroll
+      for (int m = 0; m < 3 * K / 4; ++m) xv[m] = s4[m];
+#pragma unroll
+      for (int m = 0; m < 3 * K / 4; ++m) {
+        const float xs[4] = {xv[m].x, xv[m].y, xv[m].z, xv[m].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gY[(4 * m + e) / 3] += gc3[(4 * m + e) % 3] * (double)xs[e];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) gY[k] += gc3[ch] * (double)shc[3 * k + ch];
+    }
     double gdx = 0.0, gdy = 0.0, gdz = 0.0;
     gdy += -kD1 * gY[1]; gdz += kD1 * gY[2]; gdx += -kD1 * gY[3];
     if (D > 1) {
@@ -374,104 +361,210 @@ __device__ __forceinline__ void backward_splat(const ViewDesc& V, const ges_spla
     gmu[2] = (gdz - zz_ * dd) / len;
   }
   // p = W mu + t
-  for (int c = 0; c < 3; ++c)
-    emit<kAdam, kParMeans>(G.means, A, 3 * i + c, (float)(gmu[c] + R[c] * gp0 + R[3 + c] * gp1 + R[6 + c] * gz_));
+  for (int c = 0; c < 3; ++c) out[c] = (float)(gmu[c] + R[c] * gp0 + R[3 + c] * gp1 + R[6 + c] * gz_);
+  float4* o = reinterpret_cast<float4*>(V.chain) + 3 * i;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) o[k] = make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
 }
 
-template <int D, bool kAdam>
-__device__ __forceinline__ void backward_wave(const ViewDesc& V, const ges_splat_grads& G, const AdamSplats& A,
-                                              int64_t w0, float4* rows) {
-  constexpr int K = (D + 1) * (D + 1);
-  constexpr int F4 = 3 * K / 4;   // float4s per SH-gradient row (degrees 1 and 3)
-  const int lane = threadIdx.x & 63;
-  const int64_t i = w0 + lane;
-  if (i < V.n) backward_splat<D, kAdam>(V, G, A, i, rows + lane * kRowPad);
-  if constexpr ((3 * K) % 4 == 0) {
-    if (!kAdam && !G.sh) return;
-    const int cnt = (int)min<int64_t>(64, V.n - w0);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the wave's rows are one contiguous block of float4s starting at splat w0
-    const int64_t base4 = (int64_t)F4 * w0;
-    for (int m = lane; m < cnt * F4; m += 64)
-      emit4<kAdam, kParSh>(G.sh, A, base4 + m, rows[(m / F4) * kRowPad + (m % F4)]);
-  }
-}
+// Splats a chain block gathers from: many, so that the tenth of them it takes fills its lanes; few where the
+// splats would not fill the device otherwise.
+constexpr int kChainSpan = 2048;
+inline int chain_span(int64_t n) { return n >= 262144 ? kChainSpan : 256; }
 
-template <int D, bool kAdam>
-__device__ __forceinline__ void backward_views(const DeviceBatch* db, const ges_splat_grads& G, const AdamSplats& A,
-                                               int64_t w0, float4* rows) {
-  // the views of one scene, in order: every view before the last adds its gradients to the stored ones (the
-  // first overwrites unless the caller accumulates); the last applies the update (kAdam) with the stored
-  // sum as the other views' gradients, or adds its gradients like the others
-  const int nv = db->nviews;
-  for (int v = 0; v < nv; ++v) {
-    AdamSplats a = A;
-    if (v > 0) a.accumulate = 1;
-    if (kAdam && v == nv - 1) {
-      a.accumulate = 0;
-      backward_wave<D, true>(db->views[v], G, a, w0, rows);
-    } else {
-      backward_wave<D, false>(db->views[v], G, a, w0, rows);
-    }
-    // the next view's rows reuse the LDS rows this view's SH stores read
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// One block per 256 splats of a view.  SHARED: the batch's views render the same splats and the grid
-// covers them once; each thread chains its splat through every view (backward_views).
-template <bool kAdam, bool SHARED>
-__global__ void __launch_bounds__(256) preprocess_backward_kernel(const DeviceBatch* __restrict__ db,
-                                                                   ges_splat_grads G, AdamSplats A) {
-  __shared__ float4 sRows[4 * 64 * kRowPad];
-  const int64_t blk = blockIdx.x;
-  const int wave = threadIdx.x >> 6;
-  float4* rows = sRows + wave * 64 * kRowPad;
-  if constexpr (SHARED) {
-    const ViewDesc& V0 = db->views[0];
-    const int64_t w0 = blk * 256 + wave * 64;
-    if (w0 >= V0.n) return;
-    switch (V0.sh_degree) {
-      case 0: backward_views<0, kAdam>(db, G, A, w0, rows); break;
-      case 1: backward_views<1, kAdam>(db, G, A, w0, rows); break;
-      case 2: backward_views<2, kAdam>(db, G, A, w0, rows); break;
-      default: backward_views<3, kAdam>(db, G, A, w0, rows); break;
-    }
-    return;
-  }
-  const int v = view_of_block(db->pre_prefix, db->nviews, blk);
+template <int D, bool EXACT>
+__global__ void __launch_bounds__(256, 2) preprocess_chain_kernel(const DeviceBatch* __restrict__ db, int64_t blocks,
+                                                               int span) {
+  __shared__ uint16_t list[kChainSpan];
+  __shared__ uint32_t count;
+  const int64_t v = blockIdx.x / blocks;
   const ViewDesc& V = db->views[v];
-  const int64_t w0 = (blk - db->pre_prefix[v]) * 256 + wave * 64;
-  if (w0 >= V.n) return;
-  switch (V.sh_degree) {   // uniform per block: one view per block
-    case 0: backward_wave<0, kAdam>(V, G, A, w0, rows); break;
-    case 1: backward_wave<1, kAdam>(V, G, A, w0, rows); break;
-    case 2: backward_wave<2, kAdam>(V, G, A, w0, rows); break;
-    default: backward_wave<3, kAdam>(V, G, A, w0, rows); break;
+  const int64_t base = (blockIdx.x - v * blocks) * span;
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) count = 0u;
+  __syncthreads();
+  for (int k = threadIdx.x; k < span; k += 256) {
+    const bool in = base + k < V.n;
+    const uint32_t vis = in ? V.vis[base + k] : 0u;
+    const bool take = (vis & kVisBit) && (vis & kRowBit);
+    const uint64_t m = __ballot(take);
+    uint32_t at = 0;
+    if (lane == 0 && m) at = atomicAdd(&count, (uint32_t)__builtin_popcountll(m));   // the order does not matter
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (take) list[at + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint16_t)k;
+  }
+  __syncthreads();
+  const uint32_t n = count;
+#pragma unroll 1
+  for (uint32_t r = threadIdx.x; r < n; r += 256) {
+    const ViewDesc* here = &V;
+    asm volatile("" : "+s"(here));   // keeps the camera's values and their products out of registers between splats
+    chain_splat<D, EXACT>(*here, base + list[r]);
   }
 }
 
-hipError_t launch_preprocess_backward(const DeviceBatch* dbatch, const Batch& b, const ges_splat_grads* grads,
-                                      hipStream_t stream, const AdamSplats* args, bool fused) {
+constexpr int kRowPad = 13;   // float4 slots per staged SH-gradient row (12 used at degree 3; 13 spreads LDS banks)
+
+// Adds the gradients of splat i over the views, in view order, to `acc` (see chain_splat) and its SH row in LDS.  A
+// view without rows of the splat adds zero.
+template <int D>
+__device__ __forceinline__ void sum_views(const DeviceBatch* db, const AdamSplats& A, int64_t i,
+                                          bool in, float (&acc)[12], float* row) {
+  constexpr int K = (D + 1) * (D + 1);
+  for (int v = 0; v < db->nviews; ++v) {
+    const ViewDesc& V = db->views[v];
+    const uint32_t vis = in ? V.vis[i] : 0u;
+    const bool row_here = (vis & kVisBit) && (vis & kRowBit);
+    double2* gp = reinterpret_cast<double2*>(V.grad2d + (int64_t)kGradStride * i);
+    if (in && !row_here && V.keep_grad2d) {   // inspection: rows nothing was added to read as zero
+#pragma unroll
+      for (int k = 0; k < ((vis & kVisBit) ? 5 : kGradStride / 2); ++k) gp[k] = make_double2(0.0, 0.0);
+    }
+    if (A.stat_accum && (vis & kVisBit)) {   // densification statistic: the mean-2D gradient in NDC units
+      if (row_here) {
+        const double2 g01 = gp[0];
+        const double su = g01.x * A.half_w, sv = g01.y * A.half_h;
+        A.stat_accum[i] += (float)sqrt(su * su + sv * sv);
+      }
+      A.stat_count[i] += 1.f;
+    }
+    if (!row_here) continue;
+    const float4* c = reinterpret_cast<const float4*>(V.chain) + 3 * i;
+    const float4 c0 = c[0], c1 = c[1], c2 = c[2];
+    const float val[12] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w, c2.x, c2.y, c2.z, c2.w};
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = acc[k] + val[k];
+    const double2 g67 = gp[3], g89 = gp[4];
+    const double gc3[3] = {(vis & 1u) ? 0.0 : g67.x, (vis & 2u) ? 0.0 : g67.y, (vis & 4u) ? 0.0 : g89.x};
+    const float* mu = V.means + 3 * i;
+    double x = 0.0, y = 0.0, z = 0.0, len;
+    if (D > 0) view_dir(V, mu[0], mu[1], mu[2], x, y, z, len);
+    double Y[16];
+    sh_basis_f64(x, y, z, D, Y);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) row[3 * k + ch] = row[3 * k + ch] + (float)(Y[k] * gc3[ch]);   // dL/dc = Y gc
+  }
+}
+
+__device__ __forceinline__ void rows_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One wave per 64 splats; the views of a batch (one scene) are added up on the way.
+template <int D, EmitMode M>
+__global__ void __launch_bounds__(256) preprocess_emit_kernel(const DeviceBatch* __restrict__ db, ges_splat_grads G,
+                                                              AdamSplats A) {
+  constexpr int K = (D + 1) * (D + 1);
+  __shared__ __align__(16) float sRows[4][64 * kRowPad * 4];
+  const int64_t blk = blockIdx.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float* rows = sRows[wave];
+  const int64_t n = db->views[0].n;
+  const int64_t w0 = blk * 256 + wave * 64;
+  if (w0 >= n) return;
+  const int64_t i = w0 + lane;
+  const int cnt = (int)min<int64_t>(64, n - w0);
+  float acc[12] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (M == kStore && A.accumulate && db->nviews > 1) {
+    // several views added to the stored gradients: view by view, starting from those
+    A.accumulate = 0;
+    if (G.sh)
+      for (int m = lane; m < cnt * 3 * K; m += 64)
+        rows[(m / (3 * K)) * kRowPad * 4 + (m % (3 * K))] = G.sh[(int64_t)3 * K * w0 + m];
+    if (i < n) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (G.means) acc[c] = G.means[3 * i + c];
+        if (G.log_scales) acc[3 + c] = G.log_scales[3 * i + c];
+      }
+      if (G.opacity_logits) acc[6] = G.opacity_logits[i];
+      if (G.beta) acc[7] = G.beta[i];
+      if (G.quats) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[8 + c] = G.quats[4 * i + c];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3 * K; ++k) rows[lane * kRowPad * 4 + k] = 0.f;
+  }
+  rows_fence();
+  sum_views<D>(db, A, i, i < n, acc, rows + lane * kRowPad * 4);
+  rows_fence();
+  // the wave's rows are one contiguous block of 3K x cnt floats: whole float4s at degrees 1 and 3
+  if (M != kStore || G.sh) {
+    if constexpr ((3 * K) % 4 == 0) {
+      constexpr int F4 = 3 * K / 4;
+      const int64_t base4 = (int64_t)F4 * w0;
+      const float4* r4 = reinterpret_cast<const float4*>(rows);
+#pragma unroll 4
+      for (int m = lane; m < cnt * F4; m += 64)
+        emit4<M, kParSh>(G.sh, A, base4 + m, r4[(m / F4) * kRowPad + (m % F4)]);
+    } else {
+#pragma unroll 4
+      for (int m = lane; m < cnt * 3 * K; m += 64)
+        emit<M, kParSh>(G.sh, A, (int64_t)3 * K * w0 + m, rows[(m / (3 * K)) * kRowPad * 4 + (m % (3 * K))]);
+    }
+  }
+  rows_fence();
+  // means and log-scales through LDS, so that consecutive lanes take consecutive floats
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    rows[3 * lane + c] = acc[c];
+    rows[192 + 3 * lane + c] = acc[3 + c];
+  }
+  rows_fence();
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int m = lane + 64 * c;
+    if (m < 3 * cnt) {
+      emit<M, kParMeans>(G.means, A, 3 * w0 + m, rows[m]);
+      emit<M, kParScales>(G.log_scales, A, 3 * w0 + m, rows[192 + m]);
+    }
+  }
+  if (i < n) {
+    emit4<M, kParQuats>(G.quats, A, i, make_float4(acc[8], acc[9], acc[10], acc[11]));
+    emit<M, kParOpacity>(G.opacity_logits, A, i, acc[6]);
+    emit<M, kParBeta>(G.beta, A, i, acc[7]);
+  }
+}
+
+template <int D>
+hipError_t launch_preprocess_backward_t(const DeviceBatch* dbatch, const Batch& b, const ges_splat_grads& g,
+                                        const AdamSplats& a, bool fused, hipStream_t stream) {
+  const int64_t n = b.items / b.nviews;   // the views of a backward render the same splats
+  const int span = chain_span(n);
+  const int64_t blocks = (n + span - 1) / span;
+  hipLaunchKernelGGL((b.falloff == GES_FALLOFF_PHI_EXACT ? preprocess_chain_kernel<D, true>
+                                                         : preprocess_chain_kernel<D, false>),
+                     dim3((unsigned)(blocks * b.nviews)), dim3(256), 0, stream, dbatch, blocks, span);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)(b.pre_blocks / b.nviews));
+  const int64_t bytes = n * 3 * 4 * (12 + 3 * (D + 1) * (D + 1));   // parameters and moments
+  auto kernel = !fused ? preprocess_emit_kernel<D, kStore>
+                       : bytes <= kStreamBytes ? preprocess_emit_kernel<D, kUpdate> : preprocess_emit_kernel<D, kUpdateStream>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, dbatch, g, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_preprocess_backward(const DeviceBatch* dbatch, const Batch& b, int sh_degree,
+                                      const ges_splat_grads* grads, hipStream_t stream, const AdamSplats* args,
+                                      bool fused) {
   if (b.pre_blocks == 0) return hipSuccess;
   const ges_splat_grads none{};
   const ges_splat_grads& g = grads ? *grads : none;
   const AdamSplats a = args ? *args : AdamSplats{};
-  const bool shared = b.shared_scene && b.nviews > 1;
-  const dim3 grid((unsigned)(shared ? b.pre_blocks / b.nviews : b.pre_blocks));
-  if (shared && fused)
-    hipLaunchKernelGGL((preprocess_backward_kernel<true, true>), grid, dim3(256), 0, stream, dbatch, g, a);
-  else if (shared)
-    hipLaunchKernelGGL((preprocess_backward_kernel<false, true>), grid, dim3(256), 0, stream, dbatch, g, a);
-  else if (fused)
-    hipLaunchKernelGGL((preprocess_backward_kernel<true, false>), grid, dim3(256), 0, stream, dbatch, g, a);
-  else
-    hipLaunchKernelGGL((preprocess_backward_kernel<false, false>), grid, dim3(256), 0, stream, dbatch, g, a);
-  return hipGetLastError();
+  switch (sh_degree) {   // a kernel per degree: the registers of the others would cost this one its waves
+    case 0: return launch_preprocess_backward_t<0>(dbatch, b, g, a, fused, stream);
+    case 1: return launch_preprocess_backward_t<1>(dbatch, b, g, a, fused, stream);
+    case 2: return launch_preprocess_backward_t<2>(dbatch, b, g, a, fused, stream);
+    default: return launch_preprocess_backward_t<3>(dbatch, b, g, a, fused, stream);
+  }
 }
 
 }  // namespace ges
