@@ -80,7 +80,8 @@ hipError_t mail_wait(const CountMail& m, const uint32_t* counter, hipStream_t st
 namespace {
 
 thread_local std::string g_last_error;
-thread_local ges::DeviceBatch g_host_batch;   // staging copy of the view table (pageable; copied per call)
+thread_local ges::DeviceBatch g_host_batch;   // staging copy of a larger view table (pageable; copied per call)
+thread_local ges::ViewPack g_pack;            // a smaller one goes with the call's first kernel
 
 // The key workspace and slot capacity each splat workspace was last rendered with: the backward pass reads
 // the sorted pairs and writes its rows there (its signature carries no slot count).
@@ -142,16 +143,26 @@ hipError_t timed(int stage, hipStream_t stream, F&& launch) {
   return hipSuccess;
 }
 
-// Build the batch of a step's views (one scene, one resolution) and copy it into the splat workspace.
+// Describe a step's views (one scene, one resolution) in the pack that its first kernel takes, or for more of them
+// than it holds in the view table of the splat workspace.
 hipError_t upload_views(const ges_splats* s, const ges_camera* cams, int32_t nv, const ges_raster_params* p,
                         const ges::ViewsPlan& vp, void* splat_ws, void* pixel_ws, float* out_rgb,
-                        const float* dL_drgb, hipStream_t stream, void* key_ws = nullptr, uint64_t key_slots = 0) {
+                        const float* dL_drgb, hipStream_t stream, ges::Batch& b, void* key_ws = nullptr,
+                        uint64_t key_slots = 0) {
+  const bool packed = nv <= ges::kPackViews;
   ges::DeviceBatch& hb = g_host_batch;
   const ges::FramePlan& fp = vp.fp;
   const int64_t pre = (s->n + 255) / 256;
   const size_t px3 = (size_t)3 * cams[0].width * cams[0].height;
+  if (packed) {
+    g_pack.nviews = nv;
+    g_pack.pre_blocks = pre;
+    g_pack.items = s->n;
+    g_pack.tiles = fp.tiles;
+    b.pack = &g_pack;
+  }
   hb.nviews = nv;
-  for (int32_t v = 0; v <= nv; ++v) {
+  for (int32_t v = 0; v <= nv && !packed; ++v) {
     hb.pre_prefix[v] = v * pre;
     hb.item_prefix[v] = v * s->n;
     hb.tile_prefix[v] = v * fp.tiles;
@@ -159,7 +170,7 @@ hipError_t upload_views(const ges_splats* s, const ges_camera* cams, int32_t nv,
   char* sw_base = reinterpret_cast<char*>(splat_ws);
   const ges::SortWs sw = ges::attach_sort_ws(ges::plan_sort((int64_t)nv * s->n), sw_base + vp.off_sort);
   for (int32_t v = 0; v < nv; ++v) {
-    ges::ViewDesc& V = hb.views[v];
+    ges::ViewDesc& V = packed ? g_pack.views[v] : hb.views[v];
     ges::fill_view(V, s, &cams[v], p);
     ges::attach_splat_ws(V, fp, sw_base + (size_t)v * vp.view_stride);
     V.item_key = sw.item_key + (size_t)v * s->n;
@@ -182,6 +193,7 @@ hipError_t upload_views(const ges_splats* s, const ges_camera* cams, int32_t nv,
     }
     V.keep_grad2d = (p->flags & GES_RASTER_KEEP_GRAD2D) ? 1 : 0;
   }
+  if (packed) return hipSuccess;
   return hipMemcpyAsync(sw_base + fp.off_db, &hb, ges::device_batch_bytes(nv), hipMemcpyHostToDevice, stream);
 }
 
@@ -200,8 +212,8 @@ ges::Batch views_batch(const ges_splats* s, const ges_raster_params* p, const ge
   return b;
 }
 
-const ges::DeviceBatch* dev_batch(void* splat_ws, const ges::FramePlan& fp) {
-  return reinterpret_cast<const ges::DeviceBatch*>(reinterpret_cast<char*>(splat_ws) + fp.off_db);
+ges::DeviceBatch* dev_batch(void* splat_ws, const ges::FramePlan& fp) {
+  return reinterpret_cast<ges::DeviceBatch*>(reinterpret_cast<char*>(splat_ws) + fp.off_db);
 }
 
 std::string check_all(const ges_splats* s, const ges_camera* c, const ges_raster_params* p) {
@@ -246,10 +258,10 @@ ges_status preprocess_views(const ges_splats* splats, const ges_camera* cams, in
     }
     mail = ges::mail_take();
   }
-  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, nullptr, nullptr, nullptr, stream), "upload");
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
   b.mail = mail;
-  const ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
+  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, nullptr, nullptr, nullptr, stream, b), "upload");
+  ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
   GES_CHECK_HIP(timed(GES_STAGE_PREPROCESS, stream, [&] { return ges::launch_preprocess(db, b, stream); }), "preprocess");
   GES_CHECK_HIP(timed(GES_STAGE_DEPTH_SORT, stream, [&] { return ges::launch_depth_sort(db, b, stream); }), "depth_sort");
   GES_CHECK_HIP(timed(GES_STAGE_KEY_SCAN, stream, [&] { return ges::launch_key_scan(db, b, stream); }), "key_scan");
@@ -282,15 +294,15 @@ ges_status render_forward_views(const ges_splats* splats, const ges_camera* cams
     g_keys_of_frame[splat_ws] = {num_keys > 0 ? key_ws : nullptr, num_keys};
   }
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
-  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, pixel_ws, out_rgb, nullptr, stream), "upload");
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
+  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, pixel_ws, out_rgb, nullptr, stream, b), "upload");
   b.key_capacity = num_keys;
   if (num_keys > 0) {
     b.kw = ges::attach_key_ws(kp, key_ws);
     b.sorted_pairs = b.kw.pv[0];
     b.sorted_tiles = b.kw.key[0];
   }
-  const ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
+  ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
   GES_CHECK_HIP(timed(GES_STAGE_DUPLICATE, stream, [&] { return ges::launch_duplicate(db, b, stream); }), "duplicate");
   GES_CHECK_HIP(timed(GES_STAGE_TILE_SORT, stream, [&] { return ges::launch_tile_sort(db, b, stream); }), "tile_sort");
   GES_CHECK_HIP(timed(GES_STAGE_RASTER_FORWARD, stream, [&] { return ges::launch_raster_forward(db, b, stream); }), "raster_forward");
@@ -323,16 +335,16 @@ ges_status render_backward(const ges_splats* splats, const ges_camera* cams, int
       return fail(GES_ERR_INVALID_ARGUMENT, "key_ws differs from the forward pass of this splat workspace");
     slots = it->second.second;
   }
-  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, pixel_ws, nullptr, dL_drgb, stream, key_ws,
-                             slots), "upload");
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
+  GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, pixel_ws, nullptr, dL_drgb, stream, b, key_ws,
+                             slots), "upload");
   const ges::KeyPlan kp = ges::plan_keys(slots, true);
   b.key_capacity = slots;
   if (slots) {
     b.kw = ges::attach_key_ws(kp, key_ws);
     b.sorted_pairs = b.kw.pv[0];
   }
-  const ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
+  ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
   if (slots) {   // without a slot no pixel composited anything
     GES_CHECK_HIP(timed(GES_STAGE_ZERO, stream, [&] {
                     return ges::launch_backward_prepare(
@@ -340,6 +352,8 @@ ges_status render_backward(const ges_splats* splats, const ges_camera* cams, int
                         (size_t)((slots + 31) / 32), stream);
                   }), "backward_prepare");
     GES_CHECK_HIP(timed(GES_STAGE_RASTER_BACKWARD, stream, [&] { return ges::launch_raster_backward(db, b, stream); }), "raster_backward");
+  } else {
+    GES_CHECK_HIP(ges::launch_views(db, b, stream), "views");
   }
   // every listed splat's row of grad2d (zero when its slots lie beyond the key capacity)
   char* kwb = reinterpret_cast<char*>(key_ws);

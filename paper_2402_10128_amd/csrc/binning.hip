@@ -259,7 +259,8 @@ __device__ __forceinline__ int owner_of(const uint32_t* ex, uint32_t x) {
 // those rows 64 at a time, one per lane; each slot receives (batch tile, splat index) when the exact test
 // admits the tile (always for SQUARE), else a dropped key.  Also per splat its tile count and visibility
 // bit, and per view its number of keys.
-__global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __restrict__ db,
+template <bool PACK>
+__global__ void __launch_bounds__(256) duplicate_kernel(DeviceBatch* __restrict__ db, const ViewPack pack,
                                                         const uint2* __restrict__ order,
                                                         const uint32_t* __restrict__ chunk_off, uint32_t* cells,
                                                         uint32_t* keys, uint32_t* vals, uint64_t capacity,
@@ -267,12 +268,14 @@ __global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __res
   __shared__ WaveSplats wave_lds[4];
   __shared__ uint32_t view_keys[kMaxViews];
   __shared__ uint32_t wave_total[4];
+  const Views<PACK> views{db, pack};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (PACK && blockIdx.x == 0) write_views(db, pack);
   for (int v = threadIdx.x; v < kMaxViews; v += 256) view_keys[v] = 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     const uint32_t slots = cells[1];
     cells[3] = (uint64_t)slots > capacity ? (uint32_t)capacity : slots;   // slots written below
-    if ((uint64_t)slots > capacity) atomicOr(&db->views[0].header[1], 1ull);
+    if ((uint64_t)slots > capacity) atomicOr(&views[0].header[1], 1ull);
   }
   __syncthreads();
   const uint32_t listed = cells[0];
@@ -289,9 +292,9 @@ __global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __res
     if (k < (int64_t)listed) {
       const uint2 cj = order[k];   // (candidate count, item)
       const uint32_t j = cj.y;
-      v = view_of_item(db, j);
-      const ViewDesc& V = db->views[v];
-      i = (int64_t)j - db->item_prefix[v];
+      v = PACK ? (int)(j / (uint32_t)pack.items) : view_of_item(db, j);
+      const ViewDesc& V = views[v];
+      i = (int64_t)j - (PACK ? v * pack.items : db->item_prefix[v]);
       const float4 r3 = V.rec[4 * i + 3];
       const uint32_t lo = __float_as_uint(r3.y), hi = __float_as_uint(r3.z);
       flags = (uint32_t)__float_as_int(r3.x) >> 24;
@@ -313,7 +316,7 @@ __global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __res
       W.qm[lane] = s.qm; W.inv_a[lane] = s.inv_a; W.inv_c[lane] = s.inv_c;
       W.q2[lane] = s.q2; W.det[lane] = s.det; W.Xe[lane] = s.Xe; W.Y[lane] = s.Y; W.ra[lane] = s.ra;
       W.id[lane] = (uint32_t)i;
-      W.tbase[lane] = (uint32_t)db->tile_prefix[v];
+      W.tbase[lane] = (uint32_t)(PACK ? v * pack.tiles : db->tile_prefix[v]);
       W.tx[lane] = V.tiles_x;
       W.wh[lane] = V.width | (V.height << 16);
     }
@@ -393,11 +396,11 @@ __global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __res
       done += ctotal;
       dup_wave_fence();
     }
-    if (live && W.filled[lane] != nslots) atomicOr(&db->views[0].header[1], 2ull);   // never expected
+    if (live && W.filled[lane] != nslots) atomicOr(&views[0].header[1], 2ull);   // never expected
     if (live) {
       // the preprocess left the candidate count in tiles_touched and the visibility bit set when it is
       // non-zero: rewrite them only where the exact count differs (scattered 4-byte stores)
-      const ViewDesc& V = db->views[v];
+      const ViewDesc& V = views[v];
       const uint32_t h = W.hits[lane];
       if (h != nslots) reinterpret_cast<uint32_t*>(V.rec)[16 * i + R_TOUCHED] = h;
       if (h == 0u && nslots != 0u) V.vis[i] = flags;
@@ -407,16 +410,17 @@ __global__ void __launch_bounds__(256) duplicate_kernel(const DeviceBatch* __res
     }
   }
   __syncthreads();
-  for (int vv = threadIdx.x; vv < db->nviews; vv += 256)
-    if (view_keys[vv]) atomicAdd(&db->views[vv].header[0], (unsigned long long)view_keys[vv]);
+  for (int vv = threadIdx.x; vv < views.count(); vv += 256)
+    if (view_keys[vv]) atomicAdd(&views[vv].header[0], (unsigned long long)view_keys[vv]);
 }
 
-hipError_t launch_duplicate(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
+hipError_t launch_duplicate(DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
   const SortWs& w = b.sw;
   const int64_t chunks = (b.items + 255) / 256;
-  if (chunks == 0 || b.key_capacity == 0) return hipSuccess;
+  if (chunks == 0 || b.key_capacity == 0) return launch_views(dbatch, b, stream);
   const int X = b.dup_buffer;
-  hipLaunchKernelGGL(duplicate_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, dbatch,
+  auto kernel = b.pack ? duplicate_kernel<true> : duplicate_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)chunks), dim3(256), 0, stream, dbatch, b.pack ? *b.pack : ViewPack{},
                      w.dv[w.depth_final], w.chunk_off, w.cells, b.kw.key[X],
                      reinterpret_cast<uint32_t*>(b.kw.pv[X]),
                      b.key_capacity, b.tile_cull == GES_TILES_ELLIPSE ? 1 : 0);

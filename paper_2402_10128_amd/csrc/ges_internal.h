@@ -139,6 +139,8 @@ struct KeyWs {
 };
 constexpr int kRowFloats = 12;   // floats per backward row (10 used; 48 bytes keep rows 16-byte aligned)
 
+struct ViewPack;
+
 struct Batch {
   int32_t nviews;
   int32_t falloff;               // shared by every view of a batch
@@ -154,6 +156,7 @@ struct Batch {
   uint32_t* sorted_tiles;        // [key capacity] batch tile per sorted pair (kw.key[0])
   int dup_buffer;                // buffer the duplication writes (so that the last tile pass ends in 0)
   uint64_t key_capacity;
+  const ViewPack* pack;          // host: the views, for the call's first kernel to write to the device (NULL: there)
   CountMail mail;                // where the batch's slot count is posted (slot NULL: nowhere)
 };
 
@@ -167,6 +170,36 @@ struct DeviceBatch {
   int32_t pad_;
   ViewDesc views[kMaxViews];
 };
+// The same for a few views of one resolution and scene size, passed to a call's first kernel by value: that kernel
+// works from it and writes the device table for the kernels behind it, which saves the copy of the table (a 5 us
+// blit on the stream and a staged host copy, three times per training frame).
+constexpr int kPackViews = 4;
+struct ViewPack {
+  int32_t nviews, pad_;
+  int64_t pre_blocks, items, tiles;   // per view
+  ViewDesc views[kPackViews];
+};
+static_assert(sizeof(ViewPack) <= 3072, "kernel arguments are limited to 4 KB");
+__device__ __forceinline__ void write_views(DeviceBatch* db, const ViewPack& p) {   // by one block
+  if ((int)threadIdx.x <= p.nviews) {
+    db->pre_prefix[threadIdx.x] = threadIdx.x * p.pre_blocks;
+    db->item_prefix[threadIdx.x] = threadIdx.x * p.items;
+    db->tile_prefix[threadIdx.x] = threadIdx.x * p.tiles;
+  }
+  if (threadIdx.x == 0) db->nviews = p.nviews;
+  const uint32_t* from = reinterpret_cast<const uint32_t*>(p.views);
+  uint32_t* to = reinterpret_cast<uint32_t*>(db->views);
+  for (uint32_t i = threadIdx.x; i < p.nviews * sizeof(ViewDesc) / 4; i += blockDim.x) to[i] = from[i];
+}
+// A kernel's views: from the pack it was given, or from the device table.
+template <bool PACK>
+struct Views {
+  const DeviceBatch* db;
+  const ViewPack& pack;
+  __device__ __forceinline__ int count() const { return PACK ? pack.nviews : db->nviews; }
+  __device__ __forceinline__ const ViewDesc& operator[](int v) const { return PACK ? pack.views[v] : db->views[v]; }
+};
+
 inline size_t device_batch_bytes(int nviews) { return offsetof(DeviceBatch, views) + (size_t)nviews * sizeof(ViewDesc); }
 
 constexpr int kAdamMaxGroups = GES_ADAM_MAX_GROUPS;
@@ -202,13 +235,14 @@ struct AdamSplats {
 
 // --------------------------------------------------------------------------------------------
 // launchers (implemented in the .hip files); all enqueue on `stream` and return hipError_t
-hipError_t launch_preprocess(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
+hipError_t launch_views(DeviceBatch* dbatch, const Batch& b, hipStream_t stream);   // the pack alone, if any
+hipError_t launch_preprocess(DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // depth-first binning (binning.hip): depth order of the listed splats, candidate slots along it (with the
 // batch's slot count in keys_total), then in the render: (tile, splat) pairs, the stable sort by tile and
 // the tile ranges
 hipError_t launch_depth_sort(const DeviceBatch* dbatch, Batch& b, hipStream_t stream);
 hipError_t launch_key_scan(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
-hipError_t launch_duplicate(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
+hipError_t launch_duplicate(DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 hipError_t launch_tile_sort(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // after the backward raster: the 2-D gradient of every splat with a row (nslots rows of kRowFloats floats,
 // marked in bits), its rows added in slot order (binary64); splats without a row are left alone
@@ -267,7 +301,7 @@ inline uint32_t radix_blocks(uint64_t n, int sub = 1) {
 hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // clears the row marks and, for frames whose walks are cut, lists the backward raster's work items (in
 // b.kw.pv[1]) and cut tiles (b.kw.table), with the plan in b.kw.plan; the raster then takes them
-hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
+hipError_t launch_backward_prepare(DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
                                    hipStream_t stream);
 hipError_t launch_raster_backward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
 // args (may be NULL): the fused update's arguments when `fused`; otherwise only accumulate and the

@@ -277,11 +277,14 @@ __device__ __forceinline__ void preprocess_splat(const ViewDesc& V, int64_t i) {
                                __uint_as_float((uint32_t)tx1 | ((uint32_t)ty1 << 16)), __uint_as_float(cand));
 }
 
-__global__ void __launch_bounds__(256) preprocess_kernel(const DeviceBatch* __restrict__ db) {
+template <bool PACK>
+__global__ void __launch_bounds__(256) preprocess_kernel(DeviceBatch* __restrict__ db, const ViewPack pack) {
+  const Views<PACK> views{db, pack};
   const int64_t blk = blockIdx.x;
-  const int v = view_of_block(db->pre_prefix, db->nviews, blk);
-  const ViewDesc& V = db->views[v];
-  const int64_t i = (blk - db->pre_prefix[v]) * 256 + threadIdx.x;
+  if (PACK && blk == 0) write_views(db, pack);
+  const int v = PACK ? (int)((uint32_t)blk / (uint32_t)pack.pre_blocks) : view_of_block(db->pre_prefix, db->nviews, blk);
+  const ViewDesc& V = views[v];
+  const int64_t i = (blk - (PACK ? v * pack.pre_blocks : db->pre_prefix[v])) * 256 + threadIdx.x;
   if (i >= V.n) return;
   switch (V.sh_degree) {   // uniform per block: one view per block
     case 0: preprocess_splat<0>(V, i); break;
@@ -291,9 +294,22 @@ __global__ void __launch_bounds__(256) preprocess_kernel(const DeviceBatch* __re
   }
 }
 
-hipError_t launch_preprocess(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
-  if (b.pre_blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(preprocess_kernel, dim3((unsigned)b.pre_blocks), dim3(256), 0, stream, dbatch);
+__global__ void __launch_bounds__(256) write_views_kernel(DeviceBatch* db, const ViewPack pack) {
+  write_views(db, pack);
+}
+
+hipError_t launch_views(DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
+  if (!b.pack) return hipSuccess;
+  hipLaunchKernelGGL(write_views_kernel, dim3(1), dim3(256), 0, stream, dbatch, *b.pack);
+  return hipGetLastError();
+}
+
+hipError_t launch_preprocess(DeviceBatch* dbatch, const Batch& b, hipStream_t stream) {
+  if (b.pre_blocks == 0) return launch_views(dbatch, b, stream);
+  if (b.pack)
+    hipLaunchKernelGGL(preprocess_kernel<true>, dim3((unsigned)b.pre_blocks), dim3(256), 0, stream, dbatch, *b.pack);
+  else
+    hipLaunchKernelGGL(preprocess_kernel<false>, dim3((unsigned)b.pre_blocks), dim3(256), 0, stream, dbatch, ViewPack{});
   return hipGetLastError();
 }
 

@@ -871,7 +871,9 @@ constexpr uint32_t kOrderTiles = 2048;
 // Targets of 2,560 / 4,096 / 8,192 / 16,384: four views of 512x512 686 / 602 / 561 / 568 us, GEF 300k at 801x533
 // 1,025 / 868 / 864 / 845; smaller frames reach the shortest segment with any.
 constexpr uint32_t kItemTarget = kMaxCheckpoints;   // boundaries <= walked positions / segment <= this
-__global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatch* __restrict__ db, uint2* items,
+template <bool PACK>
+__global__ void __launch_bounds__(1024) backward_prepare_kernel(DeviceBatch* __restrict__ db,
+                                                                const ViewPack pack, uint2* items,
                                                                 uint32_t* cut_tiles, uint32_t* plan, uint32_t* bits,
                                                                 size_t nwords) {
   if (blockIdx.x > 0) {
@@ -881,16 +883,18 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatc
     if (i0 < nwords - 4 * n4) bits[4 * n4 + i0] = 0u;
     return;
   }
+  if (PACK) write_views(db, pack);
   if (!items) return;
+  const Views<PACK> views{db, pack};
   __shared__ unsigned long long wsum[16];
   __shared__ unsigned long long carry;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const bool one = db->nviews == 1;
-  const uint32_t tiles = (uint32_t)db->tile_prefix[db->nviews], view_tiles = (uint32_t)db->tile_prefix[1];
-  const uint32_t* work0 = db->views[0].tile_work;
+  const bool one = views.count() == 1;
+  const uint32_t view_tiles = (uint32_t)(PACK ? pack.tiles : db->tile_prefix[1]), tiles = views.count() * view_tiles;
+  const uint32_t* work0 = views[0].tile_work;
   auto walk = [&](uint32_t t) -> uint32_t {   // the views of a backward share a resolution
     const uint32_t v = one ? 0u : t / view_tiles;
-    return (one ? work0 : db->views[v].tile_work)[t - v * view_tiles];
+    return (one ? work0 : views[v].tile_work)[t - v * view_tiles];
   };
   unsigned long long sum = 0;   // walked positions
   for (uint32_t t = threadIdx.x; t < tiles; t += 1024) sum += walk(t);
@@ -905,7 +909,7 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatc
   // positions of the list order: XCD by XCD, a padded run of groups each; one tile per thread and round
   const uint32_t gs = tiles < kOrderTiles ? 1u : (uint32_t)kXcdGroup;   // tiles dealt to an XCD together
   const uint32_t ngroups = (tiles + gs - 1) / gs, run = (ngroups + 7) / 8 * gs;
-  const uint32_t* order = one && gs > 1 ? db->views[0].group_order : nullptr;
+  const uint32_t* order = one && gs > 1 ? views[0].group_order : nullptr;
   for (uint32_t o0 = 0; o0 < 8 * run; o0 += 1024) {
     const uint32_t o = o0 + threadIdx.x, x = o / run, i = o - x * run;
     uint32_t g = 8 * (i / gs) + x, t = tiles, ns = 0;
@@ -931,7 +935,7 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatc
     if (ns > 1) {
       const uint32_t v = one ? 0u : t / view_tiles;
       cut_tiles[cut] = t;
-      db->views[v].tile_ckpt[t - v * view_tiles] = first - walks;   // the boundaries of the walks before it
+      views[v].tile_ckpt[t - v * view_tiles] = first - walks;   // the boundaries of the walks before it
     }
     for (uint32_t k = 0; k < ns; ++k) items[first + k] = make_uint2(t, k);
     __syncthreads();
@@ -950,11 +954,12 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(const DeviceBatc
 // not (cutting there: 1600x1040 354 -> 457 us, 1920x1080 420 -> 524, heavy overlap 1,366 -> 1,670).
 static bool cut_walks(const Batch& b) { return b.total_tiles <= 6144; }
 
-hipError_t launch_backward_prepare(const DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
+hipError_t launch_backward_prepare(DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
                                    hipStream_t stream) {
   const size_t clear = std::min<size_t>(1024, (nwords + 4095) / 4096);
-  hipLaunchKernelGGL(backward_prepare_kernel, dim3((unsigned)(1 + clear)), dim3(1024), 0, stream, dbatch,
-                     cut_walks(b) ? b.kw.pv[1] : nullptr, b.kw.table, b.kw.plan, bits, nwords);
+  auto kernel = b.pack ? backward_prepare_kernel<true> : backward_prepare_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(1 + clear)), dim3(1024), 0, stream, dbatch,
+                     b.pack ? *b.pack : ViewPack{}, cut_walks(b) ? b.kw.pv[1] : nullptr, b.kw.table, b.kw.plan, bits, nwords);
   return hipGetLastError();
 }
 

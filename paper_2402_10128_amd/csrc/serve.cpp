@@ -228,7 +228,7 @@ class GpuExecutor : public Executor {
 
   ges_status render(BatchWork& b, char* pool, std::string& err) override {
     hipStream_t st = streams_[b.stream];
-    const DeviceBatch* db = reinterpret_cast<const DeviceBatch*>(pool + b.table_off);
+    DeviceBatch* db = reinterpret_cast<DeviceBatch*>(pool + b.table_off);
     Batch bt = make_batch(b, pool);
     hipError_t e = launch_duplicate(db, bt, st);
     if (e == hipSuccess) e = launch_tile_sort(db, bt, st);

@@ -47,7 +47,7 @@ def _backward(t, cams, dLs, call):
 
 @pytest.mark.parametrize("n,degree", [(65, 0), (257, 1), (300, 2), (1000, 3), (380_000, 3)],
                          ids=["65_d0", "257_d1", "300_d2", "1000_d3", "380k_d3_past_the_caches"])
-@pytest.mark.parametrize("views", [1, 3])
+@pytest.mark.parametrize("views", [1, 3, 6])   # up to 4 views travel with the first kernel, more by a copy
 def test_views_and_fused_update(n, degree, views):
     """Stored gradients of a batch are the views' gradients added in view order, also onto what the buffers held;
     the fused update takes the same bits as the stand-alone one."""
