@@ -1,0 +1,45 @@
+"""The batched mixture fit at the sizes where its split of the work changes, against the binary64 oracle.
+
+A thread takes up to 4 points at a time in the residuals (256 threads: edges at multiples of 256, a second pass beyond
+1,024), a wave up to 1,024 points at a time in the gradients (groups of 4 x 64, a second chunk beyond 1,024) and the four
+waves take components in turn.  Centres on sample points, powers other than 2 and components so narrow that their
+exponentials vanish over most of the points are the values where the closed forms have a case of their own.
+Tolerances: as for the whole sweep, a gradient that sums m binary32 terms agrees to 1e-4 of the problem's largest, and
+the loss to 1e-4.  Adam's steps are not compared here: a centred component of a symmetric signal has a gradient of
+rounding only, whose sign decides them."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mixture1d as MX
+from paper_2402_10128_amd import ges as G
+from paper_2402_10128_amd import synth
+
+pytestmark = pytest.mark.gpu
+NAMES = ["gmm", "dog", "log", "gef"]
+
+
+@pytest.mark.parametrize("m", [2, 63, 65, 256, 257, 513, 769, 1024, 1025, 2100, 4096])
+def test_split_edges(m):
+    ns = {2: (1, 3), 1024: (4, 128), 4096: (5, 128)}.get(m, (1, 5))
+    W = synth.mixture_workload(seed=m, ns=ns, runs=1, m=m)
+    rng = np.random.default_rng(m)
+    par0, x = W["params"], W["x0"] + W["dx"] * np.arange(m, dtype=np.float64)
+    par0[:, :, 3] = rng.uniform(1.2, 3.0, par0.shape[:2])       # GEF powers (the others do not use it)
+    par0[::3, 0, 1] = np.float32(np.float32(W["x0"]) + np.float32(m // 2) * np.float32(W["dx"]))   # on a sample
+    par0[1::3, 0, 2] = 0.05                                     # exp(-200 d^2)
+    dev = torch.device("cuda:0")
+    def fit(epochs, grad):
+        return G.ges_mix_fit(torch.from_numpy(W["problems"]).to(dev), torch.from_numpy(W["targets"]).to(dev), W["x0"],
+                             W["dx"], torch.from_numpy(par0).to(dev), epochs, 0.01, grad_out=grad).cpu().numpy()
+
+    grad = torch.zeros(par0.shape, device=dev)
+    fit(1, grad)
+    grad, loss = grad.cpu().numpy(), fit(0, None)
+    for p in range(0, len(par0), 5):   # 5 is prime to the strides above and to the orders of models and weights
+        model, n, pos, tgt = (int(v) for v in W["problems"][p])
+        th0, y = par0[p, :n].astype(np.float64), W["targets"][tgt].astype(np.float64)
+        final, g = MX.loss_and_grad(NAMES[model], x, y, th0, bool(pos))
+        g = g.astype(np.float32)   # a narrow component between two points: 1e-61 is 0 in the type of the result
+        assert np.abs(grad[p, :n] - g).max() <= 1e-4 * np.abs(g).max(), (p, NAMES[model], n)
+        assert abs(loss[p] - final) <= 1e-4 * final + 1e-9, (p, NAMES[model], n)
