@@ -29,13 +29,9 @@ struct MaskWeights {
   int r1, r2;
 };
 
-struct MaskScratch {
-  unsigned int maxbits;   // largest |DoG| (non-negative floats order like their bits)
-};
-
 size_t freq_mask_scratch_bytes(int w, int h) {
   const size_t wl = (size_t)(w + kScale - 1) / kScale, hl = (size_t)(h + kScale - 1) / kScale;
-  return 256 + ((sizeof(MaskScratch) + 255) / 256) * 256 + 4 * wl * hl * sizeof(float) + 256;
+  return 768 + 4 * wl * hl * sizeof(float);
 }
 
 static void mask_weights(MaskWeights& mw, float s1, float s2) {
@@ -50,78 +46,189 @@ static void mask_weights(MaskWeights& mw, float s1, float s2) {
   }
 }
 
-__global__ void grey_down_kernel(const float* __restrict__ img, int w, int h, float* __restrict__ low, int wl, int hl,
-                                 MaskScratch* __restrict__ ms) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  if (x == 0 && y == 0) ms->maxbits = 0u;   // read only by the later kernels of this mask
-  if (x >= wl) return;
-  float acc = 0.f;
-  int cnt = 0;
-  for (int dy = 0; dy < kScale; ++dy) {
-    const int yy = y * kScale + dy;
-    if (yy >= h) break;
-    for (int dx = 0; dx < kScale; ++dx) {
-      const int xx = x * kScale + dx;
-      if (xx >= w) break;
-      const float* p = img + 3 * ((size_t)yy * w + xx);
-      acc += (p[0] + p[1] + p[2]) * (1.f / 3.f);
-      ++cnt;
+// The mask is three launches (four where it has more than kMaxInline tiles), each a few microseconds of latency more than
+// of work: a kernel asks for all it reads at once, stages it in LDS and walks the up to 129 taps there.  1080p, omega
+// 0.75: 41 -> 21 us; 512 x 512: 29 -> 17.  The four kernels before took the taps from memory, 8 in flight, and the maximum by 648 atomics on
+// one address.  Every sum runs in the order of the pixels or taps.
+constexpr int kRowThreads = 1024;
+constexpr int kRowSegment = 1024;                          // low pixels of a row per block: images up to 5,120 wide in one
+constexpr int kRowChunk = 512;                             // low pixels averaged at a time
+constexpr int kRowAhead = 2;                               // x 5 rows: pixels a thread has in flight
+
+// The weights to LDS, all at once: read where they are used, from the kernel's arguments, each line of 16 is a wait of its
+// own for memory.
+__device__ __forceinline__ void stage_weights(const MaskWeights& mw, float (&ws)[2][kMaxTaps + 3]) {
+  for (int k = threadIdx.x; k < 2 * kMaxTaps; k += blockDim.x) {
+    const int which = k >= kMaxTaps ? 1 : 0, e = k - which * kMaxTaps;
+    ws[which][e] = (which ? mw.w2 : mw.w1)[e];
+  }
+}
+
+// Grey, down-sampled row and the horizontal pass of both blurs.
+__global__ void __launch_bounds__(kRowThreads) mask_rows_kernel(const MaskWeights mw, const float* __restrict__ img, int w,
+                                                                int h, int wl, float* __restrict__ h1,
+                                                                float* __restrict__ h2) {
+  __shared__ float grey[kScale][kRowChunk * kScale];
+  __shared__ float low[kRowSegment + kMaxTaps - 1];
+  __shared__ __align__(16) float ws[2][kMaxTaps + 3];
+  const int t = threadIdx.x, y = blockIdx.y;
+  stage_weights(mw, ws);
+  const int xs = blockIdx.x * kRowSegment, xe = min(xs + kRowSegment, wl);
+  const int R = max(mw.r1, mw.r2);
+  const int a = max(xs - R, 0), b = min(xe + R, wl);       // low pixels this block needs
+  const int rows = min(kScale, h - y * kScale);
+  for (int c0 = a; c0 < b; c0 += kRowChunk) {
+    const int nlow = min(kRowChunk, b - c0), px0 = c0 * kScale, npx = min(nlow * kScale, w - px0);
+    const float* base = img + 3 * ((size_t)(y * kScale) * w + px0);
+    for (int p0 = 0; p0 < npx; p0 += kRowThreads * kRowAhead) {
+      float v[kRowAhead][kScale];
+#pragma unroll
+      for (int j = 0; j < kRowAhead; ++j)
+#pragma unroll
+        for (int r = 0; r < kScale; ++r) {
+          const float* q = base + 3 * ((size_t)min(r, rows - 1) * w + min(p0 + j * kRowThreads + t, npx - 1));
+          v[j][r] = (q[0] + q[1] + q[2]) * (1.f / 3.f);
+        }
+#pragma unroll
+      for (int j = 0; j < kRowAhead; ++j) {
+        const int p = p0 + j * kRowThreads + t;
+        if (p < npx)
+#pragma unroll
+          for (int r = 0; r < kScale; ++r) grey[r][p] = v[j][r];
+      }
+    }
+    __syncthreads();
+    if (t < nlow) {
+      const int cols = min(kScale, npx - t * kScale);
+      float acc = 0.f;
+      if (rows == kScale && cols == kScale) {
+#pragma unroll
+        for (int e = 0; e < kScale * kScale; ++e) acc += grey[e / kScale][t * kScale + e % kScale];
+      } else {
+        for (int dy = 0; dy < rows; ++dy)
+          for (int dx = 0; dx < cols; ++dx) acc += grey[dy][t * kScale + dx];
+      }
+      low[c0 - a + t] = acc / (float)(rows * cols);
+    }
+    __syncthreads();
+  }
+  for (int x = xs + t; x < xe; x += kRowThreads) {
+    float a1 = 0.f, a2 = 0.f;
+#pragma unroll 8
+    for (int k = 0; k <= 2 * mw.r1; ++k) a1 += ws[0][k] * low[min(max(x - mw.r1 + k, 0), wl - 1) - a];
+#pragma unroll 8
+    for (int k = 0; k <= 2 * mw.r2; ++k) a2 += ws[1][k] * low[min(max(x - mw.r2 + k, 0), wl - 1) - a];
+    h1[(size_t)y * wl + x] = a1;
+    h2[(size_t)y * wl + x] = a2;
+  }
+}
+
+constexpr int kColTileX = 32, kColTileY = 16;
+constexpr int kColThreads = kColTileX * kColTileY;
+constexpr int kColSpan = kColTileY + kMaxTaps - 1;         // rows a tile reads
+constexpr int kMaxInline = 512;                            // tile maxima that mask_up_kernel's waves take themselves
+
+// The largest of non-negative floats (or NaN, above all): they order like their bits.
+__device__ __forceinline__ unsigned wave_max_bits(unsigned m) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off, 64));
+  return m;
+}
+
+// Vertical pass, |DoG| and the tile's largest.
+__global__ void __launch_bounds__(kColThreads) mask_cols_kernel(const MaskWeights mw, const float* __restrict__ h1,
+                                                                const float* __restrict__ h2, int wl, int hl,
+                                                                float* __restrict__ dog, unsigned* __restrict__ tile_max) {
+  __shared__ float s1[kColSpan][kColTileX];
+  __shared__ float s2[kColSpan][kColTileX];
+  __shared__ unsigned wmax[kColThreads / 64];
+  __shared__ __align__(16) float ws[2][kMaxTaps + 3];
+  const int t = threadIdx.x, tx = t % kColTileX, ty = t / kColTileX;
+  const int x = blockIdx.x * kColTileX + tx, y0 = blockIdx.y * kColTileY;
+  const int n1 = kColTileY + 2 * mw.r1, n2 = kColTileY + 2 * mw.r2;
+  stage_weights(mw, ws);
+  {
+    constexpr int kPer = (kColSpan + kColTileY - 1) / kColTileY;
+    float v1[kPer], v2[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {   // rows outside the image repeat its edge
+      const int r = ty + j * kColTileY;
+      const size_t xc = min(x, wl - 1);
+      v1[j] = r < n1 ? h1[(size_t)min(max(y0 - mw.r1 + r, 0), hl - 1) * wl + xc] : 0.f;
+      v2[j] = r < n2 ? h2[(size_t)min(max(y0 - mw.r2 + r, 0), hl - 1) * wl + xc] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int r = ty + j * kColTileY;
+      if (r < n1) s1[r][tx] = v1[j];
+      if (r < n2) s2[r][tx] = v2[j];
     }
   }
-  low[(size_t)y * wl + x] = acc / (float)cnt;
-}
-
-// horizontal pass of both blurs
-__global__ void blur_h_kernel(const MaskWeights mw, const float* __restrict__ low, int wl, int hl,
-                              float* __restrict__ h1, float* __restrict__ h2) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  if (x >= wl) return;
-  const float* row = low + (size_t)y * wl;
-  float a1 = 0.f, a2 = 0.f;
-#pragma unroll 8
-  for (int k = -mw.r1; k <= mw.r1; ++k) a1 += mw.w1[k + mw.r1] * row[min(max(x + k, 0), wl - 1)];
-#pragma unroll 8
-  for (int k = -mw.r2; k <= mw.r2; ++k) a2 += mw.w2[k + mw.r2] * row[min(max(x + k, 0), wl - 1)];
-  h1[(size_t)y * wl + x] = a1;
-  h2[(size_t)y * wl + x] = a2;
-}
-
-// vertical pass, |DoG| and its maximum (a block maximum, then one atomic per block)
-__global__ void __launch_bounds__(128) blur_v_dog_kernel(MaskScratch* __restrict__ ms, const MaskWeights mw,
-                                                         const float* __restrict__ h1, const float* __restrict__ h2,
-                                                         int wl, int hl, float* __restrict__ dog) {
-  __shared__ float wmax[2];
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
+  __syncthreads();
   float d = 0.f;
-  if (x < wl) {
-    float a1 = 0.f, a2 = 0.f;   // unrolled so that several rows' loads are in flight at once
+  if (x < wl && y0 + ty < hl) {
+    float a1 = 0.f, a2 = 0.f;
 #pragma unroll 8
-    for (int k = -mw.r1; k <= mw.r1; ++k) a1 += mw.w1[k + mw.r1] * h1[(size_t)min(max(y + k, 0), hl - 1) * wl + x];
+    for (int k = 0; k <= 2 * mw.r1; ++k) a1 += ws[0][k] * s1[ty + k][tx];
 #pragma unroll 8
-    for (int k = -mw.r2; k <= mw.r2; ++k) a2 += mw.w2[k + mw.r2] * h2[(size_t)min(max(y + k, 0), hl - 1) * wl + x];
+    for (int k = 0; k <= 2 * mw.r2; ++k) a2 += ws[1][k] * s2[ty + k][tx];
     d = fabsf(a1 - a2);
-    dog[(size_t)y * wl + x] = d;
+    dog[(size_t)(y0 + ty) * wl + x] = d;
   }
-  float m = d;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  const unsigned m = wave_max_bits(__float_as_uint(d));
+  if ((t & 63) == 0) wmax[t >> 6] = m;
+  __syncthreads();
+  if (t == 0) {
+    unsigned b = wmax[0];
+    for (int k = 1; k < kColThreads / 64; ++k) b = max(b, wmax[k]);
+    tile_max[blockIdx.y * gridDim.x + blockIdx.x] = b;
+  }
+}
+
+__global__ void __launch_bounds__(1024) mask_max_kernel(unsigned* __restrict__ tile_max, int n) {
+  __shared__ unsigned wmax[16];
+  unsigned m = 0;
+  for (int k = threadIdx.x; k < n; k += 1024) m = max(m, tile_max[k]);
+  m = wave_max_bits(m);
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(&ms->maxbits, __float_as_uint(fmaxf(wmax[0], wmax[1])));
+  if (threadIdx.x == 0) {
+    for (int k = 0; k < 16; ++k) m = max(m, wmax[k]);
+    tile_max[0] = m;
+  }
 }
 
-__global__ void mask_up_kernel(const MaskScratch* __restrict__ ms, const float* __restrict__ dog, int wl, int w, int h,
-                               int invert, uint8_t* __restrict__ mask) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
+// Four neighbouring pixels of a row per thread; they lie over at most two low pixels.  words: a row's bytes can be stored
+// four at a time (the mask and its rows start at multiples of 4).
+__global__ void __launch_bounds__(256) mask_up_kernel(const unsigned* __restrict__ tile_max, int ntiles,
+                                                      const float* __restrict__ dog, int wl, int w, int invert, int words,
+                                                      uint8_t* __restrict__ mask) {
+  const int x = 4 * (blockIdx.x * 256 + threadIdx.x), y = blockIdx.y;
+  unsigned bits = 0;
+  for (int k = threadIdx.x & 63; k < ntiles; k += 64) bits = max(bits, tile_max[k]);
+  const float m = __uint_as_float(wave_max_bits(bits));
   if (x >= w) return;
-  const float m = __uint_as_float(ms->maxbits);
-  uint8_t bit = 0;
-  if (m > 1e-5f) bit = (dog[(size_t)(y / kScale) * wl + x / kScale] / m) > 0.5f ? 1 : 0;
-  mask[(size_t)y * w + x] = invert ? (uint8_t)(1 - bit) : bit;
+  const float* row = dog + (size_t)(y / kScale) * wl;
+  const int l0 = x / kScale, l1 = min(l0 + 1, wl - 1);
+  unsigned b0 = 0, b1 = 0;
+  if (m > 1e-5f) {
+    b0 = row[l0] / m > 0.5f ? 1 : 0;
+    b1 = row[l1] / m > 0.5f ? 1 : 0;
+  }
+  if (invert) {
+    b0 ^= 1;
+    b1 ^= 1;
+  }
+  const int split = (l0 + 1) * kScale - x;   // pixels of the first
+  unsigned v = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v |= (q < split ? b0 : b1) << (8 * q);
+  uint8_t* o = mask + (size_t)y * w + x;
+  if (words) {
+    *reinterpret_cast<unsigned*>(o) = v;
+  } else {
+    for (int q = 0; q < 4 && x + q < w; ++q) o[q] = (uint8_t)(v >> (8 * q));
+  }
 }
 
 hipError_t launch_freq_mask(const float* target, int w, int h, float omega, void* scratch, uint8_t* mask,
@@ -130,20 +237,24 @@ hipError_t launch_freq_mask(const float* target, int w, int h, float omega, void
   const float om = invert ? omega + 0.5f : omega;
   const float s2 = 0.1f + 10.f * om, s1 = 2.f * s2;
   const int wl = (w + kScale - 1) / kScale, hl = (h + kScale - 1) / kScale;
-  char* base = reinterpret_cast<char*>(scratch);
-  MaskScratch* ms = reinterpret_cast<MaskScratch*>(base);
-  float* low = reinterpret_cast<float*>(base + ((sizeof(MaskScratch) + 255) / 256) * 256);
-  float* h1 = low + (size_t)wl * hl;
+  float* h1 = reinterpret_cast<float*>(reinterpret_cast<char*>(scratch) + 256);
   float* h2 = h1 + (size_t)wl * hl;
   float* dog = h2 + (size_t)wl * hl;
+  unsigned* tile_max = reinterpret_cast<unsigned*>(dog + (size_t)wl * hl);   // at most one a low pixel
   MaskWeights mw;
   mask_weights(mw, s1, s2);
-  const dim3 gl((wl + 127) / 128, hl);
-  hipLaunchKernelGGL(grey_down_kernel, gl, dim3(128), 0, stream, target, w, h, low, wl, hl, ms);
-  hipLaunchKernelGGL(blur_h_kernel, gl, dim3(128), 0, stream, mw, low, wl, hl, h1, h2);
-  hipLaunchKernelGGL(blur_v_dog_kernel, gl, dim3(128), 0, stream, ms, mw, h1, h2, wl, hl, dog);
-  hipLaunchKernelGGL(mask_up_kernel, dim3((w + 255) / 256, h), dim3(256), 0, stream, ms, dog, wl, w, h,
-                     invert ? 1 : 0, mask);
+  const dim3 tiles((wl + kColTileX - 1) / kColTileX, (hl + kColTileY - 1) / kColTileY);
+  int ntiles = (int)(tiles.x * tiles.y);
+  hipLaunchKernelGGL(mask_rows_kernel, dim3((wl + kRowSegment - 1) / kRowSegment, hl), dim3(kRowThreads), 0, stream, mw,
+                     target, w, h, wl, h1, h2);
+  hipLaunchKernelGGL(mask_cols_kernel, tiles, dim3(kColThreads), 0, stream, mw, h1, h2, wl, hl, dog, tile_max);
+  if (ntiles > kMaxInline) {
+    hipLaunchKernelGGL(mask_max_kernel, dim3(1), dim3(1024), 0, stream, tile_max, ntiles);
+    ntiles = 1;
+  }
+  const int words = (w % 4 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0) ? 1 : 0;
+  hipLaunchKernelGGL(mask_up_kernel, dim3((w + 1023) / 1024, h), dim3(256), 0, stream, tile_max, ntiles, dog, wl, w,
+                     invert ? 1 : 0, words, mask);
   return hipGetLastError();
 }
 
@@ -180,8 +291,7 @@ hipError_t launch_freq_mask_static(const float* target, int w, int h, float omeg
     }
     ptr = g_static_ptr[dev];
   }
-  // the maximum word the scratch holds is cleared by the first kernel of the mask, so nothing else
-  // has to start at zero
+  // the mask's kernels write whatever they read of the scratch, so nothing has to start at zero
   return launch_freq_mask(target, w, h, omega, ptr, mask, stream);
 }
 
