@@ -124,8 +124,8 @@ hipError_t launch_depth_sort(const DeviceBatch* dbatch, Batch& b, hipStream_t st
   s.vals = w.item_cand;
   for (int k = 0; k < 2; ++k) { s.key_buf[k] = w.dk[k]; s.pair_buf[k] = w.dv[k]; }
   s.count_host = (uint32_t)b.items;
-  s.sub = radix_sub((uint64_t)b.items);
-  s.nblocks = radix_blocks((uint64_t)b.items, s.sub);
+  s.shape = radix_shape((uint64_t)b.items);
+  s.nblocks = s.shape.blocks((uint64_t)b.items);
   s.table = w.table;
   s.totals = w.totals;
   s.kept = &w.cells[0];
@@ -738,8 +738,8 @@ hipError_t launch_tile_sort(const DeviceBatch* dbatch, const Batch& b, hipStream
   s.vals = reinterpret_cast<const uint32_t*>(k.pv[X]);   // the first pass pairs each splat index with its slot
   for (int e = 0; e < 2; ++e) { s.key_buf[e] = k.key[X ^ 1 ^ e]; s.pair_buf[e] = k.pv[X ^ 1 ^ e]; }
   s.count_dev = &w.cells[3];
-  s.sub = radix_sub(b.key_capacity);
-  s.nblocks = radix_blocks(b.key_capacity, s.sub);
+  s.shape = radix_shape(b.key_capacity);
+  s.nblocks = s.shape.blocks(b.key_capacity);
   s.table = k.table;
   s.totals = k.totals;
   s.kept = &w.cells[2];

@@ -19,8 +19,10 @@ constexpr int kTilePx = kTile * kTile;   // 256 pixels, 4 per lane of one wave64
 constexpr int kRecWords = 16;            // 64-byte per-splat record
 constexpr int kGradStride = GES_GRAD2D_STRIDE;   // doubles per splat in the 2-D gradient accumulator
 constexpr int kMaxViews = 64;
-constexpr int kRadixThreads = 256;       // radix passes: blocks of 256 threads ...
-constexpr int kRadixItems = 8;           // ... holding 8 items each
+constexpr int kRadixThreads = 256;       // radix passes: blocks of at least 256 threads ...
+constexpr int kRadixItems = 8;           // ... holding at least 8 items each
+// more items than these take larger tiles (radix_shape; figures in radix.hip)
+constexpr uint64_t kRadixMid = 1ull << 21, kRadixBig = 1ull << 26;
 constexpr int kRadixMaxPasses = 4;
 constexpr uint32_t kRadixSmall = 8192;   // sorts of up to this many items are one block's work in LDS
 constexpr uint32_t kNoKey = 0xffffffffu; // radix key of an item that a filtering pass drops
@@ -250,6 +252,16 @@ hipError_t launch_row_reduce(const DeviceBatch* dbatch, const Batch& b, const fl
                              uint64_t nslots, hipStream_t stream);
 // A stable LSD radix sort of (u32 key, (u32, u32)) items by digits of up to 8 bits (radix.hip); an item's value
 // is (vals[i], i), items whose key is kNoKey are dropped.  Pass k writes buffer k & 1.
+struct RadixShape {
+  int32_t threads, items;        // a block of the downsweep and its items per thread: a tile
+  uint32_t tile() const { return (uint32_t)(threads * items); }
+  uint32_t blocks(uint64_t n) const { return (uint32_t)((n + tile() - 1) / tile()); }
+};
+inline RadixShape radix_shape(uint64_t n) {
+  if (n > kRadixBig) return {1024, 16};
+  if (n > kRadixMid) return {512, 8};
+  return {kRadixThreads, kRadixItems};
+}
 struct RadixSort {
   int32_t passes;
   int32_t bits[kRadixMaxPasses], shift[kRadixMaxPasses];   // digit k = (key >> shift) & ((1 << bits) - 1)
@@ -259,7 +271,7 @@ struct RadixSort {
   uint2* pair_buf[2];
   const uint32_t* count_dev;     // number of items (device), or NULL: count_host
   uint32_t count_host;
-  int32_t sub;                   // tiles of kRadixThreads x kRadixItems items per block
+  RadixShape shape;
   uint32_t nblocks;              // blocks covering the largest count
   uint32_t* table;               // [16][nblocks][16] (digit group, block, digit in the group)
   uint32_t* totals;              // [256]
@@ -270,7 +282,8 @@ struct RadixSort {
   uint32_t token;
 };
 struct RadixPass {
-  int32_t bits, shift, filter, sub;
+  int32_t bits, shift, filter;
+  uint32_t span;
   uint32_t nblocks;
   const uint32_t* keys_in;
   const uint32_t* vals_in;       // first pass
@@ -288,14 +301,9 @@ struct RadixPass {
   uint32_t token;
 };
 hipError_t launch_radix_sort(const RadixSort& s, hipStream_t stream);
-// Tiles of kRadixThreads x kRadixItems items that one radix block takes in turn: 1 up to 8,192 tiles (enough
-// blocks to fill the device), then up to 8 (fewer, longer blocks: a shorter digit table).
-inline int radix_sub(uint64_t n) {
-  const uint64_t tiles = (n + (uint64_t)kRadixThreads * kRadixItems - 1) / ((uint64_t)kRadixThreads * kRadixItems);
-  return (int)std::min<uint64_t>(8, std::max<uint64_t>(1, tiles / 8192));
-}
-inline uint32_t radix_blocks(uint64_t n, int sub = 1) {
-  const uint64_t span = (uint64_t)kRadixThreads * kRadixItems * sub;
+// Blocks that the smallest tile takes for n items: what the digit table is sized by.
+inline uint32_t radix_blocks(uint64_t n) {
+  const uint64_t span = (uint64_t)kRadixThreads * kRadixItems;
   return (uint32_t)((n + span - 1) / span);
 }
 hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipStream_t stream);
