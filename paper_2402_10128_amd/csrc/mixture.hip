@@ -7,18 +7,18 @@
 //
 // One workgroup of 256 threads runs one problem through all its epochs: the signal, the residuals, the
 // parameters, their Adam moments and gradients stay in LDS.  Per epoch:
-//   1. per component, its constants (MixComp);
+//   1. per component, the quantities every point needs (MixComp);
 //   2. residuals r_j = model(x_j) - y_j, threads over points, four points per thread for one read of a component;
 //   3. gradients sum_j (2/m) r_j dc_i/dtheta(x_j): the four waves take components in turn, the 64 lanes split the
-//      points.  A chunk of 1,024 points and residuals stays in registers for all of a wave's components, and a
-//      component's constant factors multiply its sums, not their terms;
-//   4. Adam on every parameter (the update shared with the splat optimiser).
-// What bounds it is VALU issue: of the 6.9 M cycles of the paper's sweep (7,680 problems x 1,000 points, 20 epochs)
-// a SIMD issues VALU instructions in 6.8 M.  The sweep took 13.1 ms when each term carried its factors, the
-// exponentials and powers were the library's, a reduction was 24 shuffles and the arrays for the largest m left room for
-// 3 blocks per CU; it takes 2.92 ms.  The exponentials and logarithms are the hardware's base-2 ones on constants that
-// are rounded once from binary64; gradients and losses are as close to binary64 as before (7e-8 to 1e-6 in the 2-norm,
-// by model and parameter).  An exponential below 2^-126 is 0.
+//      points and a butterfly adds the lanes.  A chunk of 1,024 points and residuals stays in registers for all of a
+//      wave's components;
+//   4. Adam on every parameter (the update shared with the splat optimiser), the bias corrections of 256 steps at a time
+//      from a table.
+// What bounds it is VALU issue.  @FIG@
+// Taking the constant factors out of the sums and the exponentials from the hardware's base-2 one takes 2.9 ms, no further
+// from binary64 -- but Adam's first steps are the sign of a gradient over its size, and where that is near zero other
+// roundings move a parameter by up to 6e-3 of its scale; so every term keeps its roundings, and only factors that
+// are powers of two are moved.
 // A component that would read past the LDS arrays (n outside 1..128), an unknown model or target row, or
 // m outside 1..4096 is not run: its loss is set to NaN.
 #include <cmath>
@@ -47,110 +47,96 @@ struct MixArgs {
   float lr, b1, b2, eps;
 };
 
-// Per-component constants of one epoch, computed in binary64 and rounded once.  With inv = 1/(2 s^2 + eps) the component
-// is w E, E = exp2(k q): q = d^2 = (x - mu)^2, or |d|^beta for GEF.  Step 3 sums, over the factors f:
-//   GMM  r E,             r E d,                    r E d^2
-//   DoG  r (E - E2),      r (E - k_mu E2) d,        r (E - k_s E2) d^2     E2 = exp2(k2 q), the subtracted Gaussian
-//   LoG  r P E,           r (P + k_mu) E d,         r (P + k_s) E d^2      P = 1 - q/s^2
-//   GEF  r E,             r E q / d,                r E q,                 r E q log2|d|
+// Per-component constants of one epoch.
 struct __attribute__((aligned(16))) MixComp {
-  float w, mu, k;
-  float beta_k2_is2;      // GEF, DoG, LoG
-  float at0;              // GEF: q at d = 0
-  float k_mu, k_s;
-  float f[4];             // of w_raw, mu, s, beta; 2/m included
+  float w, mu, inv1;     // inv1 = 1/(2 s^2 + eps)
+  float beta_inv2_is2;   // GEF: beta; DoG: inv2 = 1/(2 s^2/nu + eps); LoG: is2 = 1/s^2
+  float at0;             // GEF: |x - mu|^beta at x = mu
+  float dw, s, rs;       // dw/dw_raw; LoG: 1/s
 };
 
-__device__ __forceinline__ MixComp mix_prepare(const float* th, int model, int positive, double scale) {
+__device__ __forceinline__ MixComp mix_prepare(const float* th, int model, int positive) {
   MixComp c{};
-  const float w_raw = th[0], beta = th[3];
-  const double s = (double)th[2], eps = (double)kMixEps, nu = (double)kMixNu;
-  const double log2e = 1.44269504088896340736, ln2 = 0.693147180559945309417;
-  float dw = 1.f;
+  const float w_raw = th[0];
   c.mu = th[1];
-  c.w = w_raw;
+  c.s = th[2];
   if (positive) {
     c.w = w_raw > 30.f ? w_raw : log1pf(expf(fminf(w_raw, 30.f)));
-    dw = 1.f / (1.f + expf(-w_raw));
+    c.dw = 1.f / (1.f + expf(-w_raw));
+  } else {
+    c.w = w_raw;
+    c.dw = 1.f;
   }
-  const double inv = 1.0 / (2.0 * s * s + eps), w = (double)c.w * scale * inv;
-  c.k = (float)(-inv * log2e);
-  c.f[0] = (float)(dw * scale);
-  c.f[1] = (float)(2.0 * w);
-  c.f[2] = (float)(4.0 * w * s * inv);
+  c.inv1 = 1.f / (2.f * c.s * c.s + kMixEps);
   if (model == GES_MIX_GEF) {
-    c.beta_k2_is2 = beta;
-    c.at0 = powf(0.f, beta);
-    c.f[1] = (float)(w * beta);
-    c.f[3] = (float)(-w * ln2);
+    c.beta_inv2_is2 = th[3];
+    c.at0 = powf(0.f, th[3]);
   } else if (model == GES_MIX_DOG) {
-    const double inv2 = 1.0 / (2.0 * s * s / nu + eps), ratio = inv2 / inv;
-    c.beta_k2_is2 = (float)(-inv2 * log2e);
-    c.k_mu = (float)ratio;
-    c.k_s = (float)(ratio * ratio / nu);
+    c.beta_inv2_is2 = 1.f / (2.f * c.s * c.s / kMixNu + kMixEps);
   } else if (model == GES_MIX_LOG) {
-    const double is2 = 1.0 / (s * s), ratio = is2 / inv;
-    c.beta_k2_is2 = (float)is2;
-    c.k_mu = (float)ratio;
-    c.k_s = (float)(0.5 * ratio * ratio);
+    c.beta_inv2_is2 = 1.f / (c.s * c.s);
+    c.rs = 1.f / c.s;
   }
   return c;
-}
-
-// |d|^beta for a normal |d|, by the hardware's base-2 logarithm and exponential; beta log2|d| is carried in two parts.
-__device__ __forceinline__ float mix_pow(float l, float beta) {
-  const float h = beta * l;
-  const float e = fminf(__builtin_amdgcn_exp2f(h), 3.402823466e38f);   // finite: the second part may be negative
-  return __builtin_fmaf(e, __builtin_fmaf(beta, l, -h) * 0.693147180559945309417f, e);
 }
 
 // Component c at x, over w.
 template <int MODEL>
 __device__ __forceinline__ float mix_value(const MixComp& c, float x) {
-  const float d = x - c.mu;
+  const float d = x - c.mu, d2 = d * d;
   if (MODEL == GES_MIX_GEF) {
     const float ad = fabsf(d);
-    const float a = ad < 1.17549435e-38f ? c.at0 : mix_pow(__builtin_amdgcn_logf(ad), c.beta_k2_is2);
-    return __builtin_amdgcn_exp2f(a * c.k);
+    const float a = ad == 0.f ? c.at0 : expf(c.beta_inv2_is2 * logf(ad));
+    return expf(-a * c.inv1);
   }
-  const float q = d * d, E = __builtin_amdgcn_exp2f(q * c.k);
-  if (MODEL == GES_MIX_DOG) return E - __builtin_amdgcn_exp2f(q * c.beta_k2_is2);
-  if (MODEL == GES_MIX_LOG) return __builtin_fmaf(-q, c.beta_k2_is2, 1.f) * E;
-  return E;
+  const float E1 = expf(-d2 * c.inv1);
+  if (MODEL == GES_MIX_DOG) return E1 - expf(-d2 * c.beta_inv2_is2);
+  if (MODEL == GES_MIX_LOG) return (1.f - d2 * c.beta_inv2_is2) * E1;
+  return E1;
 }
 
-// Adds the terms of one point with residual r (table above MixComp).
+// Adds r times the derivatives of a component by (w_raw, mu, s, beta); that by mu is left halved but for GEF:
+// powers of two change no rounding.
 template <int MODEL>
 __device__ __forceinline__ void mix_grad(const MixComp& c, float x, float r, float (&acc)[4]) {
-  const float d = x - c.mu;
+  const float d = x - c.mu, d2 = d * d, s4 = 4.f * c.s;
+  float base, db_mu, db_s;
   if (MODEL == GES_MIX_GEF) {
-    const float ad = fabsf(d);
-    const bool at = ad < 1.17549435e-38f;   // at the centre (or a denormal off it) the derivatives but w's are 0
-    const float l = __builtin_amdgcn_logf(ad);
-    const float a = at ? c.at0 : mix_pow(l, c.beta_k2_is2);
-    const float rE = r * __builtin_amdgcn_exp2f(a * c.k), ra = rE * a;
-    acc[0] += rE;
-    acc[1] = __builtin_fmaf(ra, at ? 0.f : __builtin_amdgcn_rcpf(d), acc[1]);
-    acc[2] += ra;
-    acc[3] = __builtin_fmaf(ra, at ? 0.f : l, acc[3]);
-    return;
-  }
-  const float q = d * d, rE = r * __builtin_amdgcn_exp2f(q * c.k);
-  if (MODEL == GES_MIX_GMM) {
-    acc[0] += rE;
-    acc[1] = __builtin_fmaf(rE, d, acc[1]);
-    acc[2] = __builtin_fmaf(rE, q, acc[2]);
-  } else if (MODEL == GES_MIX_DOG) {
-    const float rE2 = r * __builtin_amdgcn_exp2f(q * c.beta_k2_is2);
-    acc[0] += rE - rE2;
-    acc[1] = __builtin_fmaf(__builtin_fmaf(-c.k_mu, rE2, rE), d, acc[1]);
-    acc[2] = __builtin_fmaf(__builtin_fmaf(-c.k_s, rE2, rE), q, acc[2]);
+    const float beta = c.beta_inv2_is2, ad = fabsf(d);
+    const bool off = ad != 0.f;
+    const float l = logf(ad);
+    const float a = off ? expf(beta * l) : c.at0;
+    base = expf(-a * c.inv1);
+    const float da_mu = off ? -beta * expf((beta - 1.f) * l) * (d > 0.f ? 1.f : -1.f) : 0.f;
+    const float da_b = off ? a * l : 0.f;
+    db_mu = -base * da_mu * c.inv1;
+    db_s = base * a * s4 * c.inv1 * c.inv1;
+    acc[3] = __builtin_fmaf(r, c.w * (-base * da_b * c.inv1), acc[3]);
   } else {
-    const float P = __builtin_fmaf(-q, c.beta_k2_is2, 1.f);
-    acc[0] = __builtin_fmaf(rE, P, acc[0]);
-    acc[1] = __builtin_fmaf(rE * d, P + c.k_mu, acc[1]);
-    acc[2] = __builtin_fmaf(rE * q, P + c.k_s, acc[2]);
+    const float E1 = expf(-d2 * c.inv1);
+    if (MODEL == GES_MIX_GMM) {
+      base = E1;
+      db_mu = E1 * d * c.inv1;
+      db_s = E1 * d2 * s4 * c.inv1 * c.inv1;
+    } else if (MODEL == GES_MIX_DOG) {
+      const float inv2 = c.beta_inv2_is2, E2 = expf(-d2 * inv2);
+      base = E1 - E2;
+      db_mu = E1 * d * c.inv1 - E2 * d * inv2;
+      db_s = E1 * d2 * s4 * c.inv1 * c.inv1 - E2 * d2 * (s4 / kMixNu) * inv2 * inv2;
+    } else {
+      const float is2 = c.beta_inv2_is2, P = 1.f - d2 * is2;
+      base = P * E1;
+      db_mu = d * is2 * E1 + base * d * c.inv1;
+      // 2 d2 is2 / s by the reciprocal: the remainder step rounds it, the last instruction of a division sees to zeros,
+      // infinities and NaN
+      const float n = 2.f * d2 * is2, q = n * c.rs;
+      const float over_s = __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, c.s, n), c.rs, q), c.s, n);
+      db_s = over_s * E1 + base * d2 * s4 * c.inv1 * c.inv1;
+    }
   }
+  acc[0] = __builtin_fmaf(r, c.dw * base, acc[0]);
+  acc[1] = __builtin_fmaf(r, c.w * db_mu, acc[1]);
+  acc[2] = __builtin_fmaf(r, c.w * db_s, acc[2]);
 }
 
 // The wave's sums of four values: row k of 16 lanes returns that of v[k], in each of its lanes.  The two swaps halve the
@@ -189,7 +175,7 @@ __device__ __forceinline__ void mix_residuals(const MixArgs& a, int n, int j0, c
   for (int i = 0; i < n; ++i) {
     const MixComp c = comp[i];
 #pragma unroll
-    for (int e = 0; e < NE; ++e) v[e] = __builtin_fmaf(c.w, mix_value<MODEL>(c, x[e]), v[e]);
+    for (int e = 0; e < NE; ++e) v[e] += c.w * mix_value<MODEL>(c, x[e]);
   }
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
@@ -206,6 +192,7 @@ struct MixLds {
   float th[kMixMaxN][4], mo[kMixMaxN][4], ve[kMixMaxN][4], gr[kMixMaxN][4];
   MixComp comp[kMixMaxN];
   float lsum[kMixThreads / 64];
+  float2 bias[kMixThreads];   // (step size, 1/sqrt(bias correction 2)) of the next steps
 };
 
 // All epochs of one problem.  sy, sr: [m] signal and residuals.
@@ -214,10 +201,15 @@ __device__ __forceinline__ void mix_fit(const MixArgs& a, int p, int n, int posi
                                         float* sr) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int M = a.m;
-  double pow1 = 1.0, pow2 = 1.0;   // b1^step, b2^step
+  const float scale = 2.f / (float)M;
   for (int ep = 0; ep <= a.epochs; ++ep) {
     // 1. per-component constants
-    for (int i = t; i < n; i += kMixThreads) L.comp[i] = mix_prepare(L.th[i], MODEL, positive, 2.0 / (double)M);
+    for (int i = t; i < n; i += kMixThreads) L.comp[i] = mix_prepare(L.th[i], MODEL, positive);
+    if (ep % kMixThreads == 0 && ep + t < a.epochs) {
+      const int step = ep + t + 1;
+      const double bc1 = 1.0 - pow((double)a.b1, (double)step), bc2 = 1.0 - pow((double)a.b2, (double)step);
+      L.bias[t] = make_float2((float)((double)a.lr / bc1), (float)(1.0 / sqrt(bc2)));
+    }
     __syncthreads();
     // 2. residuals (and, after the last update, the loss)
     float l2 = 0.f;
@@ -239,27 +231,32 @@ __device__ __forceinline__ void mix_fit(const MixArgs& a, int p, int n, int posi
       break;
     }
     __syncthreads();
-    // 3. gradients: a chunk of points in registers, the wave's components over it
-    for (int c0 = 0; c0 < M; c0 += 64 * kMixChunk) {
-      float r[kMixChunk], x[kMixChunk];
+    // 3. gradients: up to 1,024 points in registers, the wave's components over them
+    float r[kMixChunk], x[kMixChunk];
+    auto load = [&](int c0) {
 #pragma unroll
       for (int e = 0; e < kMixChunk; ++e) {
         const int j = c0 + e * 64 + lane, jc = min(j, M - 1);   // lanes past the end: the last point, with no weight
         r[e] = j < M ? sr[jc] : 0.f;
         x[e] = a.x0 + (float)jc * a.dx;
       }
-      for (int i = wave; i < n; i += kMixThreads / 64) {
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        const MixComp c = L.comp[i];
+    };
+    const bool one = M <= 64 * kMixChunk;
+    if (one) load(0);
+    for (int i = wave; i < n; i += kMixThreads / 64) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      const MixComp c = L.comp[i];
+      for (int c0 = 0; c0 < M; c0 += 64 * kMixChunk) {
+        if (!one) load(c0);
 #pragma unroll
         for (int e = 0; e < kMixChunk; ++e) {
           if (e % 4 == 0 && c0 + e * 64 >= M) break;   // uniform
           mix_grad<MODEL>(c, x[e], r[e], acc);
         }
-        const float sum = mix_sum_rows(acc);
-        const int k = lane >> 4;
-        if ((lane & 15) == 0) L.gr[i][k] = (c0 ? L.gr[i][k] : 0.f) + sum * L.comp[i].f[k];
       }
+      if (MODEL != GES_MIX_GEF) acc[1] *= 2.f;
+      const float sum = mix_sum_rows(acc);
+      if ((lane & 15) == 0) L.gr[i][lane >> 4] = sum * scale;
     }
     __syncthreads();
     if (ep == 0 && a.grad_out) {
@@ -267,14 +264,10 @@ __device__ __forceinline__ void mix_fit(const MixArgs& a, int p, int n, int posi
       for (int q = t; q < n * 4; q += kMixThreads) G[q] = L.gr[q >> 2][q & 3];
     }
     // 4. Adam (bias corrections of step ep + 1)
-    if (t < n * 4) {
-      pow1 *= (double)a.b1;
-      pow2 *= (double)a.b2;
-      const float step_size = (float)((double)a.lr / (1.0 - pow1)), inv_sqrt_bc2 = (float)(1.0 / sqrt(1.0 - pow2));
-      for (int q = t; q < n * 4; q += kMixThreads)
-        adam_update(L.th[q >> 2][q & 3], L.gr[q >> 2][q & 3], L.mo[q >> 2][q & 3], L.ve[q >> 2][q & 3], a.b1, a.b2,
-                    a.eps, step_size, inv_sqrt_bc2);
-    }
+    const float2 bias = L.bias[ep % kMixThreads];
+    for (int q = t; q < n * 4; q += kMixThreads)
+      adam_update(L.th[q >> 2][q & 3], L.gr[q >> 2][q & 3], L.mo[q >> 2][q & 3], L.ve[q >> 2][q & 3], a.b1, a.b2, a.eps,
+                  bias.x, bias.y);
     __syncthreads();
   }
 }
