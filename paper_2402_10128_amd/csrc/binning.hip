@@ -430,20 +430,31 @@ hipError_t launch_duplicate(DeviceBatch* dbatch, const Batch& b, hipStream_t str
 // After the backward raster: each splat's 2-D gradient, the sum of the rows the raster stored at its
 // candidate slots (one per tile in which some pixel composited it; about a tenth of the slots, as the tiles'
 // walks end where their pixels saturate), added in binary64 in slot order -- the same order on every run,
-// so the backward is deterministic.  A wave takes 8 words of the row marks (256 slots): it lists their marked
+// so the backward is deterministic.  A wave takes 8 or 32 words of the row marks (32 slots each): it lists their marked
 // slots in LDS, loads 64 rows at a time (one per lane; a row carries its splat's batch item and first
-// candidate slot) and the first lane of each run of one splat's rows adds the run from LDS, carrying an
+// candidate slot) and each run of one splat's rows is added from LDS, carrying an
 // unfinished run into the next 64 and, past the wave's words, through the rest of the splat's slot range.
 // The run at the start of the range belongs to the wave holding the splat's first row if that lies before
 // the range.  The splat's 2-D gradient is written and kRowBit set in its visibility word (the preprocess
 // backward takes zero without it).
-constexpr int kReduceWords = 8;
+//
+// What bounds it is the latency of a wave's steps and, of those, the sums.  A chunk of 64 rows with many runs (splats of one or two rows) is added a run per lane; one with few runs a component
+// per lane, 6 runs of 10 at a time, or the few lanes with a run would add ten numbers per row, one row after the other.
+// Both add in the same order.  A run per lane for every chunk, and 8 words per wave for every frame, took 587 us for
+// 169M slots, 215 for 5M of large splats, 102 for 13.5M and 77 for 3.9M; now 251, 59, 65 and 42.
 constexpr uint32_t kNoItem = 0xffffffffu;
+// More slots than this: ranges of 32 words per wave, as a tenth of the slots of such a frame has a row and a wave should
+// have some tens of them (169M slots 422 -> 251 us; 5M slots of large splats, most with a row, 59 -> 72).
+constexpr uint64_t kReduceWide = 1ull << 25;
+constexpr int kReduceRuns = 6;        // runs that are added together, a component per lane
+constexpr int kReduceFew = 2 * kReduceRuns;   // up to so many runs in 64 rows (1M splats: 6 43, 12 42, 24 42 us; 50k: 19, 19, 25)
 
+template <int WORDS>
 struct ReduceLds {
-  uint32_t slot[kReduceWords * 32];   // marked slots, in order
-  Vec4 row[64][3];                    // the current 64 rows
+  uint32_t slot[WORDS * 32];          // marked slots, in order
+  float row[64][kRowFloats];          // the current 64 rows
   uint32_t owner[64];
+  uint32_t start[64 + 1];             // first rows of the runs, and the end of the last
   double carry[10];                   // sums of the run left open by the last 64 rows
   uint32_t carry_owner;
 };
@@ -454,39 +465,47 @@ __device__ __forceinline__ void reduce_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ void write_grad2d(const DeviceBatch* db, uint32_t item, const double* g) {
+__device__ __forceinline__ double* grad2d_of(const DeviceBatch* db, uint32_t item, uint32_t*& vis) {
   const int v = view_of_item(db, item);
   const ViewDesc& V = db->views[v];
   const int64_t i = (int64_t)item - db->item_prefix[v];
-  double2* gs = reinterpret_cast<double2*>(V.grad2d + (int64_t)kGradStride * i);
+  vis = V.vis + i;
+  return V.grad2d + (int64_t)kGradStride * i;
+}
+
+__device__ __forceinline__ void write_grad2d(const DeviceBatch* db, uint32_t item, const double* g) {
+  uint32_t* vis;
+  double2* gs = reinterpret_cast<double2*>(grad2d_of(db, item, vis));
 #pragma unroll
   for (int c = 0; c < 5; ++c) gs[c] = make_double2(g[2 * c], g[2 * c + 1]);
-  __hip_atomic_fetch_or(V.vis + i, kRowBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_fetch_or(vis, kRowBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void add_row(double* g, const Vec4* r) {
-  g[0] += r[0][0]; g[1] += r[0][1]; g[2] += r[0][2]; g[3] += r[0][3];
-  g[4] += r[1][0]; g[5] += r[1][1]; g[6] += r[1][2]; g[7] += r[1][3];
-  g[8] += r[2][0]; g[9] += r[2][1];
+// Component c of it, by the lane that has it.
+__device__ __forceinline__ void write_grad2d(const DeviceBatch* db, uint32_t item, int c, double g) {
+  uint32_t* vis;
+  grad2d_of(db, item, vis)[c] = g;
+  if (c == 0) __hip_atomic_fetch_or(vis, kRowBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The marked slots of words [w0, w0 + kReduceWords) below `end` into L.slot, in order; returns their count.
+// The marked slots of words [w0, w0 + WORDS) below `end` into L.slot, in order; returns their count.
+template <int WORDS>
 __device__ __forceinline__ uint32_t list_marks(const GlobalU32* bits, uint64_t w0, uint64_t nwords, uint64_t end,
-                                               ReduceLds& L, int lane) {
+                                               ReduceLds<WORDS>& L, int lane) {
   const uint64_t q = w0 + (uint64_t)lane;
   uint32_t m = 0u;
-  if (lane < kReduceWords && q < nwords && q * 32 < end) {
+  if (lane < WORDS && q < nwords && q * 32 < end) {
     m = bits[q];
     if (end - q * 32 < 32) m &= (1u << (uint32_t)(end - q * 32)) - 1u;
   }
   const uint32_t cnt = (uint32_t)__builtin_popcount(m);
   uint32_t incl = cnt;
 #pragma unroll
-  for (int d = 1; d < kReduceWords; d <<= 1) {
+  for (int d = 1; d < WORDS; d <<= 1) {
     const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
     if (lane >= d) incl += y;
   }
-  const uint32_t total = (uint32_t)__shfl((int)incl, kReduceWords - 1, 64);
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WORDS - 1);
   uint32_t p = incl - cnt;
   while (m) {
     L.slot[p++] = (uint32_t)(q * 32) + (uint32_t)__builtin_ctz(m);
@@ -497,7 +516,8 @@ __device__ __forceinline__ uint32_t list_marks(const GlobalU32* bits, uint64_t w
 }
 
 // Lane-per-row load of rows [c0, c0 + n) of the list into LDS; returns the lane's row's item and first slot.
-__device__ __forceinline__ void load_rows(const GlobalVec4* rows, ReduceLds& L, uint32_t c0, uint32_t n, int lane,
+template <int WORDS>
+__device__ __forceinline__ void load_rows(const GlobalVec4* rows, ReduceLds<WORDS>& L, uint32_t c0, uint32_t n, int lane,
                                           uint32_t& item, uint32_t& first) {
   item = kNoItem;
   first = 0u;
@@ -506,29 +526,32 @@ __device__ __forceinline__ void load_rows(const GlobalVec4* rows, ReduceLds& L, 
     const Vec4 a0 = r[0], a1 = r[1], a2 = r[2];
     item = __float_as_uint(a2[2]);
     first = __float_as_uint(a2[3]);
-    L.row[lane][0] = a0;
-    L.row[lane][1] = a1;
-    L.row[lane][2] = a2;
+    Vec4* to = reinterpret_cast<Vec4*>(L.row[lane]);
+    to[0] = a0;
+    to[1] = a1;
+    to[2] = a2;
   }
   L.owner[lane] = item;
 }
 
+template <int WORDS>
 __global__ void __launch_bounds__(256) row_reduce_kernel(const DeviceBatch* __restrict__ db,
                                                          const float* __restrict__ rows_,
                                                          const uint32_t* __restrict__ bits_, uint64_t nslots) {
-  __shared__ ReduceLds lds[4];
+  __shared__ __align__(16) ReduceLds<WORDS> lds[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  ReduceLds& L = lds[wave];
+  ReduceLds<WORDS>& L = lds[wave];
   const uint64_t nwords = (nslots + 31) / 32;
-  const uint64_t w0 = ((uint64_t)blockIdx.x * 4 + wave) * kReduceWords;
+  const uint64_t w0 = ((uint64_t)blockIdx.x * 4 + wave) * WORDS;
   if (w0 >= nwords) return;
-  const uint64_t wend = min<uint64_t>((w0 + kReduceWords) * 32, nslots);   // first slot after the range
+  const uint64_t wend = min<uint64_t>((w0 + WORDS) * 32, nslots);   // first slot after the range
   const GlobalU32* bits = (const GlobalU32*)bits_;
   const GlobalVec4* rows = (const GlobalVec4*)rows_;
   const uint32_t total = list_marks(bits, w0, nwords, wend, L, lane);
   if (total == 0) return;
   if (lane == 0) L.carry_owner = kNoItem;
   uint32_t skip = kNoItem;
+  const int run = lane / 10, comp = lane - 10 * run;   // a component per lane
   for (uint32_t c0 = 0; c0 < total; c0 += 64) {
     const uint32_t n = min<uint32_t>(64u, total - c0);
     uint32_t o, lo;
@@ -549,34 +572,50 @@ __global__ void __launch_bounds__(256) row_reduce_kernel(const DeviceBatch* __re
       }
       if (earlier) skip = o0;
     }
+    reduce_fence();
     const uint32_t co = L.carry_owner;
-    double g[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) g[k] = (lane == 0 && co != kNoItem) ? L.carry[k] : 0.0;
-    reduce_fence();
-    // a run left open by the previous 64 rows that does not go on here ended with them
-    if (lane == 0 && co != kNoItem && co != L.owner[0]) {
-      write_grad2d(db, co, g);
-#pragma unroll
-      for (int k = 0; k < 10; ++k) g[k] = 0.0;
-    }
+    // a run left open by the previous 64 rows goes on here, or ended with them
+    const bool goes_on = co != kNoItem && co == L.owner[0];
+    if (co != kNoItem && !goes_on && lane < 10) write_grad2d(db, co, lane, L.carry[lane]);
     const bool head = (uint32_t)lane < n && (lane == 0 || L.owner[lane - 1] != o);
-    bool open = false;
-    if (head) {
-      if (!(lane == 0 && co == o)) {
-#pragma unroll
-        for (int k = 0; k < 10; ++k) g[k] = 0.0;
-      }
-      uint32_t k = (uint32_t)lane;
-      if (o != skip)
-        for (; k < n && L.owner[k] == o; ++k) add_row(g, L.row[k]);
-      else
-        while (k < n && L.owner[k] == o) ++k;
-      open = k == n;
-    }
+    const uint64_t heads = __ballot(head);
+    const uint32_t nruns = (uint32_t)__builtin_popcountll(heads);
+    if (head)
+      L.start[__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u))] = lane;
+    if (lane == 0) L.start[nruns] = n;
     reduce_fence();
-    if (head) {
-      if (open) {
+    if (nruns <= (uint32_t)kReduceFew) {
+      for (uint32_t r0 = 0; r0 < nruns; r0 += kReduceRuns) {
+        const uint32_t r = r0 + (uint32_t)run;
+        if (run < kReduceRuns && r < nruns) {
+          const uint32_t k0 = L.start[r], k1 = L.start[r + 1], ow = L.owner[k0];
+          double g = r == 0 && goes_on ? L.carry[comp] : 0.0;
+          if (ow != skip) {
+#pragma unroll 4
+            for (uint32_t k = k0; k < k1; ++k) g += (double)L.row[k][comp];
+          }
+          if (k1 == n) {
+            L.carry[comp] = g;
+            if (comp == 0) L.carry_owner = ow == skip ? kNoItem : ow;
+          } else if (ow != skip) {
+            write_grad2d(db, ow, comp, g);
+          }
+        }
+      }
+    } else if (head) {
+      double g[10];
+#pragma unroll
+      for (int k = 0; k < 10; ++k) g[k] = lane == 0 && goes_on ? L.carry[k] : 0.0;
+      uint32_t k = (uint32_t)lane;
+      if (o != skip) {
+        for (; k < n && L.owner[k] == o; ++k) {
+#pragma unroll
+          for (int c = 0; c < 10; ++c) g[c] += (double)L.row[k][c];
+        }
+      } else {
+        while (k < n && L.owner[k] == o) ++k;
+      }
+      if (k == n) {
 #pragma unroll
         for (int c = 0; c < 10; ++c) L.carry[c] = g[c];
         L.carry_owner = o == skip ? kNoItem : o;
@@ -589,9 +628,7 @@ __global__ void __launch_bounds__(256) row_reduce_kernel(const DeviceBatch* __re
   // the last run: finished here, or continued through the rest of its splat's slots
   const uint32_t co = L.carry_owner;
   if (co == kNoItem) return;
-  double g[10];
-#pragma unroll
-  for (int k = 0; k < 10; ++k) g[k] = L.carry[k];
+  double g = lane < 10 ? L.carry[lane] : 0.0;
   uint64_t hi;
   {
     const int v = view_of_item(db, co);
@@ -599,7 +636,7 @@ __global__ void __launch_bounds__(256) row_reduce_kernel(const DeviceBatch* __re
     const int64_t i = (int64_t)co - db->item_prefix[v];
     hi = min<uint64_t>((uint64_t)V.slot_off[i] + V.item_cand[i], nslots);
   }
-  for (uint64_t q0 = w0 + kReduceWords; q0 * 32 < hi; q0 += kReduceWords) {
+  for (uint64_t q0 = w0 + WORDS; q0 * 32 < hi; q0 += WORDS) {
     reduce_fence();
     const uint32_t cnt = list_marks(bits, q0, nwords, hi, L, lane);
     for (uint32_t c0 = 0; c0 < cnt; c0 += 64) {
@@ -607,12 +644,14 @@ __global__ void __launch_bounds__(256) row_reduce_kernel(const DeviceBatch* __re
       uint32_t o, lo;
       load_rows(rows, L, c0, n, lane, o, lo);
       reduce_fence();
-      if (lane == 0)
-        for (uint32_t k = 0; k < n; ++k) add_row(g, L.row[k]);
+      if (lane < 10) {
+#pragma unroll 4
+        for (uint32_t k = 0; k < n; ++k) g += (double)L.row[k][lane];
+      }
       reduce_fence();
     }
   }
-  if (lane == 0) write_grad2d(db, co, g);
+  if (lane < 10) write_grad2d(db, co, lane, g);
 }
 
 hipError_t launch_row_reduce(const DeviceBatch* dbatch, const Batch& b, const float* rows, const uint32_t* bits,
@@ -620,9 +659,12 @@ hipError_t launch_row_reduce(const DeviceBatch* dbatch, const Batch& b, const fl
   (void)b;
   if (nslots == 0) return hipSuccess;
   const uint64_t nwords = (nslots + 31) / 32;
-  const uint64_t waves = (nwords + kReduceWords - 1) / kReduceWords;
-  hipLaunchKernelGGL(row_reduce_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, dbatch, rows, bits,
-                     nslots);
+  if (nslots > kReduceWide)
+    hipLaunchKernelGGL(row_reduce_kernel<32>, dim3((unsigned)((nwords + 127) / 128)), dim3(256), 0, stream, dbatch, rows,
+                       bits, nslots);
+  else
+    hipLaunchKernelGGL(row_reduce_kernel<8>, dim3((unsigned)((nwords + 31) / 32)), dim3(256), 0, stream, dbatch, rows,
+                       bits, nslots);
   return hipGetLastError();
 }
 
