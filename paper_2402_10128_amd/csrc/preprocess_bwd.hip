@@ -416,10 +416,8 @@ __device__ __forceinline__ void sum_views(const DeviceBatch* db, const AdamSplat
     const uint32_t vis = in ? V.vis[i] : 0u;
     const bool row_here = (vis & kVisBit) && (vis & kRowBit);
     double2* gp = reinterpret_cast<double2*>(V.grad2d + (int64_t)kGradStride * i);
-    if (in && !row_here && V.keep_grad2d) {   // inspection: rows nothing was added to read as zero
-#pragma unroll
-      for (int k = 0; k < ((vis & kVisBit) ? 5 : kGradStride / 2); ++k) gp[k] = make_double2(0.0, 0.0);
-    }
+    if (in && V.keep_grad2d)   // inspection: rows nothing was added to, and the slots past the tenth, read as zero
+      for (int k = row_here ? 5 : 0; k < kGradStride / 2; ++k) gp[k] = make_double2(0.0, 0.0);
     if (A.stat_accum && (vis & kVisBit)) {   // densification statistic: the mean-2D gradient in NDC units
       if (row_here) {
         const double2 g01 = gp[0];
