@@ -88,9 +88,10 @@ __device__ __forceinline__ int64_t ordered_tile(int64_t blk, const uint32_t* gro
 //     barrier per batch).
 // The arithmetic of a pair, and the order of a pixel's pairs, do not depend on any of this.  Measured against two
 // waves per tile with two pixels per lane, walking every splat: 1k splats at 64x64 102 -> 36 us, 200k at 512x512
-// 363 -> 133, GEF 300k at 801x533 443 -> 329, 1M at 1600x1040 233 -> 189, 3M at 1920x1080 243 -> 229, 5M of heavy
-// overlap 828 -> 666.  Groups of 2: 41, 139, 349, 185, 228, 659 us; one splat at a time with a branch per
-// decision: 51, 169, 478, 251, 304, 905.
+// 363 -> 130, GEF 300k at 801x533 443 -> 304, 1M at 1600x1040 233 -> 188, 3M at 1920x1080 243 -> 221, 5M of heavy
+// overlap 828 -> 642.  Other group sizes (with the next records still waited for at their loads: 36, 133, 329, 189, 229,
+// 666 us): 2 everywhere 41, 139, 349, 185, 228, 659; one splat at a time with a branch per decision 51, 169, 478,
+// 251, 304, 905.
 constexpr int kFwdWaves = 4;
 constexpr int kFwdBatch = 128;              // records staged per barrier: threads 0-127 load words 0-7 of
                                             // one record each, threads 128-255 words 8-11
@@ -176,6 +177,7 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
   // staging: this thread's record of a batch, and which part of it
   const int sj = threadIdx.x & (kFwdBatch - 1);
   const bool part0 = w < kFwdWaves / 2;
+  const int first_word = part0 ? 0 : 2;
   uint32_t id = 0;
   Vec4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
   auto load_id = [&](int base) {
@@ -183,12 +185,10 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
   };
   auto load_rec = [&](int base) {
     if (base + sj < n) {
-      if (part0) {
-        r0 = rec[4 * (size_t)id];
-        r1 = rec[4 * (size_t)id + 1];
-      } else {
-        r0 = rec[4 * (size_t)id + 2];
-      }
+      // without a branch on the part: assigned in both of its arms, the words went through scratch memory, and their
+      // loads were waited for on the spot (3M splats at 1920x1080: 105 MB more written, forward 234 -> 221 us; GEF 300k at 801x533 332 -> 304)
+      r0 = rec[4 * (size_t)id + first_word];
+      r1 = rec[4 * (size_t)id + (part0 ? 1 : 2)];
     }
   };
   auto store_rec = [&](int buf) {
@@ -457,6 +457,7 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
   const uint2* list = sorted_pairs + V.ranges[lt].x;
   const int sj = threadIdx.x & (kFwdBatch - 1);
   const bool part0 = w < kFwdWaves / 2;
+  const int first_word = part0 ? 0 : 2;
   uint32_t id = 0;
   Vec4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
   auto load_id = [&](int base) {
@@ -464,12 +465,8 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
   };
   auto load_rec = [&](int base) {
     if (base >= 0 && base + sj < n) {
-      if (part0) {
-        r0 = rec[4 * (size_t)id];
-        r1 = rec[4 * (size_t)id + 1];
-      } else {
-        r0 = rec[4 * (size_t)id + 2];
-      }
+      r0 = rec[4 * (size_t)id + first_word];   // no branch on the part (see the forward)
+      r1 = rec[4 * (size_t)id + (part0 ? 1 : 2)];
     }
   };
   auto store_rec = [&](int buf) {
