@@ -95,14 +95,15 @@ def algorithmic_bytes(stage, n, sh_coeffs, K, C, L, px, R=0):
         # the slot marks (1 bit per slot) and every stored row's 10 sums and splat (44 B); the 2-D gradients
         # written (80 B per splat with a row, at most R) are left out, so this is a lower bound
         "row_reduce": C // 8 + 44 * R,
-        "preprocess_backward": n * (16 + 12 + 16 + 4 + 12 * sh_coeffs + 48 + 80 + 4 * (3 + 3 + 4 + 1 + 1 + 3 * sh_coeffs)),
+        # per splat its visibility word in and its gradients out; per listed splat its parameters and its 2-D gradient
+        # in (a splat without a row needs neither, so this is an upper bound of the reads)
+        "preprocess_backward": n * (4 + splat_in) + L * (splat_in + 80),
         # the row marks cleared before the backward raster
         "zero": C // 8,
         "loss": 37 * px,
-        # the preprocess backward with Adam fused in: its inputs as above, no gradient stores, and per
-        # parameter the two moments read (8 B) and the parameter and both moments written (12 B)
-        "preprocess_backward_adam": n * (16 + 12 + 16 + 4 + 12 * sh_coeffs + 48 + 80
-                                         + 20 * (3 + 3 + 4 + 1 + 1 + 3 * sh_coeffs)),
+        # the preprocess backward with Adam fused in: its inputs, and per parameter the value and both moments in (12 B)
+        # and out (12 B)
+        "preprocess_backward_adam": n * (4 + 6 * splat_in) + L * 80,
         # per parameter: read p, g, m, v and write p, m, v (binary32)
         "adam": 28 * n * (3 + 3 + 4 + 1 + 1 + 3 * sh_coeffs),
         # per pixel: forward reads img, target (24 B) and writes 9 maps (36 B); backward reads the maps (36 B),
@@ -159,7 +160,7 @@ def kernel_source_hash(stage):
     src = {"raster_forward": "raster.hip", "raster_backward": "raster.hip", "preprocess": "preprocess.hip",
            "preprocess_backward": "preprocess_bwd.hip", "tile_sort": "radix.hip", "depth_sort": "radix.hip",
            "duplicate": "binning.hip", "key_scan": "binning.hip", "row_reduce": "binning.hip", "loss": "loss.hip",
-           "zero": "loss.hip"}[stage]
+           "zero": "raster.hip"}[stage]
     # the kernel's source file and the shared headers it is built with (layouts and constants live there)
     csrc = os.path.join(HERE, "paper_2402_10128_amd", "csrc")
     h = hashlib.sha256()

@@ -443,14 +443,15 @@ hipError_t launch_duplicate(DeviceBatch* dbatch, const Batch& b, hipStream_t str
 // walks end where their pixels saturate), added in binary64 in slot order -- the same order on every run,
 // so the backward is deterministic.  A wave takes 8 or 32 words of the row marks (32 slots each): it lists their marked
 // slots in LDS, loads 64 rows at a time (one per lane; a row carries its splat's batch item and first
-// candidate slot) and each run of one splat's rows is added from LDS, carrying an
-// unfinished run into the next 64 and, past the wave's words, through the rest of the splat's slot range.
+// candidate slot) and each run of one splat's rows is added from LDS, carrying an unfinished run into the next 64
+// and, past the wave's words, through the rest of the splat's slot range.
 // The run at the start of the range belongs to the wave holding the splat's first row if that lies before
 // the range.  The splat's 2-D gradient is written and kRowBit set in its visibility word (the preprocess
 // backward takes zero without it).
 //
-// What bounds it is the latency of a wave's steps and, of those, the sums.  A chunk of 64 rows with many runs (splats of one or two rows) is added a run per lane; one with few runs a component
-// per lane, 6 runs of 10 at a time, or the few lanes with a run would add ten numbers per row, one row after the other.
+// What bounds it is the latency of a wave's steps and, of those, the sums.  A chunk of 64 rows with many runs (splats
+// of one or two rows) is added a run per lane; one with few runs a component per lane, 6 runs of 10 at a time, or
+// the few lanes with a run would add ten numbers per row, one row after the other.
 // Both add in the same order.  A run per lane for every chunk, and 8 words per wave for every frame, took 587 us for
 // 169M slots, 215 for 5M of large splats, 102 for 13.5M and 77 for 3.9M; now 251, 59, 65 and 42.
 constexpr uint32_t kNoItem = 0xffffffffu;

@@ -48,8 +48,8 @@ static void mask_weights(MaskWeights& mw, float s1, float s2) {
 
 // The mask is three launches (four where it has more than kMaxInline tiles), each a few microseconds of latency more than
 // of work: a kernel asks for all it reads at once, stages it in LDS and walks the up to 129 taps there.  1080p, omega
-// 0.75: 41 -> 21 us; 512 x 512: 29 -> 17.  The four kernels before took the taps from memory, 8 in flight, and the maximum by 648 atomics on
-// one address.  Every sum runs in the order of the pixels or taps.
+// 0.75: 41 -> 21 us; 512 x 512: 29 -> 17.  The four kernels before took the taps from memory, 8 in flight, and the
+// maximum by 648 atomics on one address.  Every sum runs in the order of the pixels or taps.
 constexpr int kRowThreads = 1024;
 constexpr int kRowSegment = 1024;                          // low pixels of a row per block: images up to 5,120 wide in one
 constexpr int kRowChunk = 512;                             // low pixels averaged at a time
