@@ -280,6 +280,7 @@ struct RadixSort {
   unsigned long long* weight_sums;   // [nblocks]
   unsigned long long* mail;
   uint32_t token;
+  uint32_t* weight_total;        // NULL, or receives their sum too (at most 2^32 - 1)
 };
 struct RadixPass {
   int32_t bits, shift, filter;
@@ -299,6 +300,7 @@ struct RadixPass {
   unsigned long long* weight_sums;
   unsigned long long* mail;
   uint32_t token;
+  uint32_t* weight_total;
 };
 hipError_t launch_radix_sort(const RadixSort& s, hipStream_t stream);
 // Blocks that the smallest tile takes for n items: what the digit table is sized by.

@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(kRadixThreads) radix_upsweep_kernel(RadixPass 
   if (threadIdx.x == 0) p.weight_sums[blockIdx.x] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
 }
 
-// The blocks' weight sums added up and posted, by one block.
+// The blocks' weight sums added up and handed out, by one block.
 __device__ __forceinline__ void post_weights(const RadixPass& p) {
   __shared__ unsigned long long part[kScanThreads / 64];
   unsigned long long s = 0;
@@ -112,7 +112,8 @@ __device__ __forceinline__ void post_weights(const RadixPass& p) {
   __syncthreads();
   if (threadIdx.x == 0) {
     for (uint32_t k = 1; k < blockDim.x / 64; ++k) s += part[k];
-    post_count(p.mail, p.token, s);
+    if (p.mail) post_count(p.mail, p.token, s);
+    if (p.weight_total) *p.weight_total = s > 0xffffffffull ? 0xffffffffu : (uint32_t)s;
   }
 }
 
@@ -209,7 +210,7 @@ __global__ void __launch_bounds__(THREADS) radix_downsweep_kernel(RadixPass p) {
   const int lane = threadIdx.x & 63, t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   if (block != 0 && (uint64_t)block * p.span >= n) return;   // whole block
-  if (block == 0 && p.weights && p.mail && radix_own_scan(p)) post_weights(p);   // otherwise the scan has
+  if (block == 0 && p.weights && (p.mail || p.weight_total) && radix_own_scan(p)) post_weights(p);   // otherwise the scan has
   // the global start of the block's run of each digit: the digit's items in the whole input and in the blocks before
   uint32_t gtot = 0, before_me = 0, g = 0;
   const bool digits = THREADS == 256 || t < 256;   // the threads that have a digit: whole waves
@@ -359,12 +360,13 @@ hipError_t launch_radix_sort(const RadixSort& s, hipStream_t stream) {
     p.weight_sums = s.weight_sums;
     p.mail = s.mail;
     p.token = s.token;
+    p.weight_total = k == 0 ? s.weight_total : nullptr;
     const dim3 grid(s.nblocks);
     hipLaunchKernelGGL(radix_upsweep_kernel, grid, dim3(kRadixThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!radix_own_scan(p)) {
-      hipLaunchKernelGGL(radix_scan_kernel, dim3(p.weights && p.mail ? 257 : 256), dim3(kScanThreads), 0, stream, p);
+      hipLaunchKernelGGL(radix_scan_kernel, dim3(p.weights && (p.mail || p.weight_total) ? 257 : 256), dim3(kScanThreads), 0, stream, p);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -1,4 +1,5 @@
-"""The binning's radix passes by the size of their blocks: up to 2^21 items, beyond, and beyond 2^26 (items and slots).
+"""The binning's radix passes by the size of their blocks: up to 2^21 items, beyond, and beyond 2^26 (items and slots);
+and its chunk offsets, added up by the duplication up to 2^19 items and scanned beyond.
 
 The order is checked on the device, where the sorted lists are: pairs ascend by tile and, within a tile, by candidate
 slot (the passes are stable and slots follow the depth order); every slot occurs once; along the slots the
@@ -13,8 +14,9 @@ from paper_2402_10128_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,log_scale", [(2**21, -9.0), (2**21 + 1, -9.0), (400_000, -2.45), (2**26 + 1, -12.0)],
-                         ids=["2M", "2M+1", "slots>64M", "64M+1"])
+@pytest.mark.parametrize("n,log_scale", [(2**19, -9.0), (2**19 + 1, -9.0), (2**21, -9.0), (2**21 + 1, -9.0),
+                                         (400_000, -2.45), (2**26 + 1, -12.0)],
+                         ids=["512k", "512k+1", "2M", "2M+1", "slots>64M", "64M+1"])
 def test_lists_of_large_scenes(n, log_scale):
     print(f"[large sort] n={n}", flush=True)
     dev = torch.device("cuda:0")
