@@ -647,6 +647,10 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
     // wave max of the last contributor position per band of 4 rows and over the tile, made scalars: the walk's
     // loop control (positions, the parked-splat count, the flush test) then runs on the scalar unit instead of
     // taking VALU issue slots, and a band skips the splats behind all of its pixels' last ones
+    // the logarithm of q's floor by the instruction that takes the others
+    float q_floor = 1e-12f;
+    asm volatile("" : "+v"(q_floor));
+    const float lq_floor = FALLOFF == GES_FALLOFF_GEF ? fast_log2(q_floor) : 0.f;
     uint32_t band_last[4];
   #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -772,8 +776,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
           } else {
             // dG/dq = -(beta/4) q^(beta/2 - 1) G  (q floored at 1e-12): k = -beta/4;
             // dG/dbeta = -(1/4) q^(beta/2) ln q G: the row sum of q^(beta/2) log2 q gd takes -(ln 2)/4 o
-            const float qf = __int_as_float(max(__float_as_int(q), __float_as_int(1e-12f)));   // q >= +0
-            const float qpow = fast_exp2((0.5f * B.w - 1.f) * fast_log2(qf));
+            const float qpow = fast_exp2((0.5f * B.w - 1.f) * (q >= 1e-12f ? lq : lq_floor));   // q >= +0
             dq = q0 >= 0.f ? qpow * gd : 0.f;
             pbeta = __builtin_fmaf(q > 0.f ? qb * lq : 0.f, gd, pbeta);
           }
