@@ -527,7 +527,8 @@ ges_status ges_serve_create(const ges_serve_config* cfg, void* pool, size_t pool
 /* Host-only variant for testing the scheduler without a GPU: the executor never touches device
  * memory; every view of a batch produces keys_per_view keys, a batch takes batch_ns + per_view_ns
  * per view, and batches holding a request for scene fail_scene fail with GES_ERR_DEVICE.  The pool
- * of pool_bytes is accounted but never dereferenced. */
+ * of pool_bytes is accounted but never dereferenced; a batch that is given a region of it while the
+ * other stream's batch still works there fails with GES_ERR_INTERNAL. */
 ges_status ges_serve_create_simulated(const ges_serve_config* cfg, size_t pool_bytes, uint64_t keys_per_view,
                                       uint64_t batch_ns, uint64_t per_view_ns, int32_t fail_scene,
                                       ges_server** out);

@@ -106,6 +106,8 @@ struct Request {
 struct BatchWork {
   std::vector<uint64_t> ids;
   std::vector<FramePlan> plans;
+  std::vector<int32_t> scenes;               // per view
+  std::vector<std::pair<size_t, size_t>> regions;   // per view: offset and bytes of its workspace
   size_t table_off = 0, table_bytes = 0;     // device view table, then the batch's binning buffers
   int64_t items = 0;                         // splats of the batch's views
   size_t key_off = 0, key_bytes = 0;
@@ -125,12 +127,15 @@ int64_t batch_tiles(const BatchWork& b) { return b.host ? b.host->tile_prefix[b.
 // ---- executors: the GPU one, and a simulated one for host-only tests of the scheduler ------------
 struct Executor {
   virtual ~Executor() = default;
-  // Enqueue preprocess + histogram + scan for every view; return the batch key count (waits).
+  // Enqueue preprocess + depth sort + key scan for every view; return the batch key count (waits for the count, not
+  // for the sort and the scan, which go on in the batch's regions of the pool).
   virtual ges_status count(BatchWork& b, char* pool, std::string& err) = 0;
   // Enqueue scatter + sort + raster and a completion marker.
   virtual ges_status render(BatchWork& b, char* pool, std::string& err) = 0;
   virtual bool done(BatchWork& b) = 0;
   virtual void wait(BatchWork& b) = 0;
+  // Wait for everything enqueued on the batch's stream: before the regions of a batch that will not render are released.
+  virtual void drain(BatchWork& b) = 0;
   virtual void release(BatchWork& b) = 0;
 };
 
@@ -204,7 +209,10 @@ class GpuExecutor : public Executor {
   }
   ~GpuExecutor() override {
     for (auto s : streams_)
-      if (s) (void)hipStreamDestroy(s);
+      if (s) {
+        (void)hipStreamSynchronize(s);   // the caller frees the pool next
+        (void)hipStreamDestroy(s);
+      }
   }
   bool ok() const { return streams_[0] && streams_[1]; }
 
@@ -255,6 +263,7 @@ class GpuExecutor : public Executor {
   void wait(BatchWork& b) override {
     if (b.done) (void)hipEventSynchronize(b.done);
   }
+  void drain(BatchWork& b) override { (void)hipStreamSynchronize(streams_[b.stream]); }
   void release(BatchWork& b) override {
     if (b.done) (void)hipEventDestroy(b.done);
     b.done = nullptr;
@@ -287,20 +296,24 @@ class GpuExecutor : public Executor {
 
 // Host-only executor: key count = the sum over views of `keys_per_view`, a batch takes
 // `batch_ns` plus `per_view_ns` per view; scenes whose id is `fail_scene` fail at count time.
+// As on the device, a count returns before its stream is done: the batch's regions stay in use for `batch_ns` more, and a
+// batch of the other stream that is given a part of them fails.
 class SimExecutor : public Executor {
  public:
-  SimExecutor(uint64_t keys_per_view, uint64_t batch_ns, uint64_t per_view_ns, int32_t fail_scene,
-              const std::vector<ges_splats>* scenes, std::unordered_map<uint64_t, Request>* reqs)
-      : kpv_(keys_per_view), bns_(batch_ns), vns_(per_view_ns), fail_(fail_scene), reqs_(reqs) {
-    (void)scenes;
-  }
+  SimExecutor(uint64_t keys_per_view, uint64_t batch_ns, uint64_t per_view_ns, int32_t fail_scene)
+      : kpv_(keys_per_view), bns_(batch_ns), vns_(per_view_ns), fail_(fail_scene) {}
   ges_status count(BatchWork& b, char*, std::string& err) override {
-    for (uint64_t id : b.ids)
-      if (reqs_->at(id).scene == fail_) { err = "simulated executor failure"; return GES_ERR_DEVICE; }
+    drain(b);   // the count arrives once the stream's earlier work has run
+    for (const auto& r : b.regions)
+      if (!take(r.first, r.second, b.stream, err)) return GES_ERR_INTERNAL;
+    if (!take(b.table_off, b.table_bytes, b.stream, err)) return GES_ERR_INTERNAL;
+    for (int32_t scene : b.scenes)
+      if (scene == fail_) { err = "simulated executor failure"; return GES_ERR_DEVICE; }
     b.keys = kpv_ * b.ids.size();
     return GES_OK;
   }
-  ges_status render(BatchWork& b, char*, std::string&) override {
+  ges_status render(BatchWork& b, char*, std::string& err) override {
+    if (b.has_keys && !take(b.key_off, b.key_bytes, b.stream, err)) return GES_ERR_INTERNAL;
     b.sim_done_ns = now_ns() + bns_ + vns_ * b.ids.size();
     return GES_OK;
   }
@@ -308,12 +321,32 @@ class SimExecutor : public Executor {
   void wait(BatchWork& b) override {
     while (!done(b)) std::this_thread::sleep_for(std::chrono::microseconds(50));
   }
+  void drain(BatchWork& b) override {
+    for (const Use& u : uses_)
+      while (u.stream == b.stream && now_ns() < u.until_ns) std::this_thread::sleep_for(std::chrono::microseconds(50));
+  }
   void release(BatchWork&) override {}
 
  private:
+  struct Use {
+    size_t off, bytes;
+    int stream;
+    uint64_t until_ns;
+  };
+  bool take(size_t off, size_t bytes, int stream, std::string& err) {
+    const uint64_t now = now_ns();
+    uses_.erase(std::remove_if(uses_.begin(), uses_.end(), [&](const Use& u) { return now >= u.until_ns; }), uses_.end());
+    for (const Use& u : uses_)
+      if (u.stream != stream && off < u.off + u.bytes && u.off < off + bytes) {
+        err = "a region of the pool was handed out while the other stream worked in it";
+        return false;
+      }
+    uses_.push_back({off, bytes, stream, now + bns_});
+    return true;
+  }
   uint64_t kpv_, bns_, vns_;
   int32_t fail_;
-  std::unordered_map<uint64_t, Request>* reqs_;
+  std::vector<Use> uses_;   // by the worker thread only
 };
 
 void finish_request(ges_server* s, Request& r, int32_t state, int32_t status) {
@@ -348,6 +381,19 @@ void retire(ges_server* s, std::unique_lock<std::mutex>& lk, bool wait_oldest) {
   if (any) s->cv_done.notify_all();
 }
 
+// Ends a batch that does not render (lock held): its stream may still be working in its regions, so they are released
+// once it is done.
+void fail_batch(ges_server* s, std::unique_lock<std::mutex>& lk, BatchWork& b, ges_status st) {
+  lk.unlock();
+  s->exec->drain(b);
+  lk.lock();
+  for (uint64_t id : b.ids) finish_request(s, s->reqs.at(id), GES_REQ_FAILED, st);
+  if (b.has_keys) s->alloc->release(b.key_off, b.key_bytes);
+  s->alloc->release(b.table_off, b.table_bytes);
+  s->exec->release(b);
+  s->cv_done.notify_all();
+}
+
 void build_views(ges_server* s, BatchWork& b) {
   b.host.reset(new DeviceBatch());
   DeviceBatch& h = *b.host;
@@ -355,6 +401,8 @@ void build_views(ges_server* s, BatchWork& b) {
   h.nviews = (int32_t)b.ids.size();
   b.plans.clear();
   b.inspect.clear();
+  b.scenes.clear();
+  b.regions.clear();
   int64_t pre = 0, items = 0, tiles = 0;
   b.items = 0;
   for (uint64_t id : b.ids) b.items += s->scenes[(size_t)s->reqs.at(id).scene].n;
@@ -364,6 +412,8 @@ void build_views(ges_server* s, BatchWork& b) {
     const ges_splats& sc = s->scenes[(size_t)r.scene];
     const FramePlan fp = plan_frame(sc.n, r.cam.width, r.cam.height);
     b.plans.push_back(fp);
+    b.scenes.push_back(r.scene);
+    b.regions.emplace_back(r.ws_off, r.ws_bytes);
     ViewDesc& V = h.views[v];
     fill_view(V, &sc, &r.cam, &s->params);
     attach_view(V, fp, s->pool + r.ws_off);
@@ -452,9 +502,7 @@ void worker_loop(ges_server* s) {
     ges_status st = s->exec->count(b, s->pool, err);
     lk.lock();
     if (st != GES_OK) {
-      for (uint64_t id : b.ids) finish_request(s, s->reqs.at(id), GES_REQ_FAILED, st);
-      s->alloc->release(b.table_off, b.table_bytes);
-      s->cv_done.notify_all();
+      fail_batch(s, lk, b, st);
       continue;
     }
     // ---- 3. key buffer under the budget: wait for older batches, then give back the newest views
@@ -469,7 +517,8 @@ void worker_loop(ges_server* s) {
       }
       if (!s->inflight.empty()) { retire(s, lk, true); continue; }
       if (b.ids.size() > 1) {
-        // hand the newest view back to the head of the queue and recount the rest
+        // hand the newest view back to the head of the queue and recount the rest: on the same stream, so the recount
+        // arrives after the first count's work in that view's region
         const uint64_t id = b.ids.back();
         b.ids.pop_back();
         Request& r = s->reqs.at(id);
@@ -488,9 +537,7 @@ void worker_loop(ges_server* s) {
       break;
     }
     if (!placed) {
-      for (uint64_t id : b.ids) finish_request(s, s->reqs.at(id), GES_REQ_FAILED, st);
-      s->alloc->release(b.table_off, b.table_bytes);
-      s->cv_done.notify_all();
+      fail_batch(s, lk, b, st);
       continue;
     }
     // ---- 4. render, record completion, keep going
@@ -502,12 +549,7 @@ void worker_loop(ges_server* s) {
     st = s->exec->render(b, s->pool, err);
     lk.lock();
     if (st != GES_OK) {
-      s->exec->wait(b);
-      for (uint64_t id : b.ids) finish_request(s, s->reqs.at(id), GES_REQ_FAILED, st);
-      if (b.has_keys) s->alloc->release(b.key_off, b.key_bytes);
-      s->alloc->release(b.table_off, b.table_bytes);
-      s->exec->release(b);
-      s->cv_done.notify_all();
+      fail_batch(s, lk, b, st);
       continue;
     }
     // per-view key counts are known on the device; record the batch total for every request
@@ -554,7 +596,7 @@ ges_status ges_serve_create_simulated(const ges_serve_config* cfg, size_t pool_b
                                       uint64_t batch_ns, uint64_t per_view_ns, int32_t fail_scene, ges_server** out) {
   if (!out || pool_bytes == 0 || ges::validate_config(cfg) != GES_OK) return GES_ERR_INVALID_ARGUMENT;
   std::unique_ptr<ges_server> s(new ges_server());
-  s->exec.reset(new ges::SimExecutor(keys_per_view, batch_ns, per_view_ns, fail_scene, &s->scenes, &s->reqs));
+  s->exec.reset(new ges::SimExecutor(keys_per_view, batch_ns, per_view_ns, fail_scene));
   // the simulated pool is never dereferenced: only offsets are handed out
   ges::start(s.get(), cfg, reinterpret_cast<void*>(uintptr_t(1) << 40), pool_bytes);
   *out = s.release();

@@ -114,6 +114,36 @@ def test_alone_equals_mixed_equals_plain_render():
         assert torch.equal(img, out)
 
 
+@pytest.mark.parametrize("slots", [1, 8])
+def test_requests_behind_one_whose_keys_do_not_fit(slots):
+    """A pool with room for a large request's workspace but not for its keys: that request fails with OUT_OF_MEMORY
+    while its sort may still be running, and the images of the requests queued behind it, which get the same bytes of the pool
+    on the other stream, are those of the plain render bit for bit."""
+    n = 1_000_000
+    large = synth.scene_clusters(n, 520).arrays()
+    large["log_scales"] += np.float32(1.5)
+    large, small = to_device(large), _scenes([2_000])[0]
+    cam = synth.orbit_camera(np.random.default_rng(5), 1280, 720)
+    cams = [synth.orbit_camera(np.random.default_rng(6 + i), 256, 256) for i in range(6)]
+    pool = G.ges_workspace_query(n, 1280, 720)[0] + (16 << 20)
+    outs = [torch.zeros((256, 256, 3), device="cuda") for _ in cams]
+    big = torch.zeros((720, 1280, 3), device="cuda")
+    want = [G.render(small, c, tile_cull=G.TILES_ELLIPSE)[0] for c in cams]
+    torch.cuda.synchronize()
+    with Server(pool, max_slots=slots) as s:
+        a, b = s.add_scene(large), s.add_scene(small)
+        for _ in range(3):
+            first = s.submit(a, cam, big)
+            rids = [s.submit(b, c, o) for c, o in zip(cams, outs)]
+            s.drain()
+            info = s.poll(first)
+            assert info["state"] == "FAILED" and info["status"] == 3, info
+            assert all(s.poll(r)["state"] == "DONE" for r in rids)
+            for o, w in zip(outs, want):
+                assert torch.equal(o, w)
+                o.zero_()
+
+
 def test_batched_beats_sequential_throughput_and_p99():
     scenes = _scenes([200_000, 500_000, 1_000_000])
     reqs = _requests(48, len(scenes), seed=2100)

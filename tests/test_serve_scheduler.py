@@ -171,3 +171,20 @@ def test_inspection_submit_validates_its_buffer():
         rid = s.submit(sid, CAM, 1)
         s.drain()
         assert s.poll(rid)["state"] == "DONE"
+
+
+@pytest.mark.parametrize("slots,simulated,status", [
+    (1, dict(keys_per_view=4_000_000), 3), (8, dict(keys_per_view=4_000_000), 3), (1, dict(fail_scene=0), 4)],
+    ids=["keys", "keys-batched", "count"])
+def test_regions_of_a_batch_that_does_not_render_are_free_only_once_its_stream_is_done(slots, simulated, status):
+    """The count of a batch returns while its sort still works in the batch's regions.  A request whose keys do not fit
+    beside its workspace fails (OUT_OF_MEMORY), as does one whose count fails (DEVICE); the requests behind it get the
+    same regions on the other stream, and only once that work has ended: the simulated executor fails them otherwise."""
+    n = 400_000
+    pool = req_bytes(n, 256, 256) + (16 << 20)   # with 4M keys: about 100 MB for the large workspace, and as much for keys
+    with Server(pool, max_slots=slots, simulated=dict(simulated, batch_ns=30_000_000, per_view_ns=1000)) as s:
+        large, little = s.add_scene(dict(n=n)), s.add_scene(dict(n=1000))
+        ids = [s.submit(large, CAM, 1)] + [s.submit(little, CAM, 1) for _ in range(3)]
+        s.drain()
+        infos = [s.poll(i) for i in ids]
+    assert [(x["state"], x["status"]) for x in infos] == [("FAILED", status)] + 3 * [("DONE", 0)]
