@@ -139,10 +139,11 @@ ges_status ges_key_workspace_query(uint64_t num_keys, int64_t n, int32_t width, 
  * num_keys_host: if not NULL, the call waits for the number of candidate slots of this
  * frame and stores it there -- the key capacity the frame needs, an upper bound of its
  * (tile, splat) keys (equal to it for GES_TILES_SQUARE) -- the only host synchronisation
- * of a frame.  When it returns, everything enqueued on the stream before the call has
+ * of a frame.  When it returns OK, everything enqueued on the stream before the call has
  * run and the splats have been read; the depth sort may still be running in splat_ws.
  * Not available while the stream is being captured (DEVICE).
- * Errors: INVALID_ARGUMENT (see conventions), CAPACITY if splat_ws_bytes is too small. */
+ * Errors: INVALID_ARGUMENT (see conventions), CAPACITY if splat_ws_bytes is too small or,
+ * with num_keys_host, a step has more than 2^32-2 slots (nothing runs in splat_ws then). */
 ges_status ges_preprocess(const ges_splats* splats, const ges_camera* cam, const ges_raster_params* params,
                           void* splat_ws, size_t splat_ws_bytes, uint64_t* num_keys_host, void* stream);
 

@@ -269,7 +269,10 @@ ges_status preprocess_views(const ges_splats* splats, const ges_camera* cams, in
     uint32_t k = 0;
     GES_CHECK_HIP(ges::mail_wait(mail, b.keys_total, stream, &k), "read num_keys");
     ges::mail_give(mail);
-    if (k == 0xffffffffu) return fail(GES_ERR_CAPACITY, "more than 2^32-2 candidate (tile, splat) pairs in one step");
+    if (k == 0xffffffffu) {   // no render will follow: the caller may free the workspace, in which the sort still runs
+      GES_CHECK_HIP(hipStreamSynchronize(stream), "sync");
+      return fail(GES_ERR_CAPACITY, "more than 2^32-2 candidate (tile, splat) pairs in one step");
+    }
     *num_keys_host = k;
   }
   return GES_OK;
