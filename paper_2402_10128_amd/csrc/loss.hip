@@ -128,14 +128,15 @@ constexpr int kColThreads = kColTileX * kColTileY;
 constexpr int kColSpan = kColTileY + kMaxTaps - 1;         // rows a tile reads
 constexpr int kMaxInline = 512;                            // tile maxima that mask_up_kernel's waves take themselves
 
-// The largest of non-negative floats (or NaN, above all): they order like their bits.
+// The largest of non-negative floats: they order like their bits.
 __device__ __forceinline__ unsigned wave_max_bits(unsigned m) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off, 64));
   return m;
 }
 
-// Vertical pass, |DoG| and the tile's largest.
+// Vertical pass, |DoG| and the tile's largest, over the responses that are numbers: one NaN in the target would otherwise
+// take the mask of the whole image (its bits are above all).
 __global__ void __launch_bounds__(kColThreads) mask_cols_kernel(const MaskWeights mw, const float* __restrict__ h1,
                                                                 const float* __restrict__ h2, int wl, int hl,
                                                                 float* __restrict__ dog, unsigned* __restrict__ tile_max) {
@@ -175,7 +176,7 @@ __global__ void __launch_bounds__(kColThreads) mask_cols_kernel(const MaskWeight
     d = fabsf(a1 - a2);
     dog[(size_t)(y0 + ty) * wl + x] = d;
   }
-  const unsigned m = wave_max_bits(__float_as_uint(d));
+  const unsigned m = wave_max_bits(d == d ? __float_as_uint(d) : 0u);
   if ((t & 63) == 0) wmax[t >> 6] = m;
   __syncthreads();
   if (t == 0) {

@@ -50,3 +50,40 @@ def test_mask_tile_edges(H, W, offset):
         resp = OL.dog_response(tgt.astype(np.float64), omega if omega > 0.5 else omega + 0.5)
         near = (np.abs(resp - 0.5) < 1e-4)[np.arange(H)[:, None] // 5, np.arange(W)[None, :] // 5]
         assert np.array_equal(got[~near], ref[~near]), int((got != ref).sum())
+
+
+def _mask_over_numbers(tgt, omega):
+    """The mask's definition with the largest response taken over those that are numbers; a response that is none
+    is not above the threshold."""
+    low = OL.downsample(tgt.mean(axis=2))
+    om = omega if omega > 0.5 else omega + 0.5
+    s2 = 0.1 + 10.0 * om
+    with np.errstate(invalid="ignore", divide="ignore"):
+        resp = np.abs(OL.blur(low, 2.0 * s2) - OL.blur(low, s2))
+        m = resp[~np.isnan(resp)].max(initial=0.0)
+        resp = resp / m if m > OL.ZERO_RESPONSE else np.zeros_like(resp)
+        bit = (resp > 0.5).astype(np.uint8)
+    ys, xs = np.arange(tgt.shape[0])[:, None] // 5, np.arange(tgt.shape[1])[None, :] // 5
+    near = np.abs(resp - 0.5) < 1e-4
+    return (1 - bit if omega <= 0.5 else bit)[ys, xs], near[ys, xs]
+
+
+@pytest.mark.parametrize("H,W,patch", [(533, 801, p) for p in ("nan", "minus-nan", "inf", "nan-rows", "all-nan")] +
+                         [(5001, 1700, "nan")])
+def test_a_mask_with_values_that_are_not_numbers(H, W, patch):
+    """A response that is not a number (the pixels within a blur radius of one that is not) takes no part in the
+    largest; an infinite one does.  Both sizes: the largest taken by the last kernel's waves, and by a launch of its own."""
+    rng = np.random.default_rng(H)
+    yy, xx = np.mgrid[0:H, 0:W]
+    tgt = (0.5 + 0.4 * np.sin(xx / 19.0)[..., None] * np.cos(yy / 23.0)[..., None]
+           + 0.05 * rng.standard_normal((H, W, 3))).astype(np.float32)
+    where, value = {"nan": (np.s_[H // 2, W // 3, 1], np.nan), "minus-nan": (np.s_[H // 2, W // 3, 1], -np.nan),
+                    "inf": (np.s_[7, 5, 0], np.inf), "nan-rows": (np.s_[:40], np.nan),
+                    "all-nan": (np.s_[:], np.nan)}[patch]
+    tgt[where] = value
+    for omega in (0.75, 0.2):
+        ref, near = _mask_over_numbers(tgt.astype(np.float64), omega)
+        got = G.ges_freq_mask(torch.from_numpy(tgt).cuda(), omega).cpu().numpy()
+        assert np.array_equal(got[~near], ref[~near]), (omega, int((got != ref).sum()))
+        if patch in ("nan", "minus-nan", "nan-rows"):
+    XX
