@@ -417,7 +417,7 @@ enum : int { P_STARTS = 0, P_CUT = 9, P_SEG = 10 };
 // behind it: the recurrences of the backward pass, the same operations in the same order (so that cutting a walk
 // changes no bit of the gradients), without its sums.  Launch shape and walk as in the forward pass: a quadrant
 // per wave, only the splats that can reach it, kRecGroup at a time; a splat that a pixel does not take has alpha
-// 0, which leaves its transmittance and colour exactly as they are.
+// 0, which leaves its transmittance and colour exactly as they are (a colour that is not finite is taken as 0 there).
 constexpr int kRecGroup = 4;
 template <int FALLOFF>
 __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const DeviceBatch* __restrict__ db,
@@ -495,13 +495,16 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
         bound -= seg;
       }
       if (wlast <= lo) continue;   // the quadrant's pixels all stopped before these splats
-      bool hit = false;
+      bool hit = false, inf = false;
       if (lo + lane < wlast) {
         const Vec4 A = st[0][c0 + lane];
         const Vec4 B = st[1][c0 + lane];
+        const Vec4 Cl = st[2][c0 + lane];
+        inf = !(fabsf(Cl.x) + fabsf(Cl.y) + fabsf(Cl.z) < __builtin_inff());
         hit = box_may_hit(A.z, 0.5f * A.w, B.x, B.y, A.x - bx1, A.x - bx0, A.y - by1, A.y - by0);
       }
       uint64_t mask = __ballot(hit);
+      const bool odd = __ballot(inf) != 0ull;   // a colour that is not finite (or a sum of magnitudes that is not)
       while (mask) {
         // the next kRecGroup splats from the back (a short last group repeats its first, switched off)
         int js[kRecGroup];
@@ -521,12 +524,13 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
         }
         group_loaded(A, B);
         float alpha[kRecGroup], inv[kRecGroup];
+        uint64_t take[kRecGroup];
 #pragma unroll
         for (int e = 0; e < kRecGroup; ++e) {
           float dx, dy;
           const float q0 = pair_q(A[e].x, A[e].y, A[e].z, A[e].w, B[e].x, pxf, pyf, dx, dy);
-          const uint64_t take = lanes_le(q0, B[e].y) & have[e] &
-                                __builtin_amdgcn_uicmp((uint32_t)(lo + js[e]), last, 36);   // position < last
+          take[e] = lanes_le(q0, B[e].y) & have[e] &
+                    __builtin_amdgcn_uicmp((uint32_t)(lo + js[e]), last, 36);   // position < last
           const float q = clamp_q(q0);
           float G;
           if (FALLOFF == GES_FALLOFF_PHI) {
@@ -537,8 +541,13 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
           }
           const float oG = B[e].z * G;
           const float full = oG > kAlphaMax ? kAlphaMax : oG;
-          alpha[e] = __builtin_amdgcn_inverse_ballot_w64(take) ? full : 0.f;
-          inv[e] = __builtin_amdgcn_inverse_ballot_w64(take) ? fast_rcp(1.f - alpha[e]) : 1.f;
+          alpha[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? full : 0.f;
+          inv[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? fast_rcp(1.f - alpha[e]) : 1.f;
+        }
+        if (odd) {   // 0 times an infinite colour would not leave S as it is
+#pragma unroll
+          for (int e = 0; e < kRecGroup; ++e)
+            if (!__builtin_amdgcn_inverse_ballot_w64(take[e])) Cc[e] = Vec4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int e = 0; e < kRecGroup; ++e) {

@@ -69,3 +69,52 @@ def test_a_colour_that_is_not_finite_stays_on_its_pixels(odd):
     assert (~finite).any() and finite.any()
     assert np.array_equal(a["img"][finite], b["img"][finite])
     assert np.array_equal(a["n_contrib"], b["n_contrib"]) and np.array_equal(a["final_T"], b["final_T"])
+
+
+def test_gradients_around_a_colour_that_is_not_finite():
+    """Lists of several segments of the backward's walk, with one splat of infinite colour far back in them.  A splat
+    further front, in another segment of every list the two share, that takes no pixel the infinite one takes has the
+    gradients of the scene with an ordinary colour in its place."""
+    n = 1500
+    base, _ = _scene(n, 9, -3.0, -3.2)
+    eye = np.float32([-2.3, -2.3, -2.3])   # as above
+    cam = synth.pinhole(W, H, tuple(eye), fov_x_deg=40.0)
+    sh = np.zeros((n, 4, 3), np.float32)
+    sh[:, :1] = base["sh"]
+    plain = dict(base, sh=sh)
+    dL = np.random.default_rng(4).standard_normal((H, W, 3)).astype(np.float32)
+    a = gpu_render(plain, 1, cam, 0, O.TILES_SQUARE, dL=dL)
+    rec, tx = a["records"], (W + 15) // 16
+    lists = [list(a["sorted_ids"][r0:r1]) for r0, r1 in a["ranges"]]
+
+    def footprint(i, slack):
+        dx, dy = rec[i, 0] - np.arange(W)[None, :], rec[i, 1] - np.arange(H)[:, None]
+        return rec[i, 2] * dx * dx + 2 * rec[i, 3] * dx * dy + rec[i, 4] * dy * dy <= rec[i, 5] * slack
+
+    # the last splat of the longest list that a pixel composites, with a footprint of a few pixels
+    t = int(np.argmax([len(l) for l in lists]))
+    y0, x0 = 16 * (t // tx), 16 * (t % tx)
+    last = int(a["n_contrib"][y0:y0 + 16, x0:x0 + 16].max())
+    assert last > 3 * 64
+    odd = next(int(i) for i in reversed(lists[t][:last]) if 0 < footprint(i, 1.0)[y0:y0 + 16, x0:x0 + 16].sum() <= 60)
+    far = base["means"][odd] - eye
+    wild = dict(base, sh=sh.copy())
+    wild["sh"][odd, 0] = 3e38
+    for k, c in ((1, -far[1]), (2, far[2]), (3, -far[0])):
+        wild["sh"][odd, k] = np.sign(c) * np.float32(3.4e38)
+    b = gpu_render(wild, 1, cam, 0, O.TILES_SQUARE, dL=dL)
+    assert np.isinf(b["records"][odd, 8:11]).all()
+    pixels = ~np.isfinite(b["img"]).all(axis=2)
+    assert pixels.any()
+    checked = 0
+    for i in range(n):
+        shared = [l for l in lists if i in l and odd in l]
+        if i == odd or not shared or any(l.index(i) // 64 >= l.index(odd) // 64 for l in shared):
+            continue
+        if (footprint(i, 1.001) & pixels).any():
+            continue
+        for k in a["grads"]:
+            assert np.array_equal(a["grads"][k][i], b["grads"][k][i]), (i, k)
+        checked += 1
+    print(f"[colour] {checked} splats in front, {int(pixels.sum())} pixels take the infinite one", flush=True)
+    assert checked > 20
