@@ -18,11 +18,12 @@
 // A thread filters 8 neighbouring outputs at a time: across, from 20 staged values by five 16-byte reads, so that the
 // products x^2, y^2, xy are taken 18 times for 8 outputs; down, a column of 18 values.  Two statistics (one map) are
 // filtered at a time, which keeps a block to 48 KB (24 KB) of LDS.  What bounds the forward is VALU issue (110
-// multiply-adds per pixel and channel, 134 with the halo rows, about 200 instructions with the rest: 40 us at 1080p if every
+// multiply-adds per pixel and channel, 134 with the halo rows, about 230 instructions with the rest: 46 us at 1080p if every
 // SIMD issued each cycle); the backward, latency of memory and LDS (175 MB at 1080p, 34 us at a copy's rate).  At 1080p the
-// forward went from 60 us (32 x 32 tiles, a block's three channels in turn, staging indices divided out per value,
-// four IEEE divisions) to 54, the backward from 55 to 40, and the sum's own launch of 4.3 went away; at 512 x 512 it is
-// 16.4 -> 14.4 and 13.7 -> 10.7.  Filtering down first, straight from memory in registers, and the sum of the
+// forward went from 64 us (32 x 32 tiles, a block's three channels in turn, staging indices divided out per value)
+// to 58, the backward from 56 to 43, and the sum's own launch of 4.3 went away; at 512 x 512 it is
+// 16.5 -> 16.0 and 13.0 -> 11.4.  The four quotients are IEEE divisions: reciprocals and one remainder step without their
+// scaling took 56 us, and gave 0 where a denominator's reciprocal is subnormal.  Filtering down first, straight from memory in registers, and the sum of the
 // variances as one statistic takes 39 + 34 us, but rounds differently: through Adam's moments a training step's
 // result then moves by up to 1e-3.
 //
@@ -55,18 +56,6 @@ constexpr float kSsimShift = 0.5f;
 struct SsimWeights {
   float w[kSsimTaps];
 };
-
-// n / d by a reciprocal of d that is right to the last place: one step of the remainder rounds the quotient (to the nearest but
-// for quotients within 2^-23 of a last place of the middle), and the instruction that ends a division puts in its
-// values for zeros, infinities and NaN.  The two quotients by d2 share the reciprocal: 3 x 6 + 4 x 4 instructions for 4 x 15.
-__device__ __forceinline__ float ssim_reciprocal(float d) {
-  const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
-}
-__device__ __forceinline__ float ssim_divide(float n, float d, float r) {
-  const float q = n * r;
-  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, d, n), r, q), d, n);
-}
 
 // Workgroups are dealt to the 8 XCDs in turn (block b runs on XCD b mod 8), and each XCD has its own L2.
 // Block b takes tile (b mod 8) * per + b / 8, so every XCD walks one contiguous band of tile rows and the
@@ -208,14 +197,12 @@ __global__ void __launch_bounds__(kSsimThreads) ssim_fwd_kernel(const float* __r
     const float mx = ex + kSsimShift, my = ey + kSsimShift;
     const float n1 = 2.f * mx * my + kSsimC1, n2 = 2.f * cxy + kSsimC2;
     const float d1 = mx * mx + my * my + kSsimC1, d2 = vx + vy + kSsimC2;
-    const float r1 = ssim_reciprocal(d1), r2 = ssim_reciprocal(d2);
-    const float inv = ssim_divide(1.f, d1 * d2, ssim_reciprocal(d1 * d2));
+    const float inv = 1.f / (d1 * d2);
     const float s = n1 * n2 * inv;
     ssum += s;
     // derivatives with respect to the shifted statistics (the shift moves the mean term only)
-    const float dA = 2.f * my * n2 * inv - ssim_divide(2.f * mx * s, d1, r1) + ssim_divide(2.f * ex * s, d2, r2) -
-                     2.f * ey * n1 * inv;
-    const float dB = ssim_divide(-s, d2, r2);
+    const float dA = 2.f * my * n2 * inv - 2.f * mx * s / d1 + 2.f * ex * s / d2 - 2.f * ey * n1 * inv;
+    const float dB = -s / d2;
     const float dC = 2.f * n1 * inv;
     const size_t o = c * plane + (size_t)(gy0 + q) * w + gx;
     maps[o] = dA;

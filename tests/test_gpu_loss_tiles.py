@@ -87,3 +87,19 @@ def test_a_mask_with_values_that_are_not_numbers(H, W, patch):
         assert np.array_equal(got[~near], ref[~near]), (omega, int((got != ref).sum()))
         if patch in ("nan", "minus-nan", "nan-rows"):
             assert 0 < ref.sum() < ref.size   # the reference: a mask of its own away from them
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.2e9, 2.7e9])
+def test_ssim_of_large_values(scale):
+    """Checkerboards whose product of the two denominators, about 3.2 scale^4, lies just below the largest binary32
+    number: its reciprocal is subnormal there (a quotient by way of it, without scaling, is 0).  Tolerances as above."""
+    H, W = 40, 70
+    rng = np.random.default_rng(5)
+    board = (np.add(*np.mgrid[0:H, 0:W]) % 2 * 2 - 1)[..., None]
+    tgt = (scale * (1 + 0.9 * board + 0.01 * rng.standard_normal((H, W, 3)))).astype(np.float32)
+    img = (scale * (1 + 0.8 * board + 0.05 * rng.standard_normal((H, W, 3)))).astype(np.float32)
+    loss, dl = torch.zeros((), device="cuda:0"), torch.zeros((H, W, 3), device="cuda:0")
+    G.ges_ssim_loss(torch.from_numpy(img).cuda(), torch.from_numpy(tgt).cuda(), 0.2, loss, dl)
+    lref, gref = OS.ssim_loss_and_grad(img, tgt)
+    assert abs(float(loss) - 0.2 * lref) <= 2e-6 + 1e-6 * 0.2 * lref
+    assert np.abs(dl.cpu().numpy() - 0.2 * gref).max() <= 1e-4 * np.abs(0.2 * gref).max()
