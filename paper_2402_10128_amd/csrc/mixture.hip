@@ -21,7 +21,7 @@
 // Taking the constant factors out of the sums and the exponentials from the hardware's base-2 one takes 2.9 ms, no further
 // from binary64 -- but Adam's first steps are the sign of a gradient over its size, and where that is near zero other
 // roundings move a parameter by up to 6e-3 of its scale; so every term keeps its roundings, and only factors that
-// are powers of two are moved.
+// are powers of two are moved, to where they cost no bit of a subnormal result either.
 // A component that would read past the LDS arrays (n outside 1..128), an unknown model or target row, or
 // m outside 1..4096 is not run: its loss is set to NaN.
 #include <cmath>
@@ -98,13 +98,12 @@ __device__ __forceinline__ float mix_value(const MixComp& c, float x) {
   return E1;
 }
 
-// Adds r times the derivatives of a component by (w_raw, mu, s, beta); that by mu is left halved but for GEF:
-// powers of two change no rounding.
+// Adds r times the derivatives of a component by (w_raw, mu, s, beta) at x; but for GEF, x2 = 2 x.
 template <int MODEL>
-__device__ __forceinline__ void mix_grad(const MixComp& c, float x, float r, float (&acc)[4]) {
-  const float d = x - c.mu, d2 = d * d, s4 = 4.f * c.s;
+__device__ __forceinline__ void mix_grad(const MixComp& c, float x2, float r, float (&acc)[4]) {
   float base, db_mu, db_s;
   if (MODEL == GES_MIX_GEF) {
+    const float d = x2 - c.mu, s4 = 4.f * c.s;
     const float beta = c.beta_inv2_is2, ad = fabsf(d);
     const bool off = ad != 0.f;
     const float l = logf(ad);
@@ -116,25 +115,31 @@ __device__ __forceinline__ void mix_grad(const MixComp& c, float x, float r, flo
     db_s = base * a * s4 * c.inv1 * c.inv1;
     acc[3] = __builtin_fmaf(r, c.w * (-base * da_b * c.inv1), acc[3]);
   } else {
-    const float E1 = expf(-d2 * c.inv1);
+    // twice the distance, dd, and four times its square: the factors of two and four that the derivatives have come with
+    // them.  Powers of two change no rounding but below the normal numbers, where taking them here keeps a bit that a
+    // factor left for the sum would lose (d4 overflows from a distance of 9e18 on)
+    const float dd = x2 - 2.f * c.mu, d4 = dd * dd;
+    const float E1 = expf(-d4 * (0.25f * c.inv1));
     if (MODEL == GES_MIX_GMM) {
       base = E1;
-      db_mu = E1 * d * c.inv1;
-      db_s = E1 * d2 * s4 * c.inv1 * c.inv1;
+      db_mu = E1 * dd * c.inv1;
+      db_s = E1 * d4 * c.s * c.inv1 * c.inv1;
     } else if (MODEL == GES_MIX_DOG) {
-      const float inv2 = c.beta_inv2_is2, E2 = expf(-d2 * inv2);
+      const float inv2 = c.beta_inv2_is2, E2 = expf(-d4 * (0.25f * inv2));
       base = E1 - E2;
-      db_mu = E1 * d * c.inv1 - E2 * d * inv2;
-      db_s = E1 * d2 * s4 * c.inv1 * c.inv1 - E2 * d2 * (s4 / kMixNu) * inv2 * inv2;
+      db_mu = E1 * dd * c.inv1 - E2 * dd * inv2;
+      static_assert(kMixNu == 4.f, "the variance ratio is the factor of d4");
+      db_s = E1 * d4 * c.s * c.inv1 * c.inv1 - E2 * d4 * (c.s / kMixNu) * inv2 * inv2;
     } else {
-      const float is2 = c.beta_inv2_is2, P = 1.f - d2 * is2;
+      const float is2 = c.beta_inv2_is2, P = 1.f - d4 * (0.25f * is2);
       base = P * E1;
-      db_mu = d * is2 * E1 + base * d * c.inv1;
-      // 2 d2 is2 / s by the reciprocal: the remainder step rounds it, the last instruction of a division sees to zeros,
-      // infinities and NaN
-      const float n = 2.f * d2 * is2, q = n * c.rs;
+      db_mu = dd * is2 * E1 + base * dd * c.inv1;
+      // 2 d2 is2 / s by the reciprocal rounded to nearest: the remainder step rounds it as the division would (Markstein,
+      // 1990), the last instruction of a division sees to zeros, infinities and NaN.  No scaling: where s is so large or
+      // small that it would matter, is2 is 0 or infinite
+      const float n = d4 * (0.5f * is2), q = n * c.rs;
       const float over_s = __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, c.s, n), c.rs, q), c.s, n);
-      db_s = over_s * E1 + base * d2 * s4 * c.inv1 * c.inv1;
+      db_s = over_s * E1 + base * d4 * c.s * c.inv1 * c.inv1;
     }
   }
   acc[0] = __builtin_fmaf(r, c.dw * base, acc[0]);
@@ -241,7 +246,7 @@ __device__ __forceinline__ void mix_fit(const MixArgs& a, int p, int n, int posi
       for (int e = 0; e < kMixChunk; ++e) {
         const int j = c0 + e * 64 + lane, jc = min(j, M - 1);   // lanes past the end: the last point, with no weight
         r[e] = j < M ? sr[jc] : 0.f;
-        x[e] = a.x0 + (float)jc * a.dx;
+        x[e] = (MODEL == GES_MIX_GEF ? 1.f : 2.f) * (a.x0 + (float)jc * a.dx);
       }
     };
     const bool one = M <= 64 * kMixChunk;
@@ -257,7 +262,6 @@ __device__ __forceinline__ void mix_fit(const MixArgs& a, int p, int n, int posi
           mix_grad<MODEL>(c, x[e], r[e], acc);
         }
       }
-      if (MODEL != GES_MIX_GEF) acc[1] *= 2.f;
       const float sum = mix_sum_rows(acc);
       if ((lane & 15) == 0) L.gr[i][lane >> 4] = sum * scale;
     }
