@@ -43,3 +43,28 @@ def test_split_edges(m):
         g = g.astype(np.float32)   # a narrow component between two points: 1e-61 is 0 in the type of the result
         assert np.abs(grad[p, :n] - g).max() <= 1e-4 * np.abs(g).max(), (p, NAMES[model], n)
         assert abs(loss[p] - final) <= 1e-4 * final + 1e-9, (p, NAMES[model], n)
+
+
+@pytest.mark.parametrize("epochs", [256, 257, 513])
+def test_bias_corrections_beyond_one_table(epochs):
+    """The bias corrections come 256 steps at a time.  Fits whose gradients keep their sign over all epochs (a narrow
+    component beside a tall wide peak), so that every parameter but the powers moves by about the rate each step: corrections
+    late by one step from the second table on would leave 0.3 of the rate after 513, 513 roundings of parameters
+    below 4 up to 0.06 of it.  Tolerance 0.1 of it."""
+    m, lr = 200, 1e-3
+    x = np.linspace(-5.0, 5.0, m)
+    y = (50.0 * np.exp(-((x - 1.0) ** 2) / 8.0)).astype(np.float32)[None]
+    problems = np.array([[k, 1, 0, 0] for k in (0, 1, 3)], np.int32)   # gmm, dog, gef
+    par0 = np.zeros((3, 128, 4), np.float32)
+    par0[:, 0] = (1.0, -0.75, 0.9, 2.5)
+    dev, dx = torch.device("cuda:0"), float(np.float32(10.0 / (m - 1)))
+    par = torch.from_numpy(par0).to(dev)
+    G.ges_mix_fit(torch.from_numpy(problems).to(dev), torch.from_numpy(y).to(dev), -5.0, dx, par, epochs, lr)
+    par = par.cpu().numpy()
+    xs = -5.0 + dx * np.arange(m)
+    b1, b2, eps = (float(np.float32(v)) for v in (0.9, 0.999, 1e-8))
+    for p, kind in enumerate(("gmm", "dog", "gef")):
+        th, _, _ = MX.fit(kind, xs, y[0].astype(np.float64), par0[p, :1].astype(np.float64), False, epochs,
+                          float(np.float32(lr)), b1, b2, eps)
+        assert np.abs(th[0, :3] - par0[p, 0, :3]).min() > 0.5 * lr * epochs   # all of them have moved
+        assert np.abs(par[p, 0] - th[0]).max() <= 0.1 * lr, kind
