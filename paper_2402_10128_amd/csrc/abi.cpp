@@ -17,11 +17,12 @@
 namespace ges {
 namespace {
 // One page of host memory the device can write, for the slot counts of the calls under way; a call that finds no
-// free word reads its count from the device.  Kept for the life of the process (a kernel may be posting to it).
+// free word reads its count from the device.  Kept for the life of the process (a kernel may be posting to it).  A call
+// takes its word last, before the launch that posts to it: what fails before that costs none.
 constexpr int kMailSlots = 64;
 std::mutex g_mail_mu;
 unsigned long long* g_mail_page = nullptr;
-std::vector<int> g_mail_free;
+int g_mail_free[kMailSlots], g_mail_nfree = 0;
 uint32_t g_mail_token = 0;
 }  // namespace
 
@@ -36,11 +37,10 @@ CountMail mail_take() {
     }
     std::memset(p, 0, kMailSlots * 64);
     g_mail_page = static_cast<unsigned long long*>(p);
-    for (int k = 0; k < kMailSlots; ++k) g_mail_free.push_back(k);
+    for (int k = 0; k < kMailSlots; ++k) g_mail_free[g_mail_nfree++] = k;
   }
-  if (g_mail_free.empty()) return m;
-  m.slot = g_mail_page + 8 * g_mail_free.back();
-  g_mail_free.pop_back();
+  if (g_mail_nfree == 0) return m;
+  m.slot = g_mail_page + 8 * g_mail_free[--g_mail_nfree];
   if (++g_mail_token == 0) ++g_mail_token;   // 0 marks a word nobody posted to
   m.token = g_mail_token;
   return m;
@@ -50,7 +50,7 @@ CountMail mail_take() {
 void mail_give(const CountMail& m) {
   if (!m.slot) return;
   std::lock_guard<std::mutex> lk(g_mail_mu);
-  g_mail_free.push_back((int)((m.slot - g_mail_page) / 8));
+  g_mail_free[g_mail_nfree++] = (int)((m.slot - g_mail_page) / 8);
 }
 
 hipError_t mail_wait(const CountMail& m, const uint32_t* counter, hipStream_t stream, uint32_t* count) {
@@ -248,7 +248,6 @@ ges_status preprocess_views(const ges_splats* splats, const ges_camera* cams, in
   const ges::ViewsPlan vp = ges::plan_views(splats->n, nv, cams[0].width, cams[0].height);
   if (splat_ws_bytes < vp.splat_bytes) return fail(GES_ERR_CAPACITY, "splat workspace too small");
   hipStream_t stream = reinterpret_cast<hipStream_t>(stream_);
-  ges::CountMail mail;
   if (num_keys_host) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     GES_CHECK_HIP(hipStreamIsCapturing(stream, &capture), "capture status");
@@ -256,19 +255,18 @@ ges_status preprocess_views(const ges_splats* splats, const ges_camera* cams, in
       g_last_error = "the slot count cannot be read back while the stream is being captured";
       return GES_ERR_DEVICE;
     }
-    mail = ges::mail_take();
   }
   ges::Batch b = views_batch(splats, params, vp, splat_ws);
-  b.mail = mail;
   GES_CHECK_HIP(upload_views(splats, cams, nv, params, vp, splat_ws, nullptr, nullptr, nullptr, stream, b), "upload");
   ges::DeviceBatch* db = dev_batch(splat_ws, vp.fp);
   GES_CHECK_HIP(timed(GES_STAGE_PREPROCESS, stream, [&] { return ges::launch_preprocess(db, b, stream); }), "preprocess");
+  if (num_keys_host) b.mail = ges::mail_take();
   GES_CHECK_HIP(timed(GES_STAGE_DEPTH_SORT, stream, [&] { return ges::launch_depth_sort(db, b, stream); }), "depth_sort");
   GES_CHECK_HIP(timed(GES_STAGE_KEY_SCAN, stream, [&] { return ges::launch_key_scan(db, b, stream); }), "key_scan");
   if (num_keys_host) {
     uint32_t k = 0;
-    GES_CHECK_HIP(ges::mail_wait(mail, b.keys_total, stream, &k), "read num_keys");
-    ges::mail_give(mail);
+    GES_CHECK_HIP(ges::mail_wait(b.mail, b.keys_total, stream, &k), "read num_keys");
+    ges::mail_give(b.mail);
     if (k == 0xffffffffu) {   // no render will follow: the caller may free the workspace, in which the sort still runs
       GES_CHECK_HIP(hipStreamSynchronize(stream), "sync");
       return fail(GES_ERR_CAPACITY, "more than 2^32-2 candidate (tile, splat) pairs in one step");

@@ -220,10 +220,12 @@ class GpuExecutor : public Executor {
     hipStream_t st = streams_[b.stream];
     DeviceBatch* db = reinterpret_cast<DeviceBatch*>(pool + b.table_off);
     Batch bt = make_batch(b, pool);
-    bt.mail = mail_take();
     hipError_t e = hipMemcpyAsync(db, b.host.get(), device_batch_bytes(bt.nviews), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = launch_preprocess(db, bt, st);
-    if (e == hipSuccess) e = launch_depth_sort(db, bt, st);
+    if (e == hipSuccess) {
+      bt.mail = mail_take();
+      e = launch_depth_sort(db, bt, st);
+    }
     if (e == hipSuccess) e = launch_key_scan(db, bt, st);
     uint32_t k = 0;
     if (e == hipSuccess) e = mail_wait(bt.mail, bt.keys_total, st, &k);
