@@ -77,9 +77,10 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def algorithmic_bytes(stage, n, sh_coeffs, K, C, L, px, R=0):
+def algorithmic_bytes(stage, n, sh_coeffs, K, C, L, px, R=0, S=0):
     """Minimum HBM bytes of one launch of an HBM-bound stage: n splats, K keys, C candidate slots, L listed
-    splats, px pixels, R rows stored by the backward raster (the per-unit figures are the comments below)."""
+    splats, px pixels, R rows stored by the backward raster, of S splats (the per-unit figures are the comments
+    below)."""
     splat_in = 12 + 12 + 16 + 4 + 4 + 12 * sh_coeffs
     return {
         # parameters in; record, visibility word, depth key and candidate count out
@@ -95,15 +96,15 @@ def algorithmic_bytes(stage, n, sh_coeffs, K, C, L, px, R=0):
         # the slot marks (1 bit per slot) and every stored row's 10 sums and splat (44 B); the 2-D gradients
         # written (80 B per splat with a row, at most R) are left out, so this is a lower bound
         "row_reduce": C // 8 + 44 * R,
-        # per splat its visibility word in and its gradients out; per listed splat its parameters and its 2-D gradient
-        # in (a splat without a row needs neither, so this is an upper bound of the reads)
-        "preprocess_backward": n * (4 + splat_in) + L * (splat_in + 80),
+        # per splat its visibility word in and its gradients out; per splat with a row its parameters and its 2-D gradient
+        # in
+        "preprocess_backward": n * (4 + splat_in) + S * (splat_in + 80),
         # the row marks cleared before the backward raster
         "zero": C // 8,
         "loss": 37 * px,
         # the preprocess backward with Adam fused in: its inputs, and per parameter the value and both moments in (12 B)
-        # and out (12 B)
-        "preprocess_backward_adam": n * (4 + 6 * splat_in) + L * 80,
+        # and out (12 B); the 2-D gradient in per splat with a row
+        "preprocess_backward_adam": n * (4 + 6 * splat_in) + S * 80,
         # per parameter: read p, g, m, v and write p, m, v (binary32)
         "adam": 28 * n * (3 + 3 + 4 + 1 + 1 + 3 * sh_coeffs),
         # per pixel: forward reads img, target (24 B) and writes 9 maps (36 B); backward reads the maps (36 B),
@@ -143,7 +144,8 @@ def stage_rooflines(per_stage, m, falloff, workload):
             if issued is not None:
                 row["issued_over_algorithmic"] = round(issued * 64 / slots, 3)
         else:
-            nbytes = algorithmic_bytes(stage, m["n"], m["sh_k"], m["K"], m["C"], m["L"], m["px"], m.get("R", 0))
+            nbytes = algorithmic_bytes(stage, m["n"], m["sh_k"], m["K"], m["C"], m["L"], m["px"], m.get("R", 0),
+                                       m.get("S", 0))
             if nbytes is None:
                 continue
             gbs = nbytes / (ms / 1e3) / 1e9
@@ -665,9 +667,11 @@ def fwd_bwd(dev, cfg, falloff, tile_cull, steps, warmup, log_fn):
         raise RuntimeError(f"key capacity overflow during timing: error word {int(st[1])}")
     ms_step_readback = timed(min(steps, 5), True)
     vis = int((fa["records"][:, 15].view(np.uint32) > 0).sum())
+    # splats with a row: those with a gradient (one whose sums are all exactly zero would be missed)
+    with_row = int(torch.stack([g.reshape(s.n, -1).ne(0).any(dim=1) for g in grads.values()]).any(dim=0).sum())
     m = dict(ms_step=ms_step, ms_step_readback=ms_step_readback, host_ms=t_host / steps * 1e3, per_stage=per_stage,
              dominant=dominant, dominant_ms=dom[0] / dom[1], n=s.n, sh_k=(sc.sh_degree + 1) ** 2, K=int(st[0]),
-             C=C, L=vis, px=W * H, R=fa.get("rows_stored", 0), pairs_exam=int(st[2]), pairs_blend=int(st[3]),
+             C=C, L=vis, px=W * H, R=fa.get("rows_stored", 0), S=with_row, pairs_exam=int(st[2]), pairs_blend=int(st[3]),
              bwd_walk=int(fa["n_contrib"].astype(np.int64).sum()),
              max_list=int((fa["ranges"][:, 1].astype(np.int64) - fa["ranges"][:, 0]).max(initial=0)))
     log_fn(f"{W}x{H} n={s.n}: {ms_step:.3f} ms/step, {W * H / ms_step / 1e3:.1f} Mpix/s, K={m['K']} slots={C}, "
