@@ -476,7 +476,8 @@ hipError_t launch_duplicate(DeviceBatch* dbatch, const Batch& b, hipStream_t str
 // 169M slots, 215 for 5M of large splats, 102 for 13.5M and 77 for 3.9M; now 251, 59, 65 and 42.
 constexpr uint32_t kNoItem = 0xffffffffu;
 // More slots than this: ranges of 32 words per wave, as a tenth of the slots of such a frame has a row and a wave should
-// have some tens of them (169M slots 422 -> 251 us; 5M slots of large splats, most with a row, 59 -> 72).
+// have some tens of them.  8 words against 32: 169M slots 422 / 251 us, 35M 138 / 88, 21M 103 / 70; where most slots have a
+// row, 24M 208 / 194, 12M 144 / 152, 6M 95 / 122, 5M of large splats 59 / 72.
 constexpr uint64_t kReduceWide = 1ull << 25;
 constexpr int kReduceRuns = 6;        // runs that are added together, a component per lane
 constexpr int kReduceFew = 2 * kReduceRuns;   // up to so many runs in 64 rows (1M splats: 6 43, 12 42, 24 42 us; 50k: 19, 19, 25)

@@ -124,7 +124,8 @@ struct SortWs {
   uint32_t* table;               // [16][items_blocks][16] per-block digit counts of a pass, then their prefix
   uint32_t* totals;              // [256] per-digit totals of a pass
   unsigned long long* weights;   // [items_blocks] candidate slots of each block's items
-  uint32_t* chunk_off;           // [items / 256 + 1] candidate slots before each 256-item chunk of the depth order
+  uint32_t* chunk_off;           // [items / 256 + 1] candidate slots before each 256-item chunk of the depth order, or,
+                                 // where the chunks are not scanned (chunks_unscanned in binning.hip), of each chunk
   uint32_t* cells;               // [0] listed items, [1] candidate slots (saturating), [2] keys, [3] spare
   int depth_final;               // dv[depth_final] holds the depth order after the last pass
 };
@@ -365,7 +366,6 @@ hipError_t launch_adam(const ges_adam_group* groups, int ngroups, int64_t step, 
 // native 4-float vectors (the float4 class cannot be copied out of another address space).
 typedef float Vec4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const Vec4 GlobalRec;
-typedef __attribute__((address_space(1))) double GlobalF64;
 typedef __attribute__((address_space(1))) Vec4 GlobalVec4;
 typedef __attribute__((address_space(1))) uint32_t GlobalU32;
 

@@ -19,6 +19,7 @@
 // there are blocks enough (radix_shape): 2,048 items (256 threads) up to 2M, 4,096 (512) up to 64M, 16,384 (1,024, one
 // block per CU) beyond.  Tile sort of 169M slots: 2.86 ms with 2,048, 2.54 with 4,096, 2.08 with 16,384; 13.5M slots:
 // 215 / 183 / 242 us (8,192) and 3.9M: 80 / 74 / 82; depth sort of 5M items 220 / 184, 3M 119 / 109, 1M 78 / 84, 200k 59 / 69.
+// The two larger tiles meet at the upper line: 35M slots 428 / 459, 52M 655 / 666, 70M 882 / 876, 104M 1,336 / 1,280.
 // Several tiles per block in turn (a shorter digit table), with or without the next tile's loads ahead, was slower
 // than one.  Within a block the counters are read and added to without waiting between the rounds of 64, the digit's width is
 // a template argument and the pairs reuse the keys' LDS: 262 -> 215 us for the 13.5M slots, 140 -> 120 for the 3M items.

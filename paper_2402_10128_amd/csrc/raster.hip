@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
               G = fast_exp2(kNegHalfLog2e * qb);
             }
             alpha[e] = fminf(kAlphaMax, B[e].z * G);
-}
+          }
           // transmittance behind each splat of the group, a pixel that does not take one keeping its own
           float t[kFwdGroup + 1], a0[kFwdGroup];
           t[0] = T;
@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_forward_kernel(const De
   }
 }
 
-// ---- wave64 sum with DPP: quad swaps, row rotations, then row broadcasts 15 and 31 into lane 63
+// ---- sums with DPP: quad swaps and row rotations
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_add(float x) {
   const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf, false);
@@ -373,16 +373,6 @@ __device__ __forceinline__ float row_sum(float x) {
   x = dpp_add<0x124, 0xf>(x);   // row_ror:4
   x = dpp_add<0x128, 0xf>(x);   // row_ror:8
   return x;
-}
-
-__device__ __forceinline__ float wave_sum_to_63(float x) {
-  x = dpp_add<0xB1, 0xf>(x);    // quad_perm [1,0,3,2]
-  x = dpp_add<0x4E, 0xf>(x);    // quad_perm [2,3,0,1]
-  x = dpp_add<0x124, 0xf>(x);   // row_ror:4
-  x = dpp_add<0x128, 0xf>(x);   // row_ror:8
-  x = dpp_add<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
-  x = dpp_add<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
 // One exchange step of a reduce-scatter inside rows of 16 lanes: the lane pairs with the lane that the
@@ -563,11 +553,6 @@ __global__ void __launch_bounds__(64 * kFwdWaves) raster_recover_kernel(const De
   }
 }
 
-// One block of one wave per work item.  SEGMENTED: an item is a segment of a tile's walk (see
-// backward_prepare_kernel), and a block takes further items in turn; it starts from the transmittance behind the
-// segment and the colour behind it, which are the pixel's final transmittance and nothing where its last
-// composited splat lies in the segment, else what raster_recover_kernel left at the boundary.  Otherwise an item
-// is a whole tile, dealt by ordered_tile or xcd_tile.
 // The bands of 4 pixel rows of the tile at (x0, y0) that a splat may reach (box_may_hit of each).  A wave asks this of 64
 // splats at a time, one per lane, and walks the ones that reach a band, looking at those bands only: 1M splats at
 // 1600x1040 352 -> 336 us, 5M of heavy overlap 1322 -> 1265, 3M at 1920x1080 416 -> 407, four views of 200k at 512x512
@@ -582,6 +567,11 @@ __device__ __forceinline__ uint32_t bands_reached(float u, float v, float a, flo
   return m;
 }
 
+// One block of one wave per work item.  SEGMENTED: an item is a segment of a tile's walk (see
+// backward_prepare_kernel), and a block takes further items in turn; it starts from the transmittance behind the
+// segment and the colour behind it, which are the pixel's final transmittance and nothing where its last
+// composited splat lies in the segment, else what raster_recover_kernel left at the boundary.  Otherwise an item
+// is a whole tile, dealt by ordered_tile or xcd_tile.
 template <int FALLOFF, bool SEGMENTED>
 __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* __restrict__ db,
                                                              const uint2* __restrict__ sorted_pairs,
@@ -617,7 +607,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
     const uint32_t first_pos = item.y * seg, end_pos = SEGMENTED ? first_pos + seg : ~0u;
     float pyf[4], T[4], TfB[4], g[4][3], S[4][3];
     uint32_t last[4];
-  #pragma unroll
+#pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int py = py0 + 4 * k;
       pyf[k] = (float)py;
@@ -637,7 +627,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
       // T_final (bg . g): the background's share of dL/dalpha, divided by (1 - alpha) per splat
       TfB[k] = T[k] * (V.bg[0] * g[k][0] + V.bg[1] * g[k][1] + V.bg[2] * g[k][2]);
     }
-      if constexpr (SEGMENTED) {
+    if constexpr (SEGMENTED) {
       const GlobalRec* ck = (const GlobalRec*)V.ckpt + ((size_t)V.tile_ckpt[lt] + item.y) * kTilePx + lane;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -661,7 +651,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
     asm volatile("" : "+v"(q_floor));
     const float lq_floor = FALLOFF == GES_FALLOFF_GEF ? fast_log2(q_floor) : 0.f;
     uint32_t band_last[4];
-  #pragma unroll
+#pragma unroll
     for (int k = 0; k < 4; ++k) {
       uint32_t m = last[k];
       for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
@@ -683,7 +673,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
       if (lane < nslot) {   // entries 0 .. nslot-1 hold row partials
         const uint32_t slot = sSlot[lane];
         float val[10];
-  #pragma unroll
+#pragma unroll
         for (int c = 0; c < 10; ++c)
           val[c] = (sRed[lane][0][c] + sRed[lane][1][c]) + (sRed[lane][2][c] + sRed[lane][3][c]);
         val[0] = 2.f * val[0];   // dL/du = 2 sum dq (a dx + b dy)
@@ -720,7 +710,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
         reach = bands_reached(a.x, a.y, a.z, a.w, b.x, b.y, (float)(tx * kTile), (float)(ty * kTile));
       }
       uint64_t band[4], walk = 0ull;   // the splats a band has to look at: those before the last of its pixels'
-  #pragma unroll
+#pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint32_t n = band_last[k] > (uint32_t)lo ? band_last[k] - (uint32_t)lo : 0u;
         band[k] = __ballot((reach >> k) & 1u) & (n >= 64u ? ~0ull : (1ull << n) - 1ull);
@@ -740,7 +730,7 @@ __global__ void __launch_bounds__(64) raster_backward_kernel(const DeviceBatch* 
         // (colour) and, for GEF, of dL/dbeta
         float su = 0.f, sv = 0.f, pa = 0.f, pb = 0.f, pc = 0.f, po = 0.f, pr = 0.f, pg = 0.f, pbl = 0.f, pbeta = 0.f;
         bool entered = false;   // wave-uniform: some row band had a pixel that took the splat
-  #pragma unroll
+#pragma unroll
         for (int k = 0; k < 4; ++k) {
           if (!((band[k] >> j) & 1ull)) continue;   // scalar
           float dx, dy;
@@ -986,8 +976,11 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(DeviceBatch* __r
 }
 
 // Cutting pays where the longest walk, at about 0.5 us a splat, outlasts the whole frame's work spread over the
-// device (0.27 ns a walked position); from about 6,000 tiles on it does
-// not (cutting there: 1600x1040 354 -> 457 us, 1920x1080 420 -> 524, heavy overlap 1,366 -> 1,670).
+// device (0.27 ns a walked position).  The host does not know the walks, so the number of tiles stands in for them, and
+// it is a coarse stand-in: what decides is how uneven they are.  Backward without and with the cut, clusters of 200k / 1M
+// splats and 200k in one dense cluster: 4,096 tiles 372 : 266 us, 467 : 420, 2,533 : 727; 5,120 tiles 298 : 266,
+// 371 : 420, 2,141 : 562; 6,144 tiles 256 : 258, 331 : 430, 1,469 : 415; 8,160 tiles 219 : 263, 306 : 452, 1,088 : 333;
+// views of 512x512, 200k, 4 of them 782 : 499, 6 861 : 682, 8 955 : 866.
 static bool cut_walks(const Batch& b) { return b.total_tiles <= 6144; }
 
 hipError_t launch_backward_prepare(DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
@@ -1005,8 +998,9 @@ hipError_t launch_raster_forward(const DeviceBatch* dbatch, const Batch& b, hipS
   const dim3 grid((unsigned)((b.total_tiles + span - 1) / span * span));
   // every view of a batch shares the falloff (the server fixes it per instance).  Splats per group: 4 shorten
   // the serial walk, 2 leave registers for more waves per SIMD, which counts once the frame fills the device
-  // (4 against 2, with the statistics pass: 512x512 153 / 162 us, 801x533 GEF 318 / 361, four views of 512x512
-  // 274 / 274, 1600x1040 209 / 200, 1920x1080 252 / 239, heavy overlap 710 / 678)
+  // (4 against 2, with the statistics pass: 512x512 153 / 162 us, 801x533 GEF 318 / 361; clusters of 1M splats and 200k in
+  // one dense cluster at 4,096 tiles 183 / 177, 649 / 675, at 5,120 170 / 167, 493 / 524, at 6,500 168 / 162, 367 / 392, at
+  // 8,160 165 / 156, 267 / 291; heavy overlap 710 / 678)
   const bool phi = b.falloff != GES_FALLOFF_GEF, few = b.total_tiles <= 4096;   // PHI and PHI_EXACT: Gaussian
   void (*kernel)(const DeviceBatch*, const uint2*, int64_t, uint64_t) =
       phi ? (few ? raster_forward_kernel<GES_FALLOFF_PHI, 4> : raster_forward_kernel<GES_FALLOFF_PHI, 2>)
