@@ -886,13 +886,22 @@ __global__ void __launch_bounds__(1024) raster_stats_kernel(const DeviceBatch* _
   }
 }
 
-// Before the backward raster: the blocks past the first clear the row marks; block 0 plans the walk of a frame
-// that is to be cut (items not NULL).  Its segment is the length that gives about kItemTarget items (a multiple
-// of 64, the backward's staged batch), longer walks are cut there, and every piece is a work item.  Tile groups
+// Before the backward raster: the blocks past the first clear the row marks; block 0 plans the walks of a frame
+// that may be cut (items not NULL).  Cutting pays where the longest walk, at about 0.5 us a splat, outlasts the walks of
+// all tiles spread over the device's 1,024 SIMDs, at about 0.27 ns a position, by a factor of two (kCutShare), and where
+// there are fewer than two tiles a SIMD (kCutTiles); elsewhere
+// a segment is as long as the longest walk, and no tile is cut.  Over 112 frames of 64 to 6,144 tiles and one to six
+// views, from 50k to 2M splats, times without the cut and with it: below the factor, from 3,072 tiles on, 1.09 to 0.71
+// (GEF 150k at 1536x1024 1,433 : 2,023 us, clusters of 1M there 339 : 446), and 820 : 766 for GEF 150k at 801x533 (1,734
+// tiles); from a factor of 2.1 on 1.03 up to 6 (200k in one dense cluster at 1536x1024
+// 1,472 : 415).  A segment that is cut is the length that gives about kItemTarget items (a multiple of 64, the
+// backward's staged batch), and every piece is a work item.  Tile groups
 // (tiles, in a frame of few) go to the XCDs in turn, heaviest walks first where the forward ordered them, so
 // that a group's records meet in one L2 and the last items to start are short; the items of XCD x are
 // items[plan[P_STARTS + x], plan[P_STARTS + x + 1]).  There are at most as many items as walked list positions,
 // and a boundary stands for at least 64 of them, so items and cut tiles fit the buffers of the tile sort.
+constexpr uint32_t kCutShare = 926;   // part of the walks' sum that the longest may have: 2 x 0.27 ns / 0.5 us
+constexpr uint32_t kCutTiles = 2048;
 constexpr uint32_t kOrderTiles = 2048;
 // Targets of 2,560 / 4,096 / 8,192 / 16,384: four views of 512x512 686 / 602 / 561 / 568 us, GEF 300k at 801x533
 // 1,025 / 868 / 864 / 845; smaller frames reach the shortest segment with any.
@@ -913,6 +922,7 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(DeviceBatch* __r
   if (!items) return;
   const Views<PACK> views{db, pack};
   __shared__ unsigned long long wsum[16];
+  __shared__ uint32_t wmax[16];
   __shared__ unsigned long long carry;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const bool one = views.count() == 1;
@@ -923,15 +933,29 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(DeviceBatch* __r
     return (one ? work0 : views[v].tile_work)[t - v * view_tiles];
   };
   unsigned long long sum = 0;   // walked positions
-  for (uint32_t t = threadIdx.x; t < tiles; t += 1024) sum += walk(t);
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) wsum[w] = sum;
+  uint32_t longest = 0;
+  for (uint32_t t = threadIdx.x; t < tiles; t += 1024) {
+    const uint32_t n = walk(t);
+    sum += n;
+    longest = max(longest, n);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    sum += __shfl_xor(sum, off, 64);
+    longest = max(longest, (uint32_t)__shfl_xor((int)longest, off, 64));
+  }
+  if (lane == 0) { wsum[w] = sum; wmax[w] = longest; }
   if (threadIdx.x == 0) carry = 0ull;
   __syncthreads();
   sum = 0;
-  for (int k = 0; k < 16; ++k) sum += wsum[k];
+  for (int k = 0; k < 16; ++k) {
+    sum += wsum[k];
+    longest = max(longest, wmax[k]);
+  }
   __syncthreads();
-  const uint32_t seg = (uint32_t)max(1ull, (sum + 64ull * kItemTarget - 1) / (64ull * kItemTarget)) * 64u;
+  const uint32_t whole = (longest + 63u) / 64u;   // batches of the longest walk
+  const uint32_t piece = (uint32_t)max(1ull, (sum + 64ull * kItemTarget - 1) / (64ull * kItemTarget));
+  const bool cuts = tiles < kCutTiles || (unsigned long long)longest * kCutShare > sum;
+  const uint32_t seg = (cuts ? piece : max(piece, whole)) * 64u;
   // positions of the list order: XCD by XCD, a padded run of groups each; one tile per thread and round
   const uint32_t gs = tiles < kOrderTiles ? 1u : (uint32_t)kXcdGroup;   // tiles dealt to an XCD together
   const uint32_t ngroups = (tiles + gs - 1) / gs, run = (ngroups + 7) / 8 * gs;
@@ -975,12 +999,8 @@ __global__ void __launch_bounds__(1024) backward_prepare_kernel(DeviceBatch* __r
   }
 }
 
-// Cutting pays where the longest walk, at about 0.5 us a splat, outlasts the whole frame's work spread over the
-// device (0.27 ns a walked position).  The host does not know the walks, so the number of tiles stands in for them, and
-// it is a coarse stand-in: what decides is how uneven they are.  Backward without and with the cut, clusters of 200k / 1M
-// splats and 200k in one dense cluster: 4,096 tiles 372 : 266 us, 467 : 420, 2,533 : 727; 5,120 tiles 298 : 266,
-// 371 : 420, 2,141 : 562; 6,144 tiles 256 : 258, 331 : 430, 1,469 : 415; 8,160 tiles 219 : 263, 306 : 452, 1,088 : 333;
-// views of 512x512, 200k, 4 of them 782 : 499, 6 861 : 682, 8 955 : 866.
+// Frames whose walks may be cut (the device decides, see backward_prepare_kernel): up to 6,144 tiles.  Beyond, a frame with
+// one dense cluster would gain too (8,160 tiles 1,088 : 333 us), others lose by the shared segment length (306 : 452).
 static bool cut_walks(const Batch& b) { return b.total_tiles <= 6144; }
 
 hipError_t launch_backward_prepare(DeviceBatch* dbatch, const Batch& b, uint32_t* bits, size_t nwords,
