@@ -253,10 +253,20 @@ def ges_key_workspace_query(num_keys, n, width, height):
     return a.value
 
 
+def _counting_stream(splat_ws, read_num_keys, stream):
+    """``stream``, or the current one.  The slot count arrives while the depth sort still runs there: a workspace that is
+    dropped before the render is not to be handed out for another stream until it has ended."""
+    s = torch.cuda.current_stream() if stream is None else stream
+    if read_num_keys and isinstance(s, torch.cuda.Stream):
+        splat_ws.record_stream(s)
+    return C.c_void_p(s.cuda_stream)
+
+
 def ges_preprocess(splats, cam, params, splat_ws, read_num_keys=True, stream=None):
     k = C.c_uint64(0)
     _check(lib().ges_preprocess(C.byref(splats), C.byref(cam), C.byref(params), _ptr(splat_ws),
-                                splat_ws.numel(), C.byref(k) if read_num_keys else None, _stream(stream)))
+                                splat_ws.numel(), C.byref(k) if read_num_keys else None,
+                                _counting_stream(splat_ws, read_num_keys, stream)))
     return k.value if read_num_keys else None
 
 
@@ -297,7 +307,8 @@ def ges_preprocess_views(splats, cams, params, splat_ws, read_num_keys=True, str
     """cams: list of ges_camera (one resolution).  Returns the batch's slot count when read_num_keys."""
     k = C.c_uint64(0)
     _check(lib().ges_preprocess_views(C.byref(splats), _cams(cams), len(cams), C.byref(params), _ptr(splat_ws),
-                                      splat_ws.numel(), C.byref(k) if read_num_keys else None, _stream(stream)))
+                                      splat_ws.numel(), C.byref(k) if read_num_keys else None,
+                                      _counting_stream(splat_ws, read_num_keys, stream)))
     return k.value if read_num_keys else None
 
 

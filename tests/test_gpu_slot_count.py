@@ -28,3 +28,35 @@ def test_nothing_runs_in_the_workspace_after_a_count_that_is_too_large(n):
             G.ges_preprocess(s, c, p, ws, True)
         idle = torch.cuda.current_stream().query()
         assert e.value.status == 2 and idle
+
+
+def test_a_workspace_dropped_after_the_count_is_not_handed_out_while_the_sort_runs():
+    """The count of 2M splats on a side stream, given or made the current one, then the workspace (allocated for another) is
+    dropped without a render: as long as the side stream works, an allocation of its size gets other memory."""
+    n, W, H = 2_000_000, 256, 256
+    scene = synth.scene_clusters_device(n, 3, torch.device("cuda"), degree=0)
+    s = G.splats_struct(*(scene[k] for k in G.SPLAT_PARAMS))
+    c, p = G.camera_struct(synth.pinhole(W, H, (0.0, 0.0, -8.0))), G.params_struct()
+    size = G.ges_workspace_query(n, W, H)[0]
+    side = torch.cuda.Stream()
+    busy = 0
+    for k in range(20):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        if k % 3 == 0:
+            G.ges_preprocess_views(s, [c], p, ws, True, stream=side)
+        elif k % 3 == 1:
+            G.ges_preprocess(s, c, p, ws, True, stream=side)
+        else:
+            with torch.cuda.stream(side):
+                G.ges_preprocess(s, c, p, ws, True)
+        at = ws.data_ptr()
+        del ws
+        other = torch.empty(size, dtype=torch.uint8, device="cuda")
+        if not side.query():
+            busy += 1
+            assert other.data_ptr() != at
+        del other
+        torch.cuda.synchronize()
+    print(f"[slot count] {busy} of 20 drops while the side stream worked", flush=True)
+    assert busy > 0
